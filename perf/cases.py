@@ -1,0 +1,296 @@
+"""The work that a user of the EBIC fitness evaluation has it do, as timed cases.
+
+Each case goes through the package's public entry points (``Context`` and
+the serving engine) with the default launch shapes. Matrices and populations are
+synthetic, drawn on the GPU from a seed: values of the distributions that
+expression (normal) and methylation (Beta(0.5, 0.5)) data show, with planted
+trend biclusters, and populations as an evolutionary run holds them: a
+quarter of the individuals follow (parts of) a planted trend, the others are
+random ordered column lists.
+
+Kinds of work:
+  eval        one population's counts on a resident matrix (one generation)
+  masks       counts and row masks (what an export of biclusters asks for)
+  generation  counts, then the next generation bred on the device
+  batch       the populations of many runs, in one batched launch
+  new_matrix  a matrix from host memory made resident, and its first counts
+  served      host requests of many runs through the serving engine
+"""
+from __future__ import annotations
+
+import math
+import random
+
+import numpy as np
+import torch
+
+from paper_1807_09932_amd import ebic
+
+FILL = 0.25  # the value a missing cell takes in include mode
+
+
+def _case(name, kind, rows, cols, n, dist="normal", missing=0.0, include=False, negative=True, k_max=30, pops=1):
+    c = {"kind": kind, "rows": rows, "cols": cols, "n": n, "dist": dist, "missing": missing,
+         "include": include, "negative": negative, "k_max": k_max, "pops": pops}
+    return dict(c, name=name) if name else c
+
+
+def listed():
+    return [
+        # The smallest calls: a few launches' latency (a small panel, a small run).
+        _case("eval_1000x50", "eval", 1000, 50, 100, "normal", k_max=8),
+        # An expression matrix with 5% missing cells, in both missing-value modes.
+        _case("eval_missing_exclude_20000x200", "eval", 20000, 200, 800, "normal", missing=0.05, k_max=20),
+        _case("eval_missing_include_20000x200", "eval", 20000, 200, 800, "normal", missing=0.05, include=True, k_max=20),
+        # A methylation array on few samples, and on the paper's own number of samples.
+        _case("eval_436444x64", "eval", 436444, 64, 800, "beta"),
+        _case("eval_436444x310", "eval", 436444, 310, 800, "beta"),
+        # A cohort of many samples: past the widths that the benchmark covers.
+        _case("eval_20000x900", "eval", 20000, 900, 800, "normal"),
+        # The rows of the biclusters found, for export.
+        _case("masks_54675x178", "masks", 54675, 178, 200, "normal"),
+        # A generation of an evolutionary run that stays on the device: a
+        # population of ordinary size, and the largest converged one.
+        _case("generation_54675x178", "generation", 54675, 178, 800, "normal"),
+        _case("generation_12483x150", "generation", 12483, 150, 1600, "normal"),
+        # 64 concurrent runs on one matrix, populations of uneven sizes.
+        _case("batch_100000x256", "batch", 100000, 256, 1600, "normal", k_max=40, pops=64),
+        # A new dataset: upload from host memory and the first evaluation.
+        _case("new_matrix_54675x178", "new_matrix", 54675, 178, 800, "normal"),
+        # 16 runs' requests, two each, through the serving engine.
+        _case("served_50000x200", "served", 50000, 200, 800, "normal", pops=32),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng: random.Random):
+    kind = rng.choice(["eval", "eval", "eval", "masks", "generation", "batch", "new_matrix"])
+    beta = rng.random() < 0.4
+    missing = rng.choice([0.0, 0.0, 0.0, 0.02, 0.05])
+    cols = _log(rng, 8, 1000) if kind in ("eval", "masks") else _log(rng, 8, 400)
+    top = {"eval": 436444, "masks": 100000, "generation": 436444, "batch": 100000, "new_matrix": 100000}[kind]
+    rows = _log(rng, 500, top if cols <= 320 else min(top, 20000 if cols > 512 else 100000))
+    if kind == "new_matrix":
+        rows = min(rows, 54675 * 178 // cols)
+    n = _log(rng, 20, 200 if kind == "masks" else 1600)
+    pops = _log(rng, 2, 32) if kind == "batch" else 1
+    return _case(None, kind, rows, cols, n, "beta" if beta else "normal", missing, bool(missing) and rng.random() < 0.5,
+                 rng.random() < 0.85, rng.choice([8, 20, 30, 40]), pops)
+
+
+# ---------------------------------------------------------------------------
+# Inputs
+# ---------------------------------------------------------------------------
+
+def _values(g, dist, shape):
+    if dist == "beta":  # Beta(0.5, 0.5): the arcsine distribution
+        u = torch.rand(shape, generator=g, device="cuda", dtype=torch.float64)
+        return torch.sin(u * (math.pi / 2)).square_().to(torch.float32)
+    return torch.randn(shape, generator=g, device="cuda", dtype=torch.float32)
+
+
+def _matrix(case, seed):
+    """(X float32 (rows, cols) on the GPU, the planted column orders)."""
+    g = torch.Generator(device="cuda").manual_seed(1000003 * seed + 17)
+    rng = np.random.default_rng([seed, 11])
+    rows, cols = case["rows"], case["cols"]
+    X = _values(g, case["dist"], (rows, cols))
+    perm = torch.randperm(rows, generator=g, device="cuda")
+    plants, at = [], 0
+    for p in range(8):
+        m = int(rng.integers(max(1, rows // 200), max(2, rows // 30)))
+        k = int(rng.integers(min(4, cols), min(12, cols) + 1))
+        order = rng.choice(cols, k, replace=False)
+        v = torch.sort(_values(g, case["dist"], (m, k)), dim=1, descending=bool(p % 2)).values
+        X[perm[at:at + m, None], torch.as_tensor(order, device="cuda")[None, :]] = v
+        at += m
+        plants.append(order)
+    if case["missing"]:
+        X[torch.rand((rows, cols), generator=g, device="cuda") < case["missing"]] = float("nan")
+    return X, plants
+
+
+def _population(case, seed, sub, plants, n):
+    """CSR of n individuals: a quarter follow a planted trend (a part of it,
+    half of those with another column appended), the others are random."""
+    rng = np.random.default_rng([seed, 23, sub])
+    cols, k_max = case["cols"], min(case["k_max"], case["cols"])
+    inds = []
+    for i in range(n):
+        if i % 4 == 0:
+            order = plants[int(rng.integers(len(plants)))]
+            keep = order[: max(2, int(rng.integers(2, order.size + 1)))][:k_max]
+            if rng.random() < 0.5 and keep.size < min(k_max, cols):
+                extra = int(rng.integers(cols))
+                if extra not in keep:
+                    keep = np.append(keep, extra)
+            inds.append(keep)
+        else:
+            inds.append(rng.choice(cols, int(rng.integers(min(2, k_max), k_max + 1)), replace=False))
+    return ebic.pack(inds)
+
+
+def _sizes(case):
+    rng = np.random.default_rng([case["pops"], case["n"], 37])
+    lo = max(1, min(100, case["n"] // 2))
+    return [int(rng.integers(lo, case["n"] + 1)) for _ in range(case["pops"])]
+
+
+class _Owner:
+    """Closes what a state holds when the state goes."""
+
+    def __init__(self, ctx):
+        self.ctx, self.server = ctx, None
+
+    def __del__(self):
+        if self.server is not None:
+            ebic.ebic_server_destroy(self.server)
+        self.ctx.close()
+
+
+def prepare(case, seed):
+    X, plants = _matrix(case, seed)
+    ctx = ebic.Context(0)
+    s = dict(case, owner=_Owner(ctx), ctx=ctx)
+    kind = case["kind"]
+    if kind == "new_matrix":
+        s["X"] = X.cpu().numpy()
+        offs, cols = _population(case, seed, 0, plants, case["n"])
+        s["pop"] = ctx.population(offsets=offs, cols=cols)
+        return s
+    s["mat"] = ctx.upload(X, fill=FILL)
+    del X
+    if kind == "batch":
+        sizes = _sizes(case)
+        s["matched"] = torch.zeros(sum(sizes), dtype=torch.int32, device="cuda")
+        s["negative"] = torch.zeros(sum(sizes), dtype=torch.int32, device="cuda")
+        s["pops_dev"], s["reqs"], at = [], [], 0
+        for p, n in enumerate(sizes):
+            offs, cols = _population(case, seed, p, plants, n)
+            s["pops_dev"].append(ctx.population(offsets=offs, cols=cols))
+            out = (s["matched"][at:at + n], s["negative"][at:at + n], None, None)
+            s["reqs"].append(ctx.request(s["mat"], s["pops_dev"][p], out, case["include"], case["negative"]))
+            at += n
+        return s
+    if kind == "served":
+        s["csr"] = [_population(case, seed, p, plants, n) for p, n in enumerate(_sizes(case))]
+        s["counts"] = [np.zeros((2, offs.size - 1), np.int32) for offs, _ in s["csr"]]
+        s["tags"] = np.zeros(64, np.uint64), np.zeros(64, np.int32)
+        s["server"] = s["owner"].server = ebic.ebic_server_create(ctx.handle, 64 << 20, 4, 256)
+        return s
+    offs, cols = _population(case, seed, 0, plants, case["n"])
+    s["pop"] = ctx.population(offsets=offs, cols=cols)
+    if kind == "generation":
+        n, k_max = case["n"], min(case["k_max"], case["cols"])
+        s["params"] = ebic.ebic_ea_params(case["cols"], n, min(2, k_max), k_max, max(1, n // 20), 0.5, 0.9, seed)
+        s["next"] = (torch.zeros(n + 1, dtype=torch.int32, device="cuda"),
+                     torch.zeros(n * k_max, dtype=torch.int32, device="cuda"),
+                     torch.zeros(1, dtype=torch.int32, device="cuda"))
+    return s
+
+
+def run(s):
+    ctx, kind = s["ctx"], s["kind"]
+    if kind == "batch":
+        ctx.eval_batch(s["reqs"])
+        return s["matched"], s["negative"]
+    if kind == "served":
+        flags = ctx.flags(s["include"], s["negative"])
+        for i, ((offs, cols), out) in enumerate(zip(s["csr"], s["counts"])):
+            ebic.ebic_server_submit(s["server"], s["mat"], offs.size - 1, offs.ctypes.data, cols.ctypes.data, flags,
+                                    out[0].ctypes.data, out[1].ctypes.data, None, None, i)
+        done, (tags, statuses) = 0, s["tags"]
+        while done < len(s["csr"]):
+            k = ebic.ebic_server_poll(s["server"], tags, statuses, 100000)
+            if statuses[:k].any():
+                raise RuntimeError("a served request failed")
+            done += k
+        return s["counts"]
+    if kind == "new_matrix":
+        mat = ctx.upload(s["X"], fill=FILL)
+        m, g, _, _ = ctx.eval(mat, s["pop"], s["include"], s["negative"])
+        ctx.release(mat)
+        return m, g
+    out = ctx.eval(s["mat"], s["pop"], s["include"], s["negative"], masks=kind == "masks")
+    if kind == "masks":
+        return out
+    m, g, _, _ = out
+    if kind == "generation":
+        ctx.breed(s["params"], 1, s["pop"], m, out=s["next"])
+        return (m, g) + s["next"]
+    return m, g
+
+
+def _totals(case):
+    """(individuals, columns of all individuals), on average."""
+    per = case["n"] if case["kind"] not in ("batch", "served") else (max(1, min(100, case["n"] // 2)) + case["n"]) / 2
+    n = per * case["pops"]
+    k = min(case["k_max"], case["cols"])
+    return n, n * (2 + k) / 2
+
+
+def work(case):
+    """The populations read and the outputs written once, and the least that
+    decides the rows: the first comparison of an individual on a row (and,
+    with both trends counted, the second, since the first leaves one trend
+    standing). From the values that is the matrix read once; from comparisons
+    kept with a matrix it is a bit for each, so the smaller of the two."""
+    n, nnz = _totals(case)
+    rows, cols = case["rows"], case["cols"]
+    pairs = (2 if case["negative"] else 1) * n
+    by = min(4 * rows * cols, rows * pairs / 8) + 4 * (n + nnz) + 8 * n
+    if case["kind"] == "masks":
+        by += 16 * n * -(-rows // 64)
+    if case["kind"] == "generation":
+        by += 4 * (n + nnz)
+    if case["kind"] == "new_matrix":
+        by += 8 * rows * cols  # written to the device, then read
+    return {"bytes": by, "flops": rows * pairs}
+
+
+# ---------------------------------------------------------------------------
+# The same outputs from plain torch
+# ---------------------------------------------------------------------------
+
+def _counts(Xt, offs, cols, negative, masks=False):
+    rows = Xt.shape[1]
+    present = ~torch.isnan(Xt)
+    matched, neg, mm, nm = [], [], [], []
+    for i in range(offs.size - 1):
+        c = [int(v) for v in cols[offs[i]:offs[i + 1]]]
+        p = present[c[0]].clone()
+        q = p.clone() if negative else torch.zeros_like(p)
+        for a, b in zip(c, c[1:]):
+            p &= Xt[b] >= Xt[a]
+            q &= Xt[b] <= Xt[a]
+        q &= ~p
+        matched.append((p | q).sum())
+        neg.append(q.sum())
+        if masks:
+            w = torch.zeros((2, -(-rows // 64) * 64), dtype=torch.bool, device=Xt.device)
+            w[0, :rows], w[1, :rows] = p | q, q
+            words = (w.view(2, -1, 64).long() << torch.arange(64, device=Xt.device)).sum(-1)
+            mm.append(words[0])
+            nm.append(words[1])
+    out = (torch.stack(matched).int(), torch.stack(neg).int())
+    return out + (torch.stack(mm), torch.stack(nm)) if masks else out
+
+
+def exact(case, seed):
+    if case["kind"] == "batch" and case["pops"] * case["n"] > 20000:
+        return None  # (minutes of plain torch)
+    X, plants = _matrix(case, seed)
+    Xt = X.t().contiguous()
+    if case["include"]:
+        Xt = torch.where(torch.isnan(Xt), torch.full_like(Xt, FILL), Xt)
+    neg, kind = case["negative"], case["kind"]
+    if kind in ("batch", "served"):
+        got = [_counts(Xt, *_population(case, seed, p, plants, n), neg) for p, n in enumerate(_sizes(case))]
+        if kind == "served":
+            return [torch.stack(v) for v in got]
+        return torch.cat([m for m, _ in got]), torch.cat([g for _, g in got])
+    got = _counts(Xt, *_population(case, seed, 0, plants, case["n"]), neg, kind == "masks")
+    return got + (None, None, None) if kind == "generation" else got
