@@ -143,11 +143,11 @@ class _Owner:
     """Closes what a state holds when the state goes."""
 
     def __init__(self, ctx):
-        self.ctx, self.server = ctx, None
+        self.ctx, self.server, self.destroy = ctx, None, ebic.ebic_server_destroy
 
     def __del__(self):
         if self.server is not None:
-            ebic.ebic_server_destroy(self.server)
+            self.destroy(self.server)
         self.ctx.close()
 
 
