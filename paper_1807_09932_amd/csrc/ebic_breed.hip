@@ -5,12 +5,20 @@
 // stays in device memory. The host driver (ebic_ea_step) applies the same
 // rules to the same streams: both breed the same generation.
 //
-// Populations of up to 1,024 (whose arrays fit LDS) are bred by one
-// workgroup in one launch (k_breed_small). Larger ones take five kernels:
-// fitness; the elites' order (each individual counts the ones ranking
-// before it); one thread per child breeding into a slot of k_max columns;
-// one block turning the lengths into offsets; one thread per child
-// copying its slot into the packed CSR.
+// Children of up to 64 columns are bred by one wave each (k_breed_waves:
+// lane j holds column j, so a membership test is one compare and one
+// ballot), into slots of k_max columns; the same launch ranks the
+// individuals (a wave counts the ones that rank before its own) and copies
+// the elites. A second kernel (k_breed_pack) turns the lengths into offsets
+// and packs the slots into the CSR. Two things remain for the other calls:
+//   - k_breed_small, one workgroup that needs no scratch, for populations of
+//     up to 1,024 (whose arrays fit LDS) where the stream's scratch cannot
+//     be had: under a capture before the scratch exists, or when its
+//     allocation fails; and for those with k_max above 64;
+//   - five kernels for larger populations with k_max above 64: fitness; the
+//     elites' order; one thread per child breeding into its slot; one block
+//     turning the lengths into offsets; one thread per child copying its
+//     slot into the packed CSR.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,7 +32,7 @@ namespace ebic {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kLdsMaxK = 64;  // children built in LDS up to this k_max (64 KB per block)
+constexpr int kRankTile = 2048;  // fitnesses staged per LDS tile (16 KB)
 
 __global__ void k_breed_fitness(int32_t n, const int32_t *__restrict__ offsets, const int32_t *__restrict__ matched,
                                 double *__restrict__ f)
@@ -58,21 +66,16 @@ __global__ void __launch_bounds__(kThreads) k_breed_order(int32_t n, const doubl
     if (r == 0 && best) *best = i;
 }
 
-// Child c into slots[c k_max ...], its length into lens[c]. The child is
-// built in LDS (element j of the block's thread t at j * blockDim + t, so
-// the membership scans cost LDS reads instead of dependent global ones)
-// when `in_lds`, else in its global slot directly.
+// Child c (of more than 64 columns at most) into slots[c k_max ...], its
+// length into lens[c].
 __global__ void __launch_bounds__(kThreads) k_breed_children(ebic_ea_params p, int64_t generation, int32_t n,
                                  const int32_t *__restrict__ offsets, const int32_t *__restrict__ cols,
                                  const double *__restrict__ f, const int32_t *__restrict__ order,
-                                 int32_t *__restrict__ slots, int32_t *__restrict__ lens, int32_t in_lds)
+                                 int32_t *__restrict__ slots, int32_t *__restrict__ lens)
 {
-    extern __shared__ int32_t lds_child[];
     const int32_t c = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     if (c >= n) return;
-    int32_t *slot = slots + (int64_t)c * p.k_max;
-    const breed::Strided child = in_lds ? breed::Strided{lds_child + threadIdx.x, (int32_t)blockDim.x}
-                                        : breed::Strided{slot, 1};
+    const breed::Strided child{slots + (int64_t)c * p.k_max, 1};
     int32_t len;
     if (c < p.elite) {  // the elites, best first, carried over unchanged
         const int32_t e = order[c];
@@ -83,8 +86,6 @@ __global__ void __launch_bounds__(kThreads) k_breed_children(ebic_ea_params p, i
         breed::Strided buf = child;
         len = breed::breed_child(p, rng, n, offsets, cols, f, buf);
     }
-    if (in_lds)
-        for (int32_t j = 0; j < len; ++j) slot[j] = child[j];
     lens[c] = len;
 }
 
@@ -123,6 +124,219 @@ __global__ void k_breed_compact(int32_t n, int32_t k_max, const int32_t *__restr
     const int32_t o = offsets[c], len = offsets[c + 1] - o;
     const int32_t *src = slots + (int64_t)c * k_max;
     for (int32_t j = 0; j < len; ++j) cols[o + j] = src[j];
+}
+
+// ---------------------------------------------------------------------------
+// One wave per child (k_max <= 64): lane j holds column j of the child. The
+// functions follow ebic_breed.h step by step and draw in the same order, so
+// the children are the same; every lane draws the same numbers.
+// ---------------------------------------------------------------------------
+struct WaveChild {
+    int32_t col;   // lane j: column j (any value for j >= len)
+    int32_t len;   // wave-uniform
+    int32_t lane;
+    __device__ bool contains(int32_t c) const { return __ballot(lane < len && col == c) != 0; }
+    __device__ void append(int32_t c)
+    {
+        if (lane == len) col = c;
+        ++len;
+    }
+};
+
+__device__ __forceinline__ int32_t wave_unused(const ebic_ea_params &p, breed::Rng &rng, const WaveChild &w)
+{
+    int32_t c;
+    do c = (int32_t)rng.below((uint32_t)p.n_cols);
+    while (w.contains(c));
+    return c;
+}
+
+__device__ __forceinline__ void wave_random(const ebic_ea_params &p, breed::Rng &rng, WaveChild &w)
+{
+    const int32_t k = p.k_min + (int32_t)rng.below((uint32_t)(p.k_max - p.k_min + 1));
+    w.len = 0;
+    while (w.len < k) w.append(wave_unused(p, rng, w));
+}
+
+// lane j: columns j of parents a (ca, ka) and b (cb, kb)
+__device__ __forceinline__ void wave_crossover(const ebic_ea_params &p, breed::Rng &rng, int32_t ca, int32_t ka,
+                                               int32_t cb, int32_t kb, WaveChild &w)
+{
+    const int32_t cut = ka > 1 ? 1 + (int32_t)rng.below((uint32_t)ka - 1) : 1;
+    const int32_t from = (int32_t)rng.below((uint32_t)kb);
+    w.col = ca;
+    w.len = min(cut, ka);
+    for (int32_t j = from; j < kb && w.len < p.k_max; ++j) {
+        const int32_t c = __builtin_amdgcn_readlane(cb, j);
+        if (!w.contains(c)) w.append(c);
+    }
+    while (w.len < p.k_min) w.append(wave_unused(p, rng, w));
+}
+
+__device__ __forceinline__ void wave_mutate(const ebic_ea_params &p, breed::Rng &rng, WaveChild &w)
+{
+    const int32_t k = w.len;
+    const uint32_t op = rng.below(4);
+    if (op == 0 && k < p.k_max && k < p.n_cols) {  // insert
+        const int32_t c = wave_unused(p, rng, w);
+        const int32_t at = (int32_t)rng.below((uint32_t)k + 1);
+        const int32_t before = __shfl(w.col, max(w.lane - 1, 0));
+        w.col = w.lane > at ? before : w.lane == at ? c : w.col;
+        w.len = k + 1;
+    } else if (op == 1 && k > p.k_min) {  // delete
+        const int32_t at = (int32_t)rng.below((uint32_t)k);
+        const int32_t after = __shfl(w.col, min(w.lane + 1, kWave - 1));
+        if (w.lane >= at) w.col = after;
+        w.len = k - 1;
+    } else if (op == 2 && k >= 2) {  // swap
+        const int32_t a = (int32_t)rng.below((uint32_t)k), b = (int32_t)rng.below((uint32_t)k);
+        const int32_t va = __shfl(w.col, a), vb = __shfl(w.col, b);
+        w.col = w.lane == a ? vb : w.lane == b ? va : w.col;
+    } else if (k < p.n_cols) {  // substitute
+        const int32_t c = wave_unused(p, rng, w);
+        if (w.lane == (int32_t)rng.below((uint32_t)k)) w.col = c;
+    }
+}
+
+// Ranks and elites (the first `rank_blocks` blocks) and the bred children
+// (the others), four waves per block. Nothing is passed between the two, so
+// they run side by side.
+//
+// A rank block stages the population's fitnesses tile by tile in LDS; each
+// of its waves counts, for I individuals, the ones that rank before (64 per
+// step, counted by ballot). An individual of rank r < elite is child r.
+// I = 1 up to 8,192 individuals: a block per four individuals, so that even
+// 800 of them fill 200 CUs; eight past that, where the staging of every
+// fitness by every block would cost more than the counting.
+//
+// A child's wave reads both tournaments' individuals in one round, its
+// parents' columns in a second, and stores its slot. Bound by that chain of
+// loads and by the draws (a 64-bit multiply chain). At 1,600 individuals of
+// 2-30 columns ranks, elites and children took 4.6 + 97 + 63 us as three
+// launches (a thread per individual) and now take 7.5 us; at 800 the
+// one-workgroup kernel took 76-107 us against 5.6 us.
+template <int I>
+__global__ void __launch_bounds__(kThreads) k_breed_waves(ebic_ea_params p, int64_t generation, int32_t n,
+                                                          const int32_t *__restrict__ offsets,
+                                                          const int32_t *__restrict__ cols,
+                                                          const int32_t *__restrict__ matched, int32_t rank_blocks,
+                                                          int32_t *__restrict__ slots, int32_t *__restrict__ lens,
+                                                          int32_t *__restrict__ best)
+{
+    __shared__ double ft[kRankTile];
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x / kWave);
+    constexpr int32_t waves = kThreads / kWave;
+    auto fit = [&](int32_t j) { return breed::fitness(matched[j], offsets[j + 1] - offsets[j]); };
+    if ((int32_t)blockIdx.x < rank_blocks) {
+        const int32_t i0 = ((int32_t)blockIdx.x * waves + wave) * I;
+        double fi[I];
+        int32_t r[I];
+#pragma unroll
+        for (int s = 0; s < I; ++s) {
+            fi[s] = fit(min(i0 + s, n - 1));
+            r[s] = 0;
+        }
+        for (int32_t j0 = 0; j0 < n; j0 += kRankTile) {
+            const int32_t m = min(kRankTile, n - j0);
+            if (j0) __syncthreads();
+            // (padded to whole waves with entries that rank before nothing)
+            for (int32_t j = (int32_t)threadIdx.x; j < (m + kWave - 1) / kWave * kWave; j += kThreads)
+                ft[j] = j < m ? fit(j0 + j) : -HUGE_VAL;
+            __syncthreads();
+            for (int32_t j = lane; j - lane < m; j += kWave) {
+                const double fj = ft[j];
+                const int32_t at = j < m ? j0 + j : INT32_MAX;
+#pragma unroll
+                for (int s = 0; s < I; ++s)
+                    r[s] += (int32_t)__popcll(__ballot(breed::ranks_before(fj, at, fi[s], i0 + s)));
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < I; ++s) {
+            const int32_t i = i0 + s;
+            if (i >= n) continue;
+            if (r[s] == 0 && best && lane == 0) *best = i;
+            if (r[s] < p.elite) {  // the elites, best first, carried over unchanged
+                const int32_t len = breed::parent_len(p, offsets, i);
+                if (lane < len) slots[(int64_t)r[s] * p.k_max + lane] = cols[offsets[i] + lane];
+                if (lane == 0) lens[r[s]] = len;
+            }
+        }
+        return;
+    }
+    const int32_t c = p.elite + ((int32_t)blockIdx.x - rank_blocks) * waves + wave;
+    if (c >= n) return;
+    breed::Rng rng = breed::stream(p.seed, generation, n, c);
+    // The draws up to the crossover's own do not depend on the individuals:
+    // both tournaments' are made first, so that their loads go out together.
+    const int32_t a0 = (int32_t)rng.below((uint32_t)n), a1 = (int32_t)rng.below((uint32_t)n);
+    const bool cross = rng.uniform() < p.p_crossover;
+    int32_t b0 = a0, b1 = a1;
+    if (cross) {
+        b0 = (int32_t)rng.below((uint32_t)n);
+        b1 = (int32_t)rng.below((uint32_t)n);
+    }
+    // lane 0..3: the four drawn individuals' spans and fitnesses
+    const int32_t who = lane == 0 ? a0 : lane == 1 ? a1 : lane == 2 ? b0 : b1;
+    const int32_t start = offsets[who], k = offsets[who + 1] - start;
+    const double f = breed::fitness(matched[who], k);
+    auto wins = [&](int x, int32_t ix, int32_t iy) {  // the first of lanes x, x + 1 (individuals ix, iy)?
+        const double fx = __shfl(f, x), fy = __shfl(f, x + 1);
+        return fx > fy || (fx == fy && ix <= iy);
+    };
+    const int la = __builtin_amdgcn_readfirstlane(wins(0, a0, a1) ? 0 : 1);
+    const int lb = __builtin_amdgcn_readfirstlane(wins(2, b0, b1) ? 2 : 3);
+    const int32_t ka = min(__builtin_amdgcn_readlane(k, la), p.k_max);
+    const int32_t sa = __builtin_amdgcn_readlane(start, la);
+    const int32_t kb = min(__builtin_amdgcn_readlane(k, lb), p.k_max);
+    const int32_t sb = __builtin_amdgcn_readlane(start, lb);
+    const int32_t ca = lane < ka ? cols[sa + lane] : 0;
+    const int32_t cb = cross && lane < kb ? cols[sb + lane] : 0;
+    WaveChild w{ca, ka, lane};
+    if (ka <= 0 || (cross && kb <= 0)) wave_random(p, rng, w);
+    else if (cross) wave_crossover(p, rng, ca, ka, cb, kb, w);
+    if (rng.uniform() < p.p_mutation) wave_mutate(p, rng, w);
+    if (lane < w.len) slots[(int64_t)c * p.k_max + lane] = w.col;
+    if (lane == 0) lens[c] = w.len;
+}
+
+// Lengths to offsets and slots to the packed CSR: block b takes `per` (at
+// most 64) children; its threads sum the lengths before them, each wave
+// scans the block's own, and the waves copy the children in turn. Every
+// block sums the lengths from the start (6 KB at 1,600 individuals): one
+// launch of 3.9 us instead of a scan and a copy (4.8 + 6.1 us) at 1,600.
+__global__ void __launch_bounds__(kThreads) k_breed_pack(int32_t n, int32_t k_max, int32_t per,
+                                                         const int32_t *__restrict__ slots,
+                                                         const int32_t *__restrict__ lens,
+                                                         int32_t *__restrict__ offsets, int32_t *__restrict__ cols)
+{
+    constexpr int32_t waves = kThreads / kWave;
+    __shared__ int32_t part[waves];
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x / kWave);
+    const int32_t c0 = (int32_t)blockIdx.x * per, m = min(per, n - c0);
+    const int32_t own = lane < m ? lens[c0 + lane] : 0;
+    int32_t before = 0;
+#pragma unroll 4
+    for (int32_t j = (int32_t)threadIdx.x; j < c0; j += kThreads) before += lens[j];
+    for (int d = kWave / 2; d; d >>= 1) before += __shfl_xor(before, d);
+    if (lane == 0) part[wave] = before;
+    int32_t end = own;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int32_t v = __shfl_up(end, d);
+        if (lane >= d) end += v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < waves; ++v) end += part[v];
+    if (wave == 0 && lane < m) offsets[c0 + lane + 1] = end;
+    if (blockIdx.x == 0 && threadIdx.x == 0) offsets[0] = 0;
+#pragma unroll 4
+    for (int32_t t = wave; t < m; t += waves) {
+        const int32_t len = __builtin_amdgcn_readlane(own, t), at = __builtin_amdgcn_readlane(end, t) - len;
+        if (lane < len) cols[at + lane] = slots[(int64_t)(c0 + t) * k_max + lane];
+    }
 }
 
 // The whole breeding of a population of at most 1,024 in one workgroup of
@@ -226,14 +440,62 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
         const int32_t n = n_ind;
         const int32_t ne = std::max(p.elite, 1);
         DeviceGuard g(ctx->device);
+        const size_t l_bytes = ((size_t)n * sizeof(int32_t) + 255) / 256 * 256;
+        const size_t s_bytes = (size_t)n * p.k_max * sizeof(int32_t);
         // Up to 1,024 individuals whose fitness, elite order and children
-        // fit LDS: one workgroup does it all.
+        // fit LDS can be bred by one workgroup without scratch.
         const int32_t T = (n + kWave - 1) / kWave * kWave;
         int32_t n2 = 1;
         while (n2 < n) n2 <<= 1;
         const size_t small_lds = (size_t)n2 * (2 * sizeof(double) + sizeof(int32_t)) +
                                  (size_t)T * p.k_max * sizeof(int32_t);
-        if (n <= 1024 && small_lds + 1024 * sizeof(int32_t) <= ctx->lds_per_block) {
+        const bool small = n <= 1024 && small_lds + 1024 * sizeof(int32_t) <= ctx->lds_per_block;
+        // Scratch and launches go out together: the stream's scratch is
+        // shared with the evaluations on it.
+        std::lock_guard<std::mutex> lk(ctx->launch_mu);
+        if (p.k_max <= kWave) {
+            unsigned char *base = nullptr;
+            if (small && stream_scratch_grows(ctx, s, l_bytes + s_bytes)) {
+                // A capture cannot wait for the stream, and a population of
+                // this size never needed memory: without it, one workgroup.
+                hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+                const bool free = hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+                clear_last_error();
+                try {
+                    if (free) base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes));
+                } catch (const Error &e) {
+                    if (e.code != EBIC_ENOMEM) throw;
+                }
+            } else {
+                base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes));
+            }
+            if (base) {
+                int32_t *lens = reinterpret_cast<int32_t *>(base);
+                int32_t *slots = reinterpret_cast<int32_t *>(base + l_bytes);
+                fault_point_launch(ctx, "breeding launch");
+                constexpr int32_t waves = kThreads / kWave;
+                const bool one = n <= 8192;
+                const int32_t rank_blocks = one ? (n + waves - 1) / waves : (n + waves * 8 - 1) / (waves * 8);
+                const int32_t blocks = rank_blocks + (n - p.elite + waves - 1) / waves;
+                clear_last_error();
+                if (one)
+                    hipLaunchKernelGGL(k_breed_waves<1>, dim3(blocks), dim3(kThreads), 0, s, p, generation, n, d_offsets,
+                                       d_cols, d_matched, rank_blocks, slots, lens, d_best);
+                else
+                    hipLaunchKernelGGL(k_breed_waves<8>, dim3(blocks), dim3(kThreads), 0, s, p, generation, n, d_offsets,
+                                       d_cols, d_matched, rank_blocks, slots, lens, d_best);
+                // 16 children per block up to 4,096 (a hundred blocks at
+                // 1,600); 64 past that, where summing the lengths from the
+                // start is most of a block's work.
+                const int32_t per = n <= 4096 ? 16 : kWave;
+                hip_check(hipGetLastError(), "breeding kernel");
+                hipLaunchKernelGGL(k_breed_pack, dim3((n + per - 1) / per), dim3(kThreads), 0, s, n, p.k_max, per, slots,
+                                   lens, d_next_offsets, d_next_cols);
+                hip_check(hipGetLastError(), "breeding kernels");
+                return;
+            }
+        }
+        if (small) {
             fault_point_launch(ctx, "breeding launch");
             hip_check(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_breed_small),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds),
@@ -247,8 +509,6 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
         // Scratch on the stream: fitness | elite order | lengths | child slots.
         const size_t f_bytes = (size_t)n * sizeof(double);
         const size_t o_bytes = ((size_t)ne * sizeof(int32_t) + 255) / 256 * 256;
-        const size_t l_bytes = ((size_t)n * sizeof(int32_t) + 255) / 256 * 256;
-        const size_t s_bytes = (size_t)n * p.k_max * sizeof(int32_t);
         auto *base = static_cast<unsigned char *>(stream_scratch(ctx, s, f_bytes + o_bytes + l_bytes + s_bytes));
         double *f = reinterpret_cast<double *>(base);
         int32_t *order = reinterpret_cast<int32_t *>(base + f_bytes);
@@ -260,11 +520,9 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
         hipLaunchKernelGGL(k_breed_fitness, dim3(blocks), dim3(kThreads), 0, s, n, d_offsets, d_matched, f);
         clear_last_error();
         hipLaunchKernelGGL(k_breed_order, dim3(blocks), dim3(kThreads), 0, s, n, f, ne, order, d_best);
-        const int32_t in_lds = p.k_max <= kLdsMaxK ? 1 : 0;
         clear_last_error();
-        hipLaunchKernelGGL(k_breed_children, dim3(blocks), dim3(kThreads),
-                           in_lds ? (size_t)kThreads * p.k_max * sizeof(int32_t) : 0, s, p, generation, n,
-                           d_offsets, d_cols, f, order, slots, lens, in_lds);
+        hipLaunchKernelGGL(k_breed_children, dim3(blocks), dim3(kThreads), 0, s, p, generation, n, d_offsets, d_cols,
+                           f, order, slots, lens);
         clear_last_error();
         hipLaunchKernelGGL(k_breed_offsets, dim3(1), dim3(1024), 0, s, n, lens, d_next_offsets);
         clear_last_error();

@@ -600,6 +600,13 @@ void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes)
     return sc.ptr;
 }
 
+bool stream_scratch_grows(ebic_ctx *ctx, hipStream_t s, size_t bytes)
+{
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    auto it = ctx->scratch.find(s);
+    return it == ctx->scratch.end() || !it->second.ptr || it->second.bytes < bytes;
+}
+
 hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &cfg, hipStream_t s)
 {
     int32_t mode;
@@ -609,6 +616,7 @@ hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &cfg
         mode = ctx->prof_mode;
         if (mode & 2) counter = ctx->d_step_counter;
     }
+    std::lock_guard<std::mutex> lkl(ctx->launch_mu);
     IndHead *heads = static_cast<IndHead *>(stream_scratch(ctx, s, (size_t)d.n * sizeof(IndHead)));
     fault_point_launch(ctx, "evaluation launch");
     if (log_level() >= 3)

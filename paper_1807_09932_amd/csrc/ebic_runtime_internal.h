@@ -90,6 +90,9 @@ struct ebic_ctx {
     std::mutex batch_mu;  // guards the batch graph cache (captures run outside it)
     bool batch_state_allocated = false;
     std::map<hipStream_t, ebic::Scratch> scratch;
+    // Held while a call takes its stream's scratch and enqueues the kernels
+    // that share it: calls of several threads on one stream do not mix.
+    std::mutex launch_mu;
     // Diagnostics (ebic_set_profiling / ebic_read_profile).
     int32_t prof_mode = 0;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
@@ -245,6 +248,8 @@ ReqDesc make_desc(const Matrix &m, int32_t n, const int32_t *offsets, const int3
 // At least `bytes` of device scratch private to stream `s` (grown on demand;
 // a grown buffer replaces the old one after the stream has drained).
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes);
+// Whether stream_scratch(ctx, s, bytes) would allocate.
+bool stream_scratch_grows(ebic_ctx *ctx, hipStream_t s, size_t bytes);
 // The upload's two pinned host buffers, at least `bytes` each (under mu).
 void upload_pinned(ebic_ctx *ctx, size_t bytes);
 // Copy rows [r0, r0 + nr) of a host matrix (row-major with row stride
