@@ -271,7 +271,9 @@ ebic_status ebic_autotune(ebic_ctx *ctx, const ebic_request *sample, int32_t n_r
  *                          byte codes, 16 for counts only)
  *   waves_per_block:       1 .. 16
  *   individuals_per_group: individuals that share one block's staged tiles
- *   staging:               0 = column tiles staged in LDS, 1 = direct reads,
+ *   staging:               0 = column tiles staged in LDS, 1 = direct reads
+ *                              (256-row chunks; tiles_per_wave and blocks
+ *                              ignored),
  *                          2 = the rank codes staged in LDS (2 or 4 sub-tiles;
  *                              include mode needs EBIC_KEEP_FILL_COPY),
  *                          3 = the byte rank codes staged in LDS (4, 8 or 16
@@ -317,7 +319,7 @@ ebic_status ebic_set_launch_shape(ebic_ctx *ctx, int32_t tiles_per_wave, int32_t
  * 2 = rank codes in LDS, 3 = byte rank codes in LDS, 4 = 16-bit rank codes in
  * LDS, 5 = 10-bit rank codes in LDS, 6 = the pair bitmaps (the staging
  * planned for exclude mode; for staging 6, blocks reports the 2,048-row
- * chunks).
+ * chunks, for staging 1 the 256-row chunks).
  */
 ebic_status ebic_plan_shape(ebic_ctx *ctx, int32_t matrix, int32_t n_ind, int64_t nnz,
                             int32_t *tiles_per_wave, int32_t *waves_per_block,

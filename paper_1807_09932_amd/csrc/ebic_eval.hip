@@ -2552,7 +2552,7 @@ const void *eval_pick(int L, bool neg, int staging)
     if (staging == STAGE_CODES) return neg ? eval_pick_codes<true, COUNT>(L) : eval_pick_codes<false, COUNT>(L);
     if (staging == STAGE_LDS)
         return neg ? eval_pick_L<true, STAGE_LDS, COUNT>(L) : eval_pick_L<false, STAGE_LDS, COUNT>(L);
-    return neg ? eval_pick_L<true, STAGE_DIRECT, COUNT>(L) : eval_pick_L<false, STAGE_DIRECT, COUNT>(L);
+    return nullptr;  // (direct reads and the pair bitmaps have kernels of their own)
 }
 
 const void *eval_kernel(int L, uint32_t flags, int staging, bool count)
@@ -2656,6 +2656,12 @@ hipError_t launch_eval(const ReqDesc &d, IndHead *heads, const LaunchCfg &cfg,
         if (e != hipSuccess) return e;
         if (ev1) e = hipEventRecord(ev1, s);
         return e;
+    }
+    if (cfg.staging == STAGE_DIRECT) {
+        hipError_t e;
+        if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;
+        if ((e = launch_direct(d, heads, cfg.P, cfg.W, step_counter, s)) != hipSuccess) return e;
+        return ev1 ? hipEventRecord(ev1, s) : hipSuccess;
     }
     // Four words per row group make counts only (no mask outputs).
     if (cfg.L == 16 && (d.mmask || d.nmask)) return hipErrorInvalidValue;

@@ -193,6 +193,12 @@ hipError_t launch_eval(const ReqDesc &d, IndHead *heads, const LaunchCfg &cfg,
                        unsigned long long *step_counter, hipStream_t s,
                        hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
+// The evaluation kernel on direct reads (ebic_direct.hip): groups of P
+// individuals over blocks of W waves, 256-row chunks.
+int64_t direct_chunks(int64_t rows);
+hipError_t launch_direct(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,
+                         unsigned long long *step_counter, hipStream_t s);
+
 // The no-allocation evaluation's header buffer: a fixed device array of
 // kNoAllocMaxInd headers per device. noalloc_scratch_init (called with
 // `device` current, once per device, at context creation) looks up its

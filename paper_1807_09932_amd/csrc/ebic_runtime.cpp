@@ -325,6 +325,7 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
     else cfg = tuned_cfg(ctx, m.dev.rows, m.dev.cols, n, nnz);
     const size_t lds_max = ctx->lds_per_block;
     const int32_t asked_P = cfg.P;  // (pairs: 0 = chosen here)
+    const bool asked_direct = cfg.staging == STAGE_DIRECT;
     cfg.P = std::max(1, std::min(cfg.P, std::max(1, n)));
     auto lds = [&](const LaunchCfg &c) { return item_lds_bytes(c.L, m.dev.cols, c.staging, c.P); };
     auto fits = [&](const LaunchCfg &c) { return lds(c) <= lds_max; };
@@ -419,6 +420,22 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
     if (cfg.staging == STAGE_CODES && !fits(cfg)) cfg.staging = STAGE_LDS;
     while (cfg.staging == STAGE_LDS && cfg.L > 1 && !fits(cfg)) cfg.L /= 2;
     if (cfg.staging == STAGE_LDS && !fits(cfg)) cfg.staging = STAGE_DIRECT;
+    if (cfg.staging == STAGE_DIRECT) {
+        // (no tile and no LDS: a block per 256-row chunk and group)
+        const int64_t chunks = direct_chunks(m.dev.rows);
+        if (!asked_direct || asked_P <= 0) {
+            // Four waves per block; four individuals per wave where that
+            // leaves a wave for every resident slot, else two (a wave loads
+            // two together): 20,000 x 900, 800 individuals 33.3 and 31.5 us
+            // with two and four, 100 individuals 12.1 and 12.6 us.
+            const int64_t slots = (int64_t)ctx->cu_count * 32;
+            cfg.W = 4;
+            cfg.P = std::min(cfg.W * ((int64_t)n * chunks >= 4 * slots ? 4 : 2), std::max(1, n));
+        }
+        cfg.L = 1;
+        cfg.blocks = (int32_t)chunks;  // (reported)
+        return cfg;
+    }
     while (!fits(cfg) && cfg.P > 64) cfg.P /= 2;
     const int64_t n_tiles = (m.dev.rows + 63) / 64;
     const int32_t granule = cfg.staging == STAGE_BYTES && cfg.L == 16 ? 8 : cfg.L;  // (as the kernel cuts ranges)

@@ -85,6 +85,14 @@ LaunchCfg default_codes_cfg(int64_t rows, int32_t cols, int32_t n)
         c.staging = STAGE_T10;
         c.L = 3;
         c.P = std::max(1, std::min(n, 400));
+    } else {
+        // Direct reads (their waves and groups chosen at planning, P = 0):
+        // 20,000 x 520 takes 55 us an evaluation from the FP32 tile, which
+        // leaves one block per CU, and 31 us here.
+        c.staging = STAGE_DIRECT;
+        c.L = 1;
+        c.W = 4;
+        c.P = 0;
     }
     c.blocks = 0;
     return c;
@@ -404,10 +412,12 @@ ebic_status ebic_autotune(ebic_ctx *ctx, const ebic_request *sample, int32_t n_r
                                             (int)STAGE_BYTES, (int)STAGE_HALVES, (int)STAGE_T10}) {
                                 if ((L == 3 || L == 6) != (stg == STAGE_T10)) continue;  // 10-bit codes: 3 or 6
                                 if (stg == STAGE_T10 && !have_t10) continue;
+                                if (stg == STAGE_DIRECT && L > 1) continue;  // (no sub-tiles)
                                 LaunchCfg c;
                                 c.L = L;
                                 c.W = W;
-                                c.P = std::min(P, r.n_ind);
+                                // (direct reads: 2, 4, 8 or 16 individuals per wave)
+                                c.P = std::min(stg == STAGE_DIRECT ? P / 100 * W : P, r.n_ind);
                                 c.staging = stg;
                                 if (stg != STAGE_DIRECT &&
                                     item_lds_bytes(L, cols, stg, c.P,
