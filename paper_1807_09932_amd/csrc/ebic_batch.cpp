@@ -7,9 +7,10 @@
 // kernel's stagings. Tiled requests become work items (individual group x
 // tile range), ordered largest first, which the persistent tiled kernel's
 // blocks take from a device-side counter. Pair requests are grouped by the
-// bitmap set they read (a segment); per XCD slice of 2,048-row chunks, the
-// fixed-grid pairs kernel walks each segment's chunks in order, all of its
-// groups on a chunk before the next, with a static stride (no counter). The
+// bitmap set they read (a segment); per XCD slice of 1,024-row panels, the
+// fixed-grid pairs kernel walks each segment's panels in order, all of its
+// groups on a panel before the next (with a static stride, or from a counter
+// where a list is long). The
 // planner writes a batch arena (header, request descriptors, prefix sums of
 // individuals, the pair lists and segments, the tiled items) into pinned
 // host memory. A graph captured once per (stream, launch shapes, capacity)
@@ -43,7 +44,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // Header, request descriptors, prefix sums of individuals, the pair lists
 // and segments (requests on pair bitmaps), then the tiled items.
 struct ArenaLayout {
-    size_t hdr = 0, descs = 0, first = 0, pq = 0, segs = 0, seg_req = 0, seg_gstart = 0, items = 0, bytes = 0;
+    size_t hdr = 0, descs = 0, first = 0, pq = 0, segs = 0, seg_req = 0, seg_gstart = 0, items = 0, next = 0, bytes = 0;
     ArenaLayout(int32_t n_req, int32_t n_items)
     {
         hdr = 0;
@@ -54,7 +55,8 @@ struct ArenaLayout {
         seg_req = align256(segs + sizeof(PairSeg) * (size_t)n_req);
         seg_gstart = align256(seg_req + sizeof(int32_t) * (size_t)n_req);
         items = align256(seg_gstart + sizeof(int32_t) * (size_t)n_req);
-        bytes = align256(items + sizeof(Item) * (size_t)n_items);
+        next = align256(items + sizeof(Item) * (size_t)n_items);  // (on the device only: not copied)
+        bytes = next + kPairNextBytes;
     }
 };
 
@@ -330,19 +332,19 @@ static Plan plan_batch(ebic_ctx *ctx, const ebic_request *reqs, int32_t n_reqs, 
 
     // The pair requests: segments by bitmap set (requests in order), groups
     // of pP individuals, and per XCD slice the items of each segment (its
-    // chunks of that slice x its groups).
+    // panels of that slice x its groups).
     {
-        int64_t ind_chunks = 0;
+        int64_t ind_panels = 0;
         for (int32_t q = 0; q < n_reqs; ++q)
             if (p.stagings[q] == STAGE_PAIRS && p.descs[q].n > 0)
-                ind_chunks += (int64_t)p.descs[q].n * ((p.descs[q].rows + 2047) / 2048);
-        if (p.pairs_shape && ind_chunks > 0) {
+                ind_panels += (int64_t)p.descs[q].n * pair_panels(p.descs[q].rows);
+        if (p.pairs_shape && ind_panels > 0) {
             if (p.pP <= 0) {
-                // individuals per wave: up to 8 where the work gives at least
-                // two waves per resident slot, at least 2 (an item's lookup
-                // costs about what one individual's chunk does)
-                const int64_t slots = (int64_t)ctx->cu_count * 32;
-                p.pP = (int32_t)(p.pW * std::max<int64_t>(2, std::min<int64_t>(8, ind_chunks / (2 * slots))));
+                // individuals per wave, eight to a step: up to eight steps
+                // where that leaves four items per resident wave (the
+                // batch's large items keep the counter of a list quiet)
+                const int64_t slots = (int64_t)ctx->cu_count * 20;
+                p.pP = p.pW * 8 * (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, ind_panels / (32 * slots)));
             }
             p.pP = std::max(1, std::min(p.pP, 64 * p.pW));
             std::vector<const uint8_t *> keys;
@@ -354,7 +356,7 @@ static Plan plan_batch(ebic_ctx *ctx, const ebic_request *reqs, int32_t n_reqs, 
                 if (g == keys.size()) {
                     keys.push_back(d.B);
                     PairSeg sg{};
-                    sg.n_chunks = (int32_t)((d.rows + 2047) / 2048);
+                    sg.n_panels = (int32_t)pair_panels(d.rows);
                     p.segs.push_back(sg);
                 }
             }
@@ -375,7 +377,7 @@ static Plan plan_batch(ebic_ctx *ctx, const ebic_request *reqs, int32_t n_reqs, 
                 int64_t k = 0;
                 for (auto &sg : p.segs) {
                     sg.base[x] = (int32_t)k;
-                    const int64_t in_slice = sg.n_chunks > x ? (sg.n_chunks - x + 7) / 8 : 0;
+                    const int64_t in_slice = sg.n_panels > x ? (sg.n_panels - x + 7) / 8 : 0;
                     k += in_slice * sg.groups;
                 }
                 if (k > INT32_MAX) fail(EBIC_EINVAL, "batch too large for one launch");
@@ -386,6 +388,9 @@ static Plan plan_batch(ebic_ctx *ctx, const ebic_request *reqs, int32_t n_reqs, 
             int occ = pairs_batch_occupancy(p.pW);
             if (occ <= 0) occ = 1;
             p.pgrid = std::max(8, ctx->cu_count * occ / 8 * 8);
+            // Lists of at least four items per block are taken from a counter.
+            const int32_t longest = *std::max_element(p.pq.total, p.pq.total + 8);
+            p.pq.dynamic = longest >= 4 * (p.pgrid / 8);
         }
     }
     (void)count;
@@ -452,16 +457,16 @@ static std::unique_ptr<GraphEntry> capture_graph(ebic_ctx *ctx, const GraphSpec 
             e = launch_batch(reinterpret_cast<BatchHeader *>(da + lay.hdr),
                              reinterpret_cast<const ReqDesc *>(da + lay.descs),
                              reinterpret_cast<const int64_t *>(da + lay.first),
-                             reinterpret_cast<const Item *>(da + lay.items), g->d_heads, p.cfg.L,
-                             p.set, p.cfg.W, p.cfg.P, p.tile_bytes, p.items.empty() ? 0 : p.grid, prep_blocks,
+                             reinterpret_cast<const Item *>(da + lay.items), g->d_heads,
+                             reinterpret_cast<uint32_t *>(da + lay.next), p.cfg.L, p.set, p.cfg.W, p.cfg.P, p.tile_bytes, p.items.empty() ? 0 : p.grid, prep_blocks,
                              counter, cs);
         if (e == hipSuccess && p.any_pairs())
             e = launch_pairs_batch(reinterpret_cast<const PairQueues *>(da + lay.pq),
                                    reinterpret_cast<const ReqDesc *>(da + lay.descs),
                                    reinterpret_cast<const PairSeg *>(da + lay.segs),
                                    reinterpret_cast<const int32_t *>(da + lay.seg_req),
-                                   reinterpret_cast<const int32_t *>(da + lay.seg_gstart), g->d_heads, p.pW,
-                                   p.pgrid, counter, cs);
+                                   reinterpret_cast<const int32_t *>(da + lay.seg_gstart), g->d_heads,
+                                   reinterpret_cast<uint32_t *>(da + lay.next), p.pW, p.pgrid, counter, cs);
         hipGraph_t graph = nullptr;
         hipError_t e2 = hipStreamEndCapture(cs, &graph);
         check(e, "batch capture");

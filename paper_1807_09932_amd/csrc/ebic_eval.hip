@@ -90,24 +90,37 @@ __global__ void __launch_bounds__(256) k_prep(ReqDesc d, IndHead *__restrict__ h
 }
 
 __global__ void __launch_bounds__(256) k_prep_batch(BatchHeader *hdr, const ReqDesc *__restrict__ descs,
-                                                    const int64_t *__restrict__ first, IndHead *__restrict__ heads)
+                                                    const int64_t *__restrict__ first, IndHead *__restrict__ heads,
+                                                    uint32_t *__restrict__ pair_next)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) hdr->counter = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 8) pair_next[threadIdx.x * kPairNextStride] = 0;
     const int64_t total = hdr->total_ind;
     const int32_t nreq = hdr->n_req;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t g = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave; g < total; g += stride) {
-        int32_t lo = 0, hi = nreq - 1;  // the last request with first[q] <= g
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    // A wave takes four consecutive individuals: those on the pair bitmaps
+    // together, a row of 16 lanes each, the others one after the other.
+    const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave) * 4;
+    for (int64_t g = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * 4; g < total; g += stride) {
+        const int64_t mine = min(g + (lane >> 4), total - 1);
+        int32_t lo = 0, hi = nreq - 1;  // the last request with first[q] <= mine
         while (lo < hi) {
             const int32_t mid = (lo + hi + 1) >> 1;
-            if (first[mid] <= g) lo = mid;
+            if (first[mid] <= mine) lo = mid;
             else hi = mid - 1;
         }
-        if (descs[lo].flags & kFlagPairs)
-            prep_pairs_wave(descs[lo], (int32_t)(g - first[lo]), heads, threadIdx.x & (kWave - 1));
-        else
-            prep_wave(descs[lo], (int32_t)(g - first[lo]), heads, threadIdx.x & (kWave - 1));
+        const int32_t i = (int32_t)(mine - first[lo]);
+        const bool live = g + (lane >> 4) < total;
+        const bool pairs = (descs[lo].flags & kFlagPairs) != 0;
+        if (__ballot(live && pairs) != 0) {
+            const PairPrep p = prep_pairs_quad(descs[lo], i, live && pairs, lane);
+            if (live && pairs) prep_pairs_store(descs[lo], i, p, heads, lane);
+        }
+        const uint64_t tiled = __ballot(live && !pairs);
+        for (int t = 0; t < 4; ++t)
+            if (tiled >> (16 * t) & 1)
+                prep_wave(descs[__builtin_amdgcn_readlane(lo, 16 * t)], __builtin_amdgcn_readlane(i, 16 * t), heads, lane);
     }
 }
 
@@ -2637,25 +2650,10 @@ hipError_t launch_eval(const ReqDesc &d, IndHead *heads, const LaunchCfg &cfg,
         if (e != hipSuccess) return e;
     }
     if (cfg.staging == STAGE_PAIRS) {
-        // (no tile and no LDS: a flat grid of chunk x group blocks)
-        const void *kp = pairs_kernel(d.flags, step_counter != nullptr, cfg.P, cfg.W);
-        const size_t lds = 0;
-        hipError_t e = set_lds(kp, lds);
-        if (e != hipSuccess) return e;
-        // (at most 64 individuals per wave)
-        if (cfg.P > 64 * cfg.W) return hipErrorInvalidValue;
-        ReqDesc dd = d;
-        const IndHead *hh = heads;
-        int32_t P = cfg.P, nt = (int32_t)((d.rows + 63) / 64);
-        unsigned long long *sc = step_counter;
-        void *params[] = {&dd, &hh, &P, &nt, &sc};
+        hipError_t e;
         if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;
-        const dim3 grid = pairs_grid(d.rows, d.n, cfg.P);
-        if (grid.x > 0x7fffffffu || grid.y > 65535u) return hipErrorInvalidValue;
-        e = hipLaunchKernel(kp, grid, dim3(cfg.W * kWave), params, lds, s);
-        if (e != hipSuccess) return e;
-        if (ev1) e = hipEventRecord(ev1, s);
-        return e;
+        if ((e = launch_pairs(d, heads, cfg.P, cfg.W, step_counter, s)) != hipSuccess) return e;
+        return ev1 ? hipEventRecord(ev1, s) : hipSuccess;
     }
     if (cfg.staging == STAGE_DIRECT) {
         hipError_t e;
@@ -2722,13 +2720,13 @@ IndHead *noalloc_scratch(int device)
 }
 
 hipError_t launch_batch(BatchHeader *hdr, const ReqDesc *descs, const int64_t *first,
-                        const Item *items, IndHead *heads, int32_t L, int32_t set, int32_t W, int32_t P,
-                        size_t tile_bytes, int32_t grid, int32_t prep_blocks,
+                        const Item *items, IndHead *heads, uint32_t *pair_next, int32_t L, int32_t set, int32_t W,
+                        int32_t P, size_t tile_bytes, int32_t grid, int32_t prep_blocks,
                         unsigned long long *step_counter, hipStream_t s, hipEvent_t ev0,
                         hipEvent_t ev1)
 {
     clear_last_error();
-    hipLaunchKernelGGL(k_prep_batch, dim3(prep_blocks), dim3(256), 0, s, hdr, descs, first, heads);
+    hipLaunchKernelGGL(k_prep_batch, dim3(prep_blocks), dim3(256), 0, s, hdr, descs, first, heads, pair_next);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (grid <= 0) return hipSuccess;  // (no request on the tiled kernel)

@@ -210,11 +210,12 @@ IndHead *noalloc_scratch(int device);
 // Batched evaluation over a device-resident batch arena:
 //   hdr (BatchHeader) | descs (ReqDesc[n_req]) | first (int64[n_req + 1],
 //   prefix sums of individuals) | items (Item[n_items])
-// prep_blocks x 256 threads validate every individual of every request;
+// prep_blocks x 256 threads validate every individual of every request (and
+// zero the counters of the pair lists, pair_next);
 // then `grid` persistent blocks of W waves take items from the counter.
 hipError_t launch_batch(BatchHeader *hdr, const ReqDesc *descs, const int64_t *first,
-                        const Item *items, IndHead *heads, int32_t L, int32_t set, int32_t W, int32_t P,
-                        size_t tile_bytes, int32_t grid, int32_t prep_blocks,
+                        const Item *items, IndHead *heads, uint32_t *pair_next, int32_t L, int32_t set, int32_t W,
+                        int32_t P, size_t tile_bytes, int32_t grid, int32_t prep_blocks,
                         unsigned long long *step_counter, hipStream_t s,
                         hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
@@ -257,42 +258,50 @@ inline void clear_last_error() { (void)hipGetLastError(); }
 
 // Pairwise order bitmaps (ebic_pairs.hip): words per pair for `rows`, the
 // build of every pair's words from a column-major matrix (subst: NaN takes
-// `fill` first) with each 2,048-row chunk's list of tied pairs and NaN flag
+// `fill` first; full: both orientations of every pair, needed where a cell
+// may be missing or has been substituted) with each 2,048-row chunk's list of tied pairs and NaN flag
 // in T (pair_tie_bytes, zeroed by the caller), the prep kernel writing the
-// pairs headers, the evaluation kernel for request flags (ReqDesc: B = the
-// words, T = the tie lists), and its grid.
+// pairs headers, and the evaluation kernel (ReqDesc: B = the words, T = the
+// tie lists).
 constexpr int32_t kMaxPairCols = 1024;
-constexpr int64_t kMaxPairRows = 65535ll * 8 * 2048;  // (the plain launch's grid: chunks / 8 in y)
+constexpr int64_t kMaxPairRows = 65535ll * 8 * 2048;  // (the build's grid: chunks / 8 in y)
 constexpr int32_t kDefaultPairCols = 512;  // widths planned on the bitmaps unless a shape says otherwise
 constexpr int64_t kMaxPairBytes = 32ll << 30;
 int64_t pair_words(int64_t rows);
 int64_t pair_tie_bytes(int64_t rows);
-hipError_t launch_pair_bits(const float *X, int64_t rows, int64_t ld, int32_t cols, bool subst, float fill,
+hipError_t launch_pair_bits(const float *X, int64_t rows, int64_t ld, int32_t cols, bool full, bool subst, float fill,
                             uint32_t *G, int64_t w32, uint32_t *T, hipStream_t s);
 hipError_t launch_prep_pairs(const ReqDesc &d, IndHead *heads, hipStream_t s);
-const void *pairs_kernel(uint32_t flags, bool count, int32_t P, int32_t W);
-dim3 pairs_grid(int64_t rows, int32_t n, int32_t P);
+hipError_t launch_pairs(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,
+                        unsigned long long *step_counter, hipStream_t s);
+int64_t pair_panels(int64_t rows);  // 1,024-row panels (the evaluation's unit of rows)
 
 // The pair items of a batch: eight lists, one per XCD slice (a slice: the
-// chunks c with c mod 8 = x), each walking its chunks in order segment by
+// panels c with c mod 8 = x), each walking its panels in order segment by
 // segment; a segment is the requests reading one set of bitmaps, listed in
 // the entries e0 .. e0 + n_req - 1 of seg_req (request index) and seg_gstart
 // (the request's first group within the segment, groups of P individuals).
+// The counters of the lists (the next item past each block's first, zeroed
+// by the prep kernel): word x * kPairNextStride of their own array, so that
+// each has cache lines of its own.
+constexpr int kPairNextStride = 64;
+constexpr size_t kPairNextBytes = 8 * kPairNextStride * sizeof(uint32_t);
 struct PairQueues {
     int32_t total[8];  // items per list
     int32_t n_seg;
     int32_t P;         // individuals per group (at most 64 per wave)
-    int32_t pad[6];
+    int32_t dynamic;   // items past a block's first are taken from the list's counter
+    int32_t pad[5];
 };
 struct PairSeg {
     int32_t e0, n_req;
     int32_t groups;    // groups over the segment's requests
-    int32_t n_chunks;  // 2,048-row chunks of its matrix
+    int32_t n_panels;  // 1,024-row panels of its matrix
     int32_t base[8];   // the segment's first item in each list
 };
 hipError_t launch_pairs_batch(const PairQueues *pq, const ReqDesc *descs, const PairSeg *segs,
-                              const int32_t *seg_req, const int32_t *seg_gstart, const IndHead *heads, int32_t W,
-                              int32_t grid, unsigned long long *step_counter, hipStream_t s);
+                              const int32_t *seg_req, const int32_t *seg_gstart, const IndHead *heads,
+                              uint32_t *next, int32_t W, int32_t grid, unsigned long long *step_counter, hipStream_t s);
 int pairs_batch_occupancy(int32_t W);  // blocks per CU of the batched pairs kernel
 hipError_t launch_t10_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
                             uint8_t *T10, int64_t ld10, int32_t *has_nan, int32_t *ties, hipStream_t s);

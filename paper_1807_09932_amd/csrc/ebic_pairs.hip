@@ -20,44 +20,58 @@
 // bit: the bitmaps hold the compares' outcomes, ties and signed zeros
 // included.
 //
-// Layout: chunk by chunk (2,048 rows: one 32-bit word per lane of a wave),
-// and within a chunk pair by pair, pair (a, b) of chunk q at word
-// ((q * cols + a) * cols + b) * 64; bit i of a lane's word is row
-// 2048 q + 32 lane + i. Rows past the matrix are 0. A chunk's pairs span
-// cols^2 x 256 bytes, so a wave addresses them with 32-bit offsets from the
-// chunk's base. Include mode reads a second set built from the
-// fill-substituted values (the same set when no cell is missing).
+// Layout: panel by panel (1,024 rows, two to a chunk of 2,048), and within
+// a panel pair by pair, pair (a, b) of panel h at word
+// ((h * cols + a) * cols + b) * 32; bit i of word w is row 1024 h + 32 w + i.
+// A pair's words on a panel are one 128-byte cache line. Rows past the
+// matrix are 0. A panel's pairs span cols^2 x 128 bytes, so a wave addresses
+// them with 32-bit offsets from the panel's base. Include mode reads a
+// second set built from the fill-substituted values (the same set when no
+// cell is missing).
 //
 // Behind the bitmaps, 512 bytes per chunk list its ties: word 0 counts the
 // entries, word 1 is non-zero if a NaN occurs in the chunk, and words
-// 64 .. 127 hold the byte offsets of both orders of each pair of different
-// columns with two equal values on some row (up to 32 pairs; a count past
-// 64 means more). Where a chunk has no NaN and a pair (a, b), a != b, is not
-// listed, every row has x_a, x_b present and distinct, so the reversed
-// pair's word is the complement of the pair's on the matrix's rows: the
-// reversed chain then needs no loads of its own.
+// 64 .. 95 hold the byte offsets of the pairs (a, b), a < b, with two equal
+// values on some row (a count past 32 means more). Where a chunk has no NaN
+// and a pair is not listed, every row has x_a, x_b present and distinct, so
+// the reversed pair's word is the complement of the pair's on the matrix's
+// rows: one orientation (the ascending one) serves both chains of both
+// orientations, and a panel's working set is half its pairs.
 //
-// Evaluation: a block per (group of individuals, chunk), its waves taking
-// the group's individuals in turn. A prep kernel writes each individual's
-// 64-byte pairs header: k, the CSR start, the byte offsets of the pairs of
-// its first eight columns (consecutive repeats left out: a pair (c, c) is
-// implied by the pairs next to it, and the first pair is of two different
-// columns), and the window's columns. Per individual and chunk the wave
-// loads the seven pairs (two individuals' at a time), ANDs them, takes the
-// reversed chain as their complement where the chunk allows it (else loads
-// the reversed pairs), and follows the columns past the window eight at a
-// time while any row is left. Where a wave takes many individuals per item
-// (the batched kernel, and plain launches of eight or more per wave), the
-// next two individuals' headers are loaded while the current pairs are in
-// flight. No tile is staged: the words come through L2
-// and the Infinity Cache, where the pairs shared by the individuals of a
-// chunk are reused, and the blocks of a chunk are placed on one XCD and run
-// together. The counts of the wave's 2,048 rows are summed across lanes by
-// DPP (row shifts, then row broadcasts) into a lane of the wave's own, and
+// Evaluation: a wave takes eight individuals at a time (a step), eight lanes
+// each, on one panel: a lane holds 128 rows, one 16-byte load per pair, so a
+// load instruction reads eight cache lines whole. A prep kernel writes each
+// individual's header (ebic_prep.h); a step's eight headers (256 bytes) go
+// through LDS, where every lane reads its group's. The wave loads the seven
+// window pairs, ANDs them for one chain and takes the complement of their OR
+// for the other; where the chunk is dirty (NaN, or more ties than the list
+// holds) or a window pair is tied, both orientations are loaded. Individuals
+// with rows left and columns past the window wait in LDS, with their rows,
+// until eight of them (or the last of the item) are finished together, four
+// pairs at a time: a step goes on without them, and where one individual in
+// four has such rows (any population that follows a trend) the dependent
+// loads of their columns and words are paid once for eight. Counts are
+// summed over a group's lanes by DPP moves into a lane per individual, and
 // added to the outputs once per item.
+//
+// What bounds it, and why this shape. The kernel began with one individual
+// per wave on a chunk: a 4-byte load per lane, both orientations stored and
+// read. Three things held it (rocprofv3 counters, 436,444 x 64 and the batch
+// of 64 populations on 100,000 x 256, matrices and populations in turn):
+//   - the texture units return four lanes a clock whatever a lane asks for:
+//     256 bytes took as long as the kilobyte of a 16-byte load;
+//   - the scalar unit's 54 instructions per individual and chunk are now
+//     shared by eight individuals;
+//   - L2 misses. A panel of 256 columns in one orientation is 4.2 MB, about
+//     an XCD's L2; a chunk in both was 16.8 MB, read 3.6 times over.
+// 436,444 x 64, 800 individuals 38.6 -> 31.6 us an evaluation, x 310 51 ->
+// 49 us (there 266 MB of distinct words come from HBM at about 5.5 TB/s),
+// the batch 822 -> 383 us. Four individuals of 16 lanes (8-byte loads): 38,
+// 57 and 585 us.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "ebic_internal.h"
 #include "ebic_prep.h"
@@ -69,371 +83,661 @@ constexpr int kChunkRows = 2048;  // rows per wave step: 64 lanes x 32 rows
 constexpr int kChunkWords = 64;
 constexpr int kTieWords = 128;    // per chunk: count, NaN flag, ..., 64 listed offsets
 constexpr int kTieList = 64;      // (the list's first word)
-constexpr uint32_t kNoPair = 0xffffffffu;  // never a pair's offset (those are multiples of 256)
-constexpr int kPipeMin = 8;       // individuals per wave and item from which the headers are loaded ahead
+constexpr int kTieMax = 32;       // pairs it holds
+constexpr uint32_t kNoPair = kHeadOffset;  // no pair's offset (1,024 columns end below it)
+constexpr int kPanelRows = 1024;  // rows of one step: 8 lanes x 128 rows
+constexpr int kPanelWords = 32;
+constexpr int kGroup = 8;         // lanes per individual (16 bytes of a pair's line each)
+constexpr int kStep = kWave / kGroup;  // individuals per wave and step
+constexpr int kQueue = 2 * kStep - 1;  // individuals that wait for their columns past the window
+// LDS of a wave: a step's headers, and the queue's rows and (k, start, index).
+constexpr size_t kWaveLds = kStep * 32 + kQueue * (2 * 128 + 16);
 
 __global__ void __launch_bounds__(256) k_prep_pairs(ReqDesc d, IndHead *__restrict__ heads)
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int32_t i = blockIdx.x * (blockDim.x / kWave) + wave;
-    if (i < d.n) prep_pairs_wave(d, i, heads, threadIdx.x & (kWave - 1));
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int32_t i = (int32_t)(blockIdx.x * (blockDim.x / 16) + threadIdx.x / 16);
+    const PairPrep p = prep_pairs_quad(d, i, i < d.n, lane);
+    if (i < d.n) prep_pairs_store(d, i, p, heads, lane);
 }
 
-// One wave per block: columns a0 = A t .. A t + A - 1 of one chunk against
-// every b >= a0, the words of pairs (a, b) and (b, a) on the chunk's rows;
-// lane l covers rows chunk*2048 + 32 l ... + 31 (one 128-byte run of each
-// column), and each column b is loaded once for the block's A columns. Ties
-// and NaN go to the chunk's list (T, zeroed beforehand). The grid is
-// (8 x ceil(cols / A), chunks / 8): block (x, y) takes chunk 8 y + x mod 8
-// and t = x / 8, so a chunk's blocks all run on one XCD, one after another,
-// and its columns stay in that XCD's L2 while they do.
-template <int A>
-__global__ void __launch_bounds__(64) k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld,
-                                                  int32_t cols, int32_t subst, float fill,
-                                                  uint32_t *__restrict__ G, uint32_t *__restrict__ T)
+// ---------------------------------------------------------------------------
+// The build. A block takes 16 columns a (two to each of its eight waves, in
+// registers: lane l holds rows 32 l .. 32 l + 31 of the chunk) against a run
+// of `run` columns b >= a, staged four at a time through LDS: read from the
+// matrix in whole lines, each once per block, and from LDS as every lane's
+// 128 bytes (rows padded to 144 bytes: no bank conflicts). The grid is
+// (8 x tiles, chunks / 8): block (x, y) takes chunk 8 y + x mod 8 and tile
+// x / 8, so a chunk's blocks run on one XCD and its columns stay in its L2.
+//
+// A pair's word is built bit by bit: a compare into a scalar pair, and an
+// add with carry that shifts the word left and takes the bit. Without
+// missing cells (FULL false) only the ascending orientation's words are
+// written, and a second compare (equal, kept as one mask per word) finds the
+// pairs with a tie, whose reverse is then computed and written too and which
+// go to the chunk's list: three vector instructions per row and pair. With
+// missing cells (FULL), or on the chunks whose list has overflowed (a second
+// launch; `dirty` = the list's limit, chunks below it exit at once), both
+// orientations are built with four. The first version compared both ways
+// with about eight (a compare, its wait states, a select, half an or), read
+// each column with lanes 128 bytes apart (64 lines per load) and wrote both
+// orientations of every pair.
+//
+// Bound by the vector unit (114 instructions per pair and 2,048 rows) and,
+// with four waves per SIMD, by the waits for LDS and the barriers: 54,675 x
+// 178 507 -> 190 us, 436,444 x 64 330 -> 258 us, 436,444 x 310 5.0 -> 3.0
+// ms; 20,000 x 200 with 5% missing cells 476 -> 147 us, and 818 -> 156 us of
+// the substituted values, whose every pair ties: a block stops listing once
+// the list has overflowed.
+// ---------------------------------------------------------------------------
+constexpr int kBuildWaves = 8;
+constexpr int kBuildA = 2;                          // columns a per wave
+constexpr int kBuildCols = kBuildWaves * kBuildA;   // columns a per block
+constexpr int kBuildB = 4;                          // columns b staged together
+constexpr int kLaneFloats = 36;                     // a lane's 32 rows in LDS, padded
+constexpr int kBuildTile = kBuildWaves * kWave * kLaneFloats;  // (the waves' columns a; then four columns b twice)
+
+// Bits of x[i] >= y[i] for four rows, the highest first, into `word`, and
+// the lanes with x[i] == y[i] into `tie` (no NaN).
+__device__ __forceinline__ void ge4_ties(uint32_t &word, uint64_t &tie, const float *x, const float *y)
 {
-    const int64_t n_chunks = (rows + kChunkRows - 1) / kChunkRows;
+    uint64_t g0, g1, g2, g3, t0, t1, t2, t3;
+    asm volatile("v_cmp_ge_f32_e64 %[g3], %[x3], %[y3]\n\t"
+                 "v_cmp_ge_f32_e64 %[g2], %[x2], %[y2]\n\t"
+                 "v_cmp_ge_f32_e64 %[g1], %[x1], %[y1]\n\t"
+                 "v_cmp_ge_f32_e64 %[g0], %[x0], %[y0]\n\t"
+                 "v_cmp_eq_f32_e64 %[t3], %[x3], %[y3]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g3], %[w], %[w], %[g3]\n\t"
+                 "v_cmp_eq_f32_e64 %[t2], %[x2], %[y2]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g2], %[w], %[w], %[g2]\n\t"
+                 "v_cmp_eq_f32_e64 %[t1], %[x1], %[y1]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g1], %[w], %[w], %[g1]\n\t"
+                 "v_cmp_eq_f32_e64 %[t0], %[x0], %[y0]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g0], %[w], %[w], %[g0]\n\t"
+                 "s_or_b64 %[t3], %[t3], %[t2]\n\t"
+                 "s_or_b64 %[t1], %[t1], %[t0]\n\t"
+                 "s_or_b64 %[tie], %[tie], %[t3]\n\t"
+                 "s_or_b64 %[tie], %[tie], %[t1]"
+                 : [w] "+v"(word), [tie] "+s"(tie), [g0] "=&s"(g0), [g1] "=&s"(g1), [g2] "=&s"(g2), [g3] "=&s"(g3),
+                   [t0] "=&s"(t0), [t1] "=&s"(t1), [t2] "=&s"(t2), [t3] "=&s"(t3)
+                 : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [y0] "v"(y[0]), [y1] "v"(y[1]),
+                   [y2] "v"(y[2]), [y3] "v"(y[3])
+                 : "scc");
+}
+
+// The same bits alone.
+__device__ __forceinline__ void ge4(uint32_t &word, const float *x, const float *y)
+{
+    uint64_t g0, g1, g2, g3;
+    asm volatile("v_cmp_ge_f32_e64 %[g3], %[x3], %[y3]\n\t"
+                 "v_cmp_ge_f32_e64 %[g2], %[x2], %[y2]\n\t"
+                 "v_cmp_ge_f32_e64 %[g1], %[x1], %[y1]\n\t"
+                 "v_cmp_ge_f32_e64 %[g0], %[x0], %[y0]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g3], %[w], %[w], %[g3]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g2], %[w], %[w], %[g2]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g1], %[w], %[w], %[g1]\n\t"
+                 "v_addc_co_u32_e64 %[w], %[g0], %[w], %[w], %[g0]"
+                 : [w] "+v"(word), [g0] "=&s"(g0), [g1] "=&s"(g1), [g2] "=&s"(g2), [g3] "=&s"(g3)
+                 : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [y0] "v"(y[0]), [y1] "v"(y[1]),
+                   [y2] "v"(y[2]), [y3] "v"(y[3]));
+}
+
+template <bool FULL>
+__global__ void __launch_bounds__(kBuildWaves *kWave) __attribute__((amdgpu_waves_per_eu(4)))
+k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols, int32_t subst, float fill, int32_t run,
+            int32_t dirty, uint32_t *__restrict__ G, uint32_t *__restrict__ T)
+{
+    __shared__ __align__(16) float tile[kBuildTile];
     const int64_t chunk = 8 * (int64_t)blockIdx.y + (blockIdx.x & 7);
-    const int32_t a0 = A * (int32_t)(blockIdx.x >> 3);
-    if (chunk >= n_chunks || a0 >= cols) return;
-    const int lane = (int)threadIdx.x;
-    const int64_t r0 = chunk * kChunkRows + 32 * lane;
-    // valid rows of this lane's 32 as a bit mask
-    const int64_t nvalid = rows - r0;
-    const uint32_t vmask = nvalid >= 32 ? 0xffffffffu : nvalid <= 0 ? 0u : ((1u << nvalid) - 1u);
-    auto load32 = [&](int32_t c, float (&v)[32]) {
-        if (r0 < ld) {
-            const float4 *p = reinterpret_cast<const float4 *>(X + (int64_t)c * ld + r0);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float4 f = p[q];
-                v[4 * q] = f.x;
-                v[4 * q + 1] = f.y;
-                v[4 * q + 2] = f.z;
-                v[4 * q + 3] = f.w;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 32; ++i) v[i] = __builtin_nanf("");
-        }
-        if (subst) {
-#pragma unroll
-            for (int i = 0; i < 32; ++i) v[i] = v[i] != v[i] ? fill : v[i];
-        }
-    };
+    const int32_t runs = (cols + run - 1) / run;
+    const int32_t a0 = (int32_t)(blockIdx.x >> 3) / runs * kBuildCols, b0 = (int32_t)(blockIdx.x >> 3) % runs * run;
+    const int32_t b1 = min(b0 + run, cols);
+    if (chunk * kChunkRows >= rows || b1 <= a0) return;
     uint32_t *tl = T + chunk * kTieWords;
-    const uint32_t cb = (uint32_t)cols * 256u;
-    // the words of pairs (a, b) and (b, a), b >= a
-    auto emit = [&](int32_t a, const float (&xa)[32], int32_t b, const float (&xb)[32]) {
-        uint32_t ge = 0, le = 0;  // x_b >= x_a, x_a >= x_b
-#pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            ge |= (xb[i] >= xa[i] ? 1u : 0u) << i;
-            le |= (xa[i] >= xb[i] ? 1u : 0u) << i;
+    if (dirty && (int32_t)__builtin_amdgcn_readfirstlane(tl[0]) <= dirty) return;
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int64_t c0 = chunk * kChunkRows, r0 = c0 + 32 * lane;
+    const int64_t panel = 2 * chunk + (lane >> 5);
+    const int64_t nvalid = rows - r0;
+    const uint32_t vmask = nvalid >= 32 ? ~0u : nvalid <= 0 ? 0u : ((1u << nvalid) - 1u);
+
+    // Rows r .. r + 3 of column c; rows past the matrix take `pad` (unequal
+    // for a and b, so that they never tie).
+    auto fetch = [&](int32_t c, int64_t r) {
+        return r < ld && c < cols ? *reinterpret_cast<const float4 *>(X + (int64_t)c * ld + r) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    auto fixed = [&](float4 f, int64_t r, float pad) {
+        if (subst) {
+            f.x = f.x != f.x ? fill : f.x;
+            f.y = f.y != f.y ? fill : f.y;
+            f.z = f.z != f.z ? fill : f.z;
+            f.w = f.w != f.w ? fill : f.w;
         }
-        G[((chunk * cols + a) * cols + b) * kChunkWords + lane] = ge & vmask;
-        if (b != a) G[((chunk * cols + b) * cols + a) * kChunkWords + lane] = le & vmask;
-        const uint32_t odd = (b == a ? ~ge : (ge & le)) & vmask;  // NaN rows; tied rows
-        if (__ballot(odd != 0) != 0 && lane == 0) {
-            if (b == a) {
-                atomicOr(tl + 1, 1u);
-            } else {
-                const uint32_t slot = atomicAdd(tl, 2u);
-                if (slot + 2 <= (uint32_t)kTieList) {
-                    tl[kTieList + slot] = (uint32_t)a * cb + ((uint32_t)b << 8);
-                    tl[kTieList + slot + 1] = (uint32_t)b * cb + ((uint32_t)a << 8);
-                }
-            }
+        if (r + 3 >= rows) {
+            if (r >= rows) f.x = pad;
+            if (r + 1 >= rows) f.y = pad;
+            if (r + 2 >= rows) f.z = pad;
+            f.w = pad;
+        }
+        return f;
+    };
+    // (four rows f of a column go to lane f / 8's part)
+    auto place = [](int f) { return (f >> 3) * kLaneFloats + (f & 7) * 4; };
+    auto take = [&](const float *column, float (&v)[32]) {
+        const float4 *p = reinterpret_cast<const float4 *>(column + lane * kLaneFloats);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float4 f = p[i];
+            v[4 * i] = f.x;
+            v[4 * i + 1] = f.y;
+            v[4 * i + 2] = f.z;
+            v[4 * i + 3] = f.w;
         }
     };
-    float xa[A][32];
-#pragma unroll
-    for (int j = 0; j < A; ++j) load32(min(a0 + j, cols - 1), xa[j]);
-    for (int32_t b = a0; b < cols; ++b) {
-        float xb[32];
-        load32(b, xb);
-#pragma unroll
-        for (int j = 0; j < A; ++j)
-            if (b >= a0 + j) emit(a0 + j, xa[j], b, xb);
-    }
-}
-
-// Sum over the wave's 64 lanes, returned to every lane: an inclusive scan
-// within each row of 16 lanes (row shifts by 1, 2, 4, 8), then row 0's
-// total added into row 1 and row 2's into row 3 (row broadcast of lane 15),
-// then lane 31's into rows 2 and 3 (row broadcast of lane 31): lane 63 holds
-// the sum.
-__device__ __forceinline__ uint32_t wave_total(uint32_t v)
-{
-    int s = (int)v;
-    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xf, 0xf, true);   // row_shr:1
-    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xf, 0xf, true);   // row_shr:2
-    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xf, 0xf, true);   // row_shr:4
-    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xf, 0xf, true);   // row_shr:8
-    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane(s, 63);
-}
-
-// What the item loop takes from a pairs header up front (the CSR start and
-// the window's columns are read where they are needed: the reversed pairs'
-// loads and the columns past the window).
-struct PairScal {
-    int32_t k;
-    uint32_t f[7];
-};
-
-__device__ __forceinline__ PairScal pair_scal(const PairHead *h)
-{
-    const int4 *p = reinterpret_cast<const int4 *>(h);
-    const int4 x0 = p[0], x1 = p[1];
-    const uint32_t x2 = h->fwd[6];
-    PairScal s;
-    s.k = __builtin_amdgcn_readfirstlane(x0.x);
-    s.f[0] = (uint32_t)__builtin_amdgcn_readfirstlane(x0.z);
-    s.f[1] = (uint32_t)__builtin_amdgcn_readfirstlane(x0.w);
-    s.f[2] = (uint32_t)__builtin_amdgcn_readfirstlane(x1.x);
-    s.f[3] = (uint32_t)__builtin_amdgcn_readfirstlane(x1.y);
-    s.f[4] = (uint32_t)__builtin_amdgcn_readfirstlane(x1.z);
-    s.f[5] = (uint32_t)__builtin_amdgcn_readfirstlane(x1.w);
-    s.f[6] = (uint32_t)__builtin_amdgcn_readfirstlane((int)x2);
-    return s;
-}
-
-// One work item: individuals [i0, i0 + np) of a request on one 2,048-row
-// chunk, by the W waves of a block (the wave's individuals in turn, at most
-// 64 per wave); each lane of a wave keeps the counts of one of the wave's
-// individuals, added to the outputs at the end.
-template <bool NEG, bool COUNT, bool PIPE>
-__device__ __forceinline__ void pairs_item(const ReqDesc &d, const IndHead *__restrict__ heads, int32_t i0,
-                                           int32_t np, int32_t chunk, int lane, int wave, int W, uint64_t &steps)
-{
-    const int32_t C = d.cols;
-    const uint32_t cb = (uint32_t)C * 256u;  // pairs (a, 0 .. C-1) of a chunk
-    const int voff = lane * 4;
-    const PairHead *hb = reinterpret_cast<const PairHead *>(heads + d.head_base + i0);
-    // mask words (as 32-bit halves, little-endian: the uint64 layout)
-    const int64_t words32 = 2 * ((d.rows + 63) / 64);
-    const bool masks = d.mmask || d.nmask;
-    uint32_t acc_m = 0, acc_g = 0;  // lane t: the wave's t-th individual
-
+    static_assert(kChunkRows == 4 * kBuildWaves * kWave, "a thread stages four rows of each column b");
+    // The wave's columns a, through a part of the LDS of its own.
+    float xa[kBuildA][32];
     {
-        const uint32_t *gchunk = reinterpret_cast<const uint32_t *>(d.B) + (int64_t)chunk * C * C * kChunkWords;
-        const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(gchunk), (short)0, C * C * 256, 0x00020000);
-        // pair (a, c) of the chunk, this lane's word: offset a * C * 256 + c * 256
-        auto ld = [&](uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(rs, voff, (int)off, 0); };
-        // The chunk's ties: lane l holds listed offset l (kNoPair past the
-        // count); `dirty` when the list overflowed or a NaN occurs.
-        const uint32_t *tl = reinterpret_cast<const uint32_t *>(d.T) + (int64_t)chunk * kTieWords;
-        const uint32_t n_tied = __builtin_amdgcn_readfirstlane(tl[0]);
-        const uint32_t nan_flag = __builtin_amdgcn_readfirstlane(tl[1]);  // (read either way: no dependent load)
-        const bool dirty = (n_tied > (uint32_t)kTieList) | (nan_flag != 0);
-        const uint32_t tied = (uint32_t)lane < n_tied ? tl[kTieList + lane] : kNoPair;
-        const bool clean = n_tied == 0 && !dirty;
-        const int64_t nvalid = d.rows - ((int64_t)chunk * kChunkRows + 32 * lane);
-        const uint32_t vmask = nvalid >= 32 ? 0xffffffffu : nvalid <= 0 ? 0u : ((1u << nvalid) - 1u);
-        // may the reversed chain over these pair offsets be the complement?
-        auto untied = [&](const uint32_t *off, int n) {
-            if (clean) return true;
-            if (dirty) return false;
-            bool hit = false;
-            for (int t = 0; t < n; ++t) hit |= tied == off[t];
-            return __ballot(hit) == 0;
-        };
-        const int64_t word = (int64_t)chunk * kChunkWords + lane;
-        const bool store = word < words32;
-
-        // The reversed chain of the window from its columns (loads of the
-        // reversed pairs; (c, c): "present", implied by the pairs next to it).
-        auto slow_window = [&](const PairHead *h) {
-            const uint32_t *hw = h->win;
-            uint32_t wp[4];
+        float *own = tile + wave * kWave * kLaneFloats;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) wp[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)hw[u]);
-            uint32_t q[7];
+        for (int i = 0; i < kBuildA; ++i) {
 #pragma unroll
-            for (int u = 0; u < 7; ++u) {
-                const uint32_t a = (wp[u >> 1] >> ((u & 1) * 16)) & 0xffffu;
-                const uint32_t c = (wp[(u + 1) >> 1] >> (((u + 1) & 1) * 16)) & 0xffffu;
-                q[u] = ld(c * cb + (a << 8));
+            for (int q = 0; q < kBuildWaves; ++q) {
+                const int f = q * kWave + lane;
+                *reinterpret_cast<float4 *>(own + place(f)) =
+                    fixed(fetch(a0 + kBuildA * wave + i, c0 + 4 * f), c0 + 4 * f, __builtin_inff());
             }
-            return q[0] & q[1] & q[2] & q[3] & q[4] & q[5] & q[6];
-        };
-        // The columns past the window, eight at a time (the last one
-        // repeated past the end), while a row is left.
-        auto tail = [&](uint32_t &Pw, uint32_t &Nw, int32_t k, const PairHead *h) {
-            const int32_t *cc = d.colidx + __builtin_amdgcn_readfirstlane(h->begin);
-            uint32_t prev = (uint32_t)__builtin_amdgcn_readfirstlane((int)h->win[3]) >> 16;  // the window's last column
-            for (int32_t u = 8; u < k; u += 8) {
-                uint32_t cn[8], fo[8], pp[8];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            take(own, xa[i]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    }
+    bool listing = dirty == 0;
+    const int64_t rb = c0 + 4 * (int64_t)threadIdx.x;
+    float4 pre[kBuildB];
+    const int32_t aw = a0 + kBuildA * wave;
+    const int32_t bs = max(b0, a0) / kBuildB * kBuildB;  // (a0 and b0 are multiples of the step)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) cn[e] = (uint32_t)__builtin_amdgcn_readfirstlane(cc[min(u + e, k - 1)]);
+    for (int q = 0; q < kBuildB; ++q) pre[q] = fetch(bs + q, rb);
+    __syncthreads();
+    // (two buffers in turn: one barrier per step)
+    float *buf = tile;
+    for (int32_t bt = bs; bt < b1; bt += kBuildB) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    fo[e] = (e == 0 ? prev : cn[e - 1]) * cb + (cn[e] << 8);
-                    pp[e] = ld(fo[e]);
+        for (int q = 0; q < kBuildB; ++q)
+            *reinterpret_cast<float4 *>(buf + q * kWave * kLaneFloats + place((int)threadIdx.x)) = fixed(pre[q], rb, 0.f);
+        __syncthreads();
+        if (bt + kBuildB < b1)
+#pragma unroll
+            for (int q = 0; q < kBuildB; ++q) pre[q] = fetch(bt + kBuildB + q, rb);
+#pragma unroll 1
+        for (int q = 0; q < kBuildB; ++q) {  // (the same columns for every wave)
+            const int32_t b = bt + q;
+            if (b >= b1 || b < aw) continue;
+            float xb[32];
+            take(buf + q * kWave * kLaneFloats, xb);
+#pragma unroll
+            for (int i = 0; i < kBuildA; ++i) {
+                const int32_t a = aw + i;
+                if (a > b || a >= cols) continue;
+                __builtin_amdgcn_sched_barrier(0);  // (pair by pair: registers)
+                uint32_t ge = 0;
+                uint64_t tie = 0;
+                const int64_t up = ((panel * cols + a) * cols + b) * kPanelWords + (lane & 31);
+                const int64_t down = ((panel * cols + b) * cols + a) * kPanelWords + (lane & 31);
+                if (!FULL) {
+#pragma unroll
+                    for (int r = 28; r >= 0; r -= 4) ge4_ties(ge, tie, xb + r, xa[i] + r);
+                    G[up] = ge & vmask;
+                    if (a == b || tie == 0) continue;
+                } else {
+#pragma unroll
+                    for (int r = 28; r >= 0; r -= 4) ge4(ge, xb + r, xa[i] + r);
+                    G[up] = ge & vmask;
                 }
-                Pw &= pp[0] & pp[1] & pp[2] & pp[3] & pp[4] & pp[5] & pp[6] & pp[7];
-                if (NEG) {
-                    if (untied(fo, 8)) {
-                        // (c, c) pairs: "present", all the chunk's rows
-                        uint32_t nq = 0;
+                __builtin_amdgcn_sched_barrier(0);
+                uint32_t le = 0;
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) nq |= (e == 0 ? prev : cn[e - 1]) == cn[e] ? 0u : pp[e];
-                        Nw &= ~nq;
+                for (int r = 28; r >= 0; r -= 4) ge4(le, xa[i] + r, xb + r);
+                if (a != b) G[down] = le & vmask;
+                const uint32_t odd = (a == b ? ~ge : (ge & le)) & vmask;  // rows with NaN; tied rows
+                if (listing && __ballot(odd != 0) != 0) {
+                    if (a == b) {
+                        if (lane == 0) atomicOr(tl + 1, 1u);
+                        listing = false;
                     } else {
-                        uint32_t qq[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) qq[e] = ld(cn[e] * cb + ((e == 0 ? prev : cn[e - 1]) << 8));
-                        Nw &= qq[0] & qq[1] & qq[2] & qq[3] & qq[4] & qq[5] & qq[6] & qq[7];
+                        uint32_t slot = 0;
+                        if (lane == 0) {
+                            slot = atomicAdd(tl, 1u);
+                            if (slot < (uint32_t)kTieMax) tl[kTieList + slot] = pair_offset((uint32_t)cols, (uint32_t)a, (uint32_t)b);
+                        }
+                        // (a list that has overflowed takes no more)
+                        listing = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) < (uint32_t)kTieMax;
                     }
                 }
-                prev = cn[7];
-                if (COUNT) steps += (uint64_t)min(8, k - u);
-                if (__ballot((Pw | Nw) != 0) == 0) break;
-            }
-        };
-        // Masks and counts of the wave's t-th individual (ii).
-        auto finish = [&](uint32_t Pw, uint32_t Nw, int32_t ii, int32_t t) {
-            const uint32_t mw = Pw | Nw, gw = NEG ? (Nw & ~Pw) : 0u;
-            if (masks && store) {
-                if (d.mmask) reinterpret_cast<uint32_t *>(d.mmask)[(int64_t)(i0 + ii) * words32 + word] = mw;
-                if (d.nmask) reinterpret_cast<uint32_t *>(d.nmask)[(int64_t)(i0 + ii) * words32 + word] = gw;
-            }
-            if (__ballot(mw != 0) == 0) return;
-            const uint32_t both =
-                wave_total((uint32_t)__builtin_popcount(mw) | ((uint32_t)__builtin_popcount(gw) << 16));
-            if (lane == t) {
-                acc_m += both & 0xffffu;
-                if (NEG) acc_g += both >> 16;
-            }
-        };
-
-        // Two individuals at a time (ii and ii + W, the wave's t-th and
-        // (t + 1)-th): both windows' loads in flight together, and the
-        // next two individuals' headers loaded while they are. The window
-        // needs no branch: an individual of one column has the diagonal
-        // pair in every slot (its reversed chain, whatever it gives, adds
-        // nothing: its rows are all positive), and an invalid one (k = 0)
-        // is zeroed after the loads.
-        int32_t ii = wave;
-        if (ii < np) {
-            int32_t t = 0;
-            PairScal A = pair_scal(hb + ii), B = pair_scal(hb + min(ii + W, np - 1));
-            for (;;) {
-                const bool two = ii + W < np;
-                uint32_t pa[7], pb[7];
-#pragma unroll
-                for (int u = 0; u < 7; ++u) {
-                    pa[u] = ld(A.f[u]);
-                    pb[u] = ld(B.f[u]);
-                }
-                const int32_t jn = ii + 2 * W;
-                const bool more = jn < np;
-                PairScal An, Bn;
-                if (PIPE && more) {
-                    An = pair_scal(hb + jn);
-                    Bn = pair_scal(hb + min(jn + W, np - 1));
-                }
-                uint32_t Pa = pa[0] & pa[1] & pa[2] & pa[3] & pa[4] & pa[5] & pa[6];
-                uint32_t Pb = pb[0] & pb[1] & pb[2] & pb[3] & pb[4] & pb[5] & pb[6];
-                uint32_t Na = 0, Nb = 0;
-                if (NEG) {
-                    Na = untied(A.f, 7) ? ~(pa[0] | pa[1] | pa[2] | pa[3] | pa[4] | pa[5] | pa[6]) & vmask
-                                        : slow_window(hb + ii);
-                    Nb = untied(B.f, 7) ? ~(pb[0] | pb[1] | pb[2] | pb[3] | pb[4] | pb[5] | pb[6]) & vmask
-                                        : slow_window(hb + min(ii + W, np - 1));
-                }
-                if (A.k == 0) Pa = Na = 0u;
-                if (B.k == 0) Pb = Nb = 0u;
-                if (COUNT) steps += (A.k > 1 ? 7 : A.k) + (two ? (B.k > 1 ? 7 : B.k) : 0);
-                if (A.k > 8 && __ballot((Pa | Na) != 0) != 0) tail(Pa, Na, A.k, hb + ii);
-                finish(Pa, Na, ii, t);
-                if (two) {
-                    if (B.k > 8 && __ballot((Pb | Nb) != 0) != 0)
-                        tail(Pb, Nb, B.k, hb + ii + W);
-                    finish(Pb, Nb, ii + W, t + 1);
-                }
-                if (!more) break;
-                if (PIPE) {
-                    A = An;
-                    B = Bn;
-                } else {
-                    A = pair_scal(hb + jn);
-                    B = pair_scal(hb + min(jn + W, np - 1));
-                }
-                ii = jn;
-                t += 2;
             }
         }
-    }
-    // the wave's individuals wave + t W, t = lane
-    const int32_t ii = wave + lane * W;
-    if (ii < np) {
-        if (acc_m) atomicAdd(d.matched + i0 + ii, (int32_t)acc_m);
-        if (NEG && acc_g && d.negative) atomicAdd(d.negative + i0 + ii, (int32_t)acc_g);
+        buf = buf == tile ? tile + kBuildB * kWave * kLaneFloats : tile;
     }
 }
 
-// The plain launch: a 2-D grid of (8 x groups, chunks / 8) blocks. Block
-// (x, y) works on chunk 8 y + x mod 8 and group x / 8: blocks are dispatched
-// x first, and with gridDim.x a multiple of 8 the linear block index is
-// x mod 8 modulo 8, so on MI355X's round-robin placement of blocks over the
-// eight XCDs the blocks of a chunk all run on one XCD and share its L2, and
-// the blocks of eight consecutive chunks (all their groups) are dispatched
-// together.
-template <bool NEG, bool COUNT, bool PIPE>
-__global__ void __launch_bounds__(1024) k_eval_pairs(ReqDesc d, const IndHead *__restrict__ heads, int32_t P,
-                                                     int32_t n_tiles, unsigned long long *step_counter)
+// Moves within the groups of eight lanes (half a DPP row), one individual
+// each: lane u of the group to all of it; the sum over the group in every
+// lane; the group's bits of a wave mask.
+template <int U>
+__device__ __forceinline__ uint32_t group_bcast(uint32_t v)
 {
-    const int32_t n_chunks = (n_tiles + 31) / 32;
-    const int32_t chunk = (int32_t)(8 * blockIdx.y + (blockIdx.x & 7));
-    const int32_t grp = (int32_t)(blockIdx.x >> 3);
-    if (chunk >= n_chunks) return;
-    const int32_t i0 = grp * P;
-    const int32_t np = min(P, d.n - i0);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x150 + U, 0xf, 0x3, false);      // row_newbcast:U, lanes 0..7
+    return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)v, 0x158 + U, 0xf, 0xc, false);   // row_newbcast:8 + U, lanes 8..15
+}
+__device__ __forceinline__ uint32_t group_total(uint32_t v)
+{
+    int s = (int)v;
+    s += __builtin_amdgcn_update_dpp(0, s, 0xb1, 0xf, 0xf, true);   // quad_perm:[1,0,3,2]
+    s += __builtin_amdgcn_update_dpp(0, s, 0x4e, 0xf, 0xf, true);   // quad_perm:[2,3,0,1]
+    s += __builtin_amdgcn_update_dpp(0, s, 0x141, 0xf, 0xf, true);  // row_half_mirror
+    return (uint32_t)s;
+}
+__device__ __forceinline__ uint32_t group_bits(uint64_t m, int lane)
+{
+    const uint32_t w = lane & 32 ? (uint32_t)(m >> 32) : (uint32_t)m;
+    return __builtin_amdgcn_ubfe(w, (uint32_t)lane & 24u, 8u);
+}
+
+// 128 rows of a lane.
+struct Bits {
+    uint32_t w[4];
+};
+// The two chains of one individual on them.
+struct Rows {
+    Bits p, n;
+    __device__ __forceinline__ bool any() const
+    {
+        return ((p.w[0] | p.w[1] | p.w[2]) | (p.w[3] | n.w[0] | n.w[1]) | (n.w[2] | n.w[3])) != 0;
+    }
+};
+
+// A wave's walk over (individual, panel) units, eight individuals at a time
+// (lane group g: the step's individual g).
+template <bool NEG, bool COUNT>
+struct PairWave {
+    const ReqDesc &d;
+    const int lane, j, g;
+    const uint32_t lane16;  // this lane's byte in a pair's line
+    const uint32_t cols;
+    const int64_t panel_words;
+    uint64_t steps = 0;
+
+    __device__ PairWave(const ReqDesc &dd, int l)
+        : d(dd), lane(l), j(l & (kGroup - 1)), g(l / kGroup), lane16((uint32_t)(l & (kGroup - 1)) * 16u),
+          cols((uint32_t)dd.cols), panel_words((int64_t)dd.cols * dd.cols * kPanelWords)
+    {
+    }
+
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(int64_t panel) const
+    {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(d.B) + panel * panel_words;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p), (short)0, (int)(panel_words * 4), 0x00020000);
+    }
+    __device__ __forceinline__ const uint32_t *ties(int64_t panel) const
+    {
+        return reinterpret_cast<const uint32_t *>(d.T) + (panel >> 1) * kTieWords;
+    }
+    __device__ __forceinline__ static Bits load(__amdgpu_buffer_rsrc_t rs, uint32_t off)
+    {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
+        return Bits{{v[0], v[1], v[2], v[3]}};
+    }
+    template <int N, class F>
+    __device__ __forceinline__ static void each(F &&f)
+    {
+        if constexpr (N > 0) {
+            each<N - 1>(f);
+            f(std::integral_constant<int, N - 1>{});
+        }
+    }
+
+    __device__ __forceinline__ uint32_t line(uint32_t word) const
+    {
+        return (word & kHeadOffset) | (lane16 & ~kHeadOffset);  // (one v_bfi)
+    }
+
+    // The groups with one of their pairs among the chunk's n_tied listed
+    // ones (lane e of `tie`: entry e). asc: the header's word j in lane j < 7
+    // (kNoPair in lanes without a pair); hit: the lane's own pair is one.
+    __device__ __forceinline__ bool listed(uint32_t asc, uint32_t tie, uint32_t n_tied, bool &hit) const
+    {
+        asc &= kHeadOffset;
+        hit = false;
+#pragma unroll 1
+        for (uint32_t e = 0; e < n_tied; ++e) hit |= asc == (uint32_t)__builtin_amdgcn_readlane((int)tie, (int)e);
+        return group_bits(__ballot(hit), lane) != 0;
+    }
+
+    // N pairs from their lines in one orientation, ANDed into both chains: a
+    // pair's line is its own for the chain that it ascends or descends with
+    // (own = ~0: the >= chain). w: lane u of the group holds pair u's word
+    // (offset, and its direction in bit 31); lanes with sk set are left out.
+    // The lines of lanes with comp set are complemented.
+    template <int N, bool SKIP>
+    __device__ __forceinline__ void lines(Rows &o, int64_t panel, uint32_t w, uint32_t rest, uint32_t sk, uint32_t comp) const
+    {
+        // (rare in most calls: its broadcasts stay here, not in registers of
+        // the loop around it)
+        asm volatile("" : "+v"(w));
+        __builtin_amdgcn_sched_barrier(0);
+        const auto rs = rsrc(panel);
+        Bits f[N];
+        each<N>([&](auto u) { f[u] = load(rs, line(group_bcast<u>(w))); });
+        each<N>([&](auto u) {
+            const uint32_t m = (uint32_t)((int32_t)group_bcast<u>(w) >> 31) ^ rest;
+            const uint32_t s = SKIP ? group_bcast<u>(sk) : 0u, c = group_bcast<u>(comp);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t x = f[u].w[q] ^ c;
+                o.p.w[q] &= x | m | s;
+                if (NEG) o.n.w[q] &= x | ~m | s;
+                // (pair by pair: words held back to be folded together
+                // would take registers that the hot path pays for)
+                asm volatile("" : "+v"(o.p.w[q]), "+v"(o.n.w[q]));
+            }
+        });
+    }
+    // N pairs in both orientations: asc as above, desc the offset of the
+    // other orientation's line, which the build has written for the pairs
+    // with a tie (`both` set) and for every pair of a dirty chunk; the
+    // others' is the complement of the ascending one.
+    template <int N, bool SKIP>
+    __device__ __forceinline__ void both_ways(Rows &o, int64_t panel, uint32_t asc, uint32_t desc, uint32_t sk, bool both) const
+    {
+        lines<N, SKIP>(o, panel, asc, 0u, sk, 0u);
+        lines<N, SKIP>(o, panel, both ? (desc & kHeadOffset) | (asc & ~kHeadOffset) : asc, ~0u, sk, both ? 0u : ~0u);
+    }
+
+    // Masks of the group's individual (its index in the request).
+    __device__ __forceinline__ void put_masks(const Rows &o, int64_t panel, int64_t ind, bool there) const
+    {
+        if (!(d.mmask || d.nmask)) return;
+        int32_t jj = j;
+        asm volatile("" : "+v"(jj));  // (no address kept in registers for calls without masks)
+        const int64_t words = (d.rows + 63) / 64, word = panel * (kPanelRows / 64) + 2 * jj;
+        auto put = [&](uint64_t *m, const Bits &v) {
+            if (word < words) m[ind * words + word] = (uint64_t)v.w[0] | ((uint64_t)v.w[1] << 32);
+            if (word + 1 < words) m[ind * words + word + 1] = (uint64_t)v.w[2] | ((uint64_t)v.w[3] << 32);
+        };
+        Bits m, e;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            m.w[q] = o.p.w[q] | o.n.w[q];
+            e.w[q] = o.n.w[q] & ~o.p.w[q];
+        }
+        if (there && d.mmask) put(d.mmask, m);
+        if (there && d.nmask) put(d.nmask, e);
+    }
+    // The group's counts on the panel, in each of its lanes: matched, and
+    // negative in the high half (at most 1,024 rows).
+    __device__ __forceinline__ uint32_t counts(const Rows &o) const
+    {
+        uint32_t c = 0, e = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c += (uint32_t)__builtin_popcount(o.p.w[q] | o.n.w[q]);
+            if (NEG) e += (uint32_t)__builtin_popcount(o.n.w[q] & ~o.p.w[q]);
+        }
+        return group_total(c | (e << 16));
+    }
+    __device__ __forceinline__ void add(int64_t ind, uint32_t c) const
+    {
+        if (c & 0xffffu) atomicAdd(d.matched + ind, (int32_t)(c & 0xffffu));
+        if (NEG && c >> 16 && d.negative) atomicAdd(d.negative + ind, (int32_t)(c >> 16));
+    }
+
+    // LDS of a wave: the step's headers, and the individuals with rows left
+    // past the window: the two chains' rows and (k, CSR start, index). Eight
+    // of them are finished together, whichever steps they come from.
+    struct Shared {
+        uint32_t head[kStep][8];
+        Bits p[kQueue][kGroup], n[kQueue][kGroup];
+        int4 who[kQueue];
+    };
+    // The group's header, from LDS each time that it is needed (not kept in
+    // registers in between).
+    __device__ __forceinline__ void read_head(const Shared *q, uint32_t (&w)[8]) const
+    {
+        int32_t at = g;
+        asm volatile("" : "+v"(at));
+        const uint4 *p = reinterpret_cast<const uint4 *>(q->head[at]);
+        const uint4 x = p[0], y = p[1];
+        w[0] = x.x, w[1] = x.y, w[2] = x.z, w[3] = x.w;
+        w[4] = y.x, w[5] = y.y, w[6] = y.z, w[7] = y.w;
+    }
+    __device__ __forceinline__ void finish_queued(Shared *q, int32_t from, int32_t count, int64_t panel, bool dirty,
+                                                  uint32_t n_tied, uint32_t tie)
+    {
+        const bool mine = g < count;
+        const int32_t at = from + (mine ? g : 0);
+        const int4 who = q->who[at];
+        Rows o;
+        o.p = q->p[at][j];
+        o.n = q->n[at][j];
+        const int32_t k = who.x;
+        const int32_t *cc = d.colidx + who.y;
+        bool left = mine;
+#pragma unroll 1
+        for (int32_t u = 8; __ballot(left && u < k) != 0; u += 4) {
+            if (left && u < k) {
+                // lane j: column u - 1 + j and the next
+                const uint32_t a = (uint32_t)cc[min(u - 1 + j, k - 1)], b = row_next(a);
+                const uint32_t f = pair_offset(cols, a, b), r = pair_offset(cols, b, a);
+                const uint32_t asc = min(f, r) | (f > r ? 0x80000000u : 0u), sk = a == b ? ~0u : 0u;
+                bool exact = dirty, both = dirty;
+                if (!dirty) {
+                    const auto rs = rsrc(panel);
+                    Bits w[4];
+                    each<4>([&](auto e) { w[e] = load(rs, line(group_bcast<e>(asc))); });
+                    if (n_tied) exact = listed(j < 4 ? asc : kNoPair, tie, n_tied, both);
+                    if (!exact)
+                        each<4>([&](auto e) {
+                            const uint32_t m = (uint32_t)((int32_t)group_bcast<e>(asc) >> 31), s = group_bcast<e>(sk);
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) {
+                                o.p.w[x] &= (w[e].w[x] ^ m) | s;
+                                if (NEG) o.n.w[x] &= ~(w[e].w[x] ^ m) | s;
+                                asm volatile("" : "+v"(o.p.w[x]), "+v"(o.n.w[x]));
+                            }
+                        });
+                }
+                if (exact) both_ways<4, true>(o, panel, asc, max(f, r), sk, both);
+                if (COUNT && j == 0) steps += (uint64_t)min(4, k - u);
+                left = group_bits(__ballot(o.any()), lane) != 0;
+            }
+        }
+        put_masks(o, panel, who.z, mine);
+        const uint32_t c = counts(o);
+        if (mine && j == 0) add(who.z, c);
+    }
+
+    // Individuals [first, first + n) of the request (at most 64), eight per
+    // step, on one panel.
+    __device__ __forceinline__ void item(const IndHead *__restrict__ heads, int32_t first, int32_t n, int64_t panel, Shared *q)
+    {
+        const uint32_t *tl = ties(panel);
+        const uint32_t nt = __builtin_amdgcn_readfirstlane(tl[0]), nan = __builtin_amdgcn_readfirstlane(tl[1]);
+        const bool dirty = nt > (uint32_t)kTieMax || nan != 0;
+        const uint32_t n_tied = dirty ? 0u : nt, tie = n_tied ? tl[kTieList + (lane & (kTieMax - 1))] : 0u;
+        // headers of 8 words; the descending orientations' offsets past them
+        const uint32_t *hw = reinterpret_cast<const uint32_t *>(heads + d.head_base) + 8 * (int64_t)first;
+        const uint32_t *hd = hw + 8 * (int64_t)d.n;
+        auto at = [&](int32_t i) { return (uint32_t)(8 * min(i + g, n - 1) + j); };
+        const bool last = (panel + 1) * kPanelRows > d.rows;
+        uint32_t h = __builtin_nontemporal_load(hw + at(0));
+        uint32_t acc = 0;
+        int32_t queued = 0;
+#pragma unroll 1
+        for (int32_t i = 0; i < n || queued > 0; i += kStep) {
+            if (i < n) {
+                // lane j of the group has word j of its header; all of them
+                // to all of its lanes
+                q->head[g][j] = h;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const uint32_t flags = q->head[g][0];
+                Rows o;
+                bool exact = dirty, both = dirty;
+                if (!dirty) {
+                    const auto rs = rsrc(panel);
+                    uint32_t head[8];
+                    read_head(q, head);
+                    Bits w[7];
+#pragma unroll
+                    for (int u = 0; u < 7; ++u) w[u] = load(rs, line(head[u]));
+                    h = __builtin_nontemporal_load(hw + at(i + kStep));
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        uint32_t a = ~0u, b = 0;
+#pragma unroll
+                        for (int u = 0; u < 7; ++u) {
+                            const uint32_t m = (uint32_t)((int32_t)head[u] >> 31);
+                            a &= w[u].w[x] ^ m;
+                            if (NEG) b |= w[u].w[x] ^ m;
+                        }
+                        o.p.w[x] = a;
+                        o.n.w[x] = NEG ? ~b : 0u;
+                        asm volatile("" : "+v"(o.p.w[x]), "+v"(o.n.w[x]));
+                    }
+                    if (n_tied) exact = listed(j < 7 ? q->head[g][j] : kNoPair, tie, n_tied, both);
+                } else {
+                    h = __builtin_nontemporal_load(hw + at(i + kStep));
+                }
+                if (exact) {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) o.p.w[x] = ~0u, o.n.w[x] = NEG ? ~0u : 0u;
+                    both_ways<7, false>(o, panel, q->head[g][j], __builtin_nontemporal_load(hd + at(i)), 0, both);
+                }
+                const bool there = i + g < n;
+                const bool live = there && (flags & kHeadValid) != 0;
+                if (last || __ballot(live) != ~0ull) {  // the matrix's rows, the valid individuals
+                    int32_t rows = (int32_t)min(d.rows - panel * kPanelRows, (int64_t)kPanelRows);
+                    asm volatile("" : "+s"(rows));
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const int32_t c = rows - (128 * j + 32 * x);
+                        const uint32_t v = !live ? 0u : c >= 32 ? ~0u : c <= 0 ? 0u : ((1u << c) - 1u);
+                        o.p.w[x] &= v;
+                        o.n.w[x] &= v;
+                    }
+                }
+                if (COUNT && j == 0 && live) steps += 7;
+                const uint64_t any = __ballot(o.any());
+                const bool wait = (flags & kHeadLonger) != 0 && group_bits(any, lane) != 0;
+                const uint64_t waiting = __ballot(wait), leads = waiting & 0x0101010101010101ull;
+                if (waiting) {
+                    if (wait) {
+                        // (the leading lanes of the groups before this one)
+                        const int32_t to = queued - (j > 0 ? 1 : 0) +
+                                           (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(leads >> 32),
+                                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)leads, 0));
+                        q->p[to][j] = o.p;
+                        q->n[to][j] = o.n;
+                        if (j == 0) {
+                            uint32_t head[8], k = 0;  // (six bits in each of words 1 .. 6)
+                            read_head(q, head);
+#pragma unroll
+                            for (int u = 1; u < 7; ++u) k |= (head[u] & 63u) << (6 * (u - 1));
+                            q->who[to] = make_int4((int32_t)k, (int32_t)head[7], first + i + g, 0);
+                        }
+                    }
+                    queued += (int32_t)__popcll(leads);
+                }
+                put_masks(o, panel, first + i + g, there && !wait);
+                if (any & ~waiting) {
+                    const uint32_t c = counts(o);
+                    if (j == i / kStep && !wait) acc = c;
+                }
+            }
+            // eight that wait, or the last ones
+            if (queued >= kStep || (i + kStep >= n && queued > 0)) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const int32_t now = min(queued, kStep);
+                queued -= now;
+                finish_queued(q, queued, now, panel, dirty, n_tied, tie);
+            }
+        }
+        if (kStep * j + g < n) add(first + kStep * j + g, acc);
+    }
+};
+
+// The plain launch: a grid of (8 x groups, panels / 8 over y and z) blocks.
+// Block (x, y, z) works on panel 8 (z Y + y) + x mod 8 and group x / 8 (P
+// individuals, `per` to a wave): blocks are dispatched x first, and with
+// gridDim.x a multiple of 8 the linear block index is x mod 8 modulo 8, so
+// on MI355X's round-robin placement of blocks over the eight XCDs the blocks
+// of a panel all run on one XCD and share its L2, and the blocks of eight
+// consecutive panels (all their groups) are dispatched together.
+// (72 vector registers: seven waves per SIMD without spills)
+template <bool NEG, bool COUNT>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7)))
+k_eval_pairs(ReqDesc d, const IndHead *__restrict__ heads, int32_t P, int32_t per, unsigned long long *step_counter)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int64_t panel = 8 * ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) + (blockIdx.x & 7);
+    if (panel * kPanelRows >= d.rows) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    uint64_t steps = 0;
-    pairs_item<NEG, COUNT, PIPE>(d, heads, i0, np, chunk, lane, wave, blockDim.x / kWave, steps);
-    if (COUNT && lane == 0 && steps) atomicAdd(step_counter, (unsigned long long)steps);
+    const int32_t i0 = (int32_t)(blockIdx.x >> 3) * P;
+    const int32_t first = i0 + wave * per, n = min(min(d.n, i0 + P) - first, per);
+    if (n <= 0) return;
+    using Wave = PairWave<NEG, COUNT>;
+    Wave w(d, lane);
+    w.item(heads, first, n, panel, reinterpret_cast<typename Wave::Shared *>(lds) + wave);
+    if (COUNT && w.steps) atomicAdd(step_counter, (unsigned long long)w.steps);
 }
 
 // The batched launch: a fixed grid (a multiple of 8 blocks) over eight item
-// lists, one per XCD slice: block b walks list b mod 8 with a stride of
-// grid / 8 (items b / 8, b / 8 + grid / 8, ...), so the blocks of a slice
-// take its items in order, all of them near the same chunk at a time, with
-// no counter to contend for. A list walks its slice's chunks in order,
+// lists, one per XCD slice. Block b starts on item b / 8 of list b mod 8;
+// short lists are walked with a stride of grid / 8 from there, with no
+// counter to contend for, long ones (`dynamic`) by taking the list's next
+// item from a counter, fetched while the block works on the item before. A
+// stride lets the blocks of a slice drift apart over the items, so that two
+// panels and more are in the L2 at a time; from the counter they stay
+// within one (the batch above: 19.7 to 9.5 million L2 misses, 462 -> 383
+// us). The counters have cache lines of their own: eight in one line took
+// 24 ns an item. A list walks its slice's panels in order,
 // segment by segment (the requests that read one set of bitmaps), every
-// group of every request of the segment on a chunk before the next chunk:
-// item k of slice x in segment g is chunk 8 (l / groups) + x and group
+// group of every request of the segment on a panel before the next panel:
+// item k of slice x in segment g is panel 8 (l / groups) + x and group
 // l mod groups (l = k minus the segment's first item in the list), the
 // group found among the segment's requests by their first groups.
+// (five waves per SIMD, without spills: 402 us for the batch above against
+// 412 with six and a few)
 template <bool COUNT>
-__global__ void __launch_bounds__(1024) k_eval_pairs_batch(const PairQueues *__restrict__ pq,
-                                                           const ReqDesc *__restrict__ descs,
-                                                           const PairSeg *__restrict__ segs,
-                                                           const int32_t *__restrict__ seg_req,
-                                                           const int32_t *__restrict__ seg_gstart,
-                                                           const IndHead *__restrict__ heads,
-                                                           unsigned long long *step_counter)
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
+k_eval_pairs_batch(const PairQueues *__restrict__ pq, const ReqDesc *__restrict__ descs,
+                   const PairSeg *__restrict__ segs, const int32_t *__restrict__ seg_req,
+                   const int32_t *__restrict__ seg_gstart, const IndHead *__restrict__ heads,
+                   uint32_t *__restrict__ next, unsigned long long *step_counter)
 {
+    extern __shared__ __align__(16) unsigned char lds[];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int W = blockDim.x / kWave;
     const int32_t n_seg = pq->n_seg;
     const int32_t P = min(pq->P, 64 * W);  // (the planner keeps it there)
+    const int32_t per = (P + W - 1) / W;
     const int slice = (int)(blockIdx.x % 8);
     const int32_t stride = (int32_t)(gridDim.x / 8);
     const int32_t total = pq->total[slice];
     uint64_t steps = 0;
     int32_t g = 0;  // (items come in order: the segment only moves forward)
-    for (int32_t k = (int32_t)(blockIdx.x / 8); k < total; k += stride) {
+    __shared__ int32_t ticket[2];
+    int slot = 0;
+    for (int32_t k = (int32_t)(blockIdx.x / 8); k < total;) {
+        int32_t mine = 0;
+        if (pq->dynamic && threadIdx.x == 0) mine = (int32_t)atomicAdd(next + slice * kPairNextStride, 1u);
         while (g + 1 < n_seg && segs[g + 1].base[slice] <= k) ++g;
         const int32_t local = k - segs[g].base[slice];
         const int32_t groups = segs[g].groups;
-        const int32_t chunk = 8 * (local / groups) + slice;
+        const int64_t panel = 8 * (int64_t)(local / groups) + slice;
         const int32_t pos = local % groups;
         int32_t lo = segs[g].e0, hi = segs[g].e0 + segs[g].n_req - 1;  // the last entry starting at or before pos
         while (lo < hi) {
@@ -442,46 +746,75 @@ __global__ void __launch_bounds__(1024) k_eval_pairs_batch(const PairQueues *__r
             else hi = mid - 1;
         }
         const ReqDesc &d = descs[seg_req[lo]];
-        const int32_t i0 = (pos - seg_gstart[lo]) * P;
-        const int32_t np = min(P, d.n - i0);
-        if (d.flags & kFlagNeg) pairs_item<true, COUNT, true>(d, heads, i0, np, chunk, lane, wave, W, steps);
-        else pairs_item<false, COUNT, true>(d, heads, i0, np, chunk, lane, wave, W, steps);
+        const int32_t first = (pos - seg_gstart[lo]) * P + wave * per;
+        const int32_t n = min(min(d.n, (pos - seg_gstart[lo]) * P + P) - first, per);
+        if (n <= 0) {
+        } else if (d.flags & kFlagNeg) {
+            using Wave = PairWave<true, COUNT>;
+            Wave w(d, lane);
+            w.item(heads, first, n, panel, reinterpret_cast<typename Wave::Shared *>(lds) + wave);
+            steps += w.steps;
+        } else {
+            using Wave = PairWave<false, COUNT>;
+            Wave w(d, lane);
+            w.item(heads, first, n, panel, reinterpret_cast<typename Wave::Shared *>(lds) + wave);
+            steps += w.steps;
+        }
+        if (pq->dynamic) {
+            if (threadIdx.x == 0) ticket[slot] = mine;
+            __syncthreads();
+            k = stride + __builtin_amdgcn_readfirstlane(ticket[slot]);
+            slot ^= 1;
+        } else {
+            k += stride;
+        }
     }
-    if (COUNT && lane == 0 && steps) atomicAdd(step_counter, (unsigned long long)steps);
+    if (COUNT && steps) atomicAdd(step_counter, (unsigned long long)steps);
 }
 
 }  // namespace
 
 int64_t pair_words(int64_t rows) { return (rows + kChunkRows - 1) / kChunkRows * kChunkWords; }
 
+int64_t pair_panels(int64_t rows) { return (rows + kPanelRows - 1) / kPanelRows; }
+
 int64_t pair_tie_bytes(int64_t rows)
 {
     return (rows + kChunkRows - 1) / kChunkRows * kTieWords * (int64_t)sizeof(uint32_t);
 }
 
-hipError_t launch_pair_bits(const float *X, int64_t rows, int64_t ld, int32_t cols, bool subst, float fill,
+hipError_t launch_pair_bits(const float *X, int64_t rows, int64_t ld, int32_t cols, bool full, bool subst, float fill,
                             uint32_t *G, int64_t w32, uint32_t *T, hipStream_t s)
 {
     if (cols < 1 || cols > kMaxPairCols || w32 != pair_words(rows) || ld % 64 != 0) return hipErrorInvalidValue;
     const int64_t chunks = w32 / kChunkWords;
     const int64_t per_slice = (chunks + 7) / 8;
     if (per_slice > 65535) return hipErrorInvalidValue;
-    // Four columns per block past 128 columns (the loads of each b shared
-    // four ways), two below, where fewer blocks per chunk would be left.
-    const bool four = cols > 128;
-    const int A = four ? 4 : 2;
-    const dim3 grid((unsigned)(8 * ((cols + A - 1) / A)), (unsigned)per_slice);
+    // Columns b per block: 32; 64 where the tiles still make eight blocks per
+    // CU (less time goes to staging the columns a: 436,444 x 310 3.12 -> 2.99
+    // ms), 16 where they make less than two (1,000 x 50 45 -> 27 us). At
+    // 54,675 x 178 16, 32 and 64 take 199, 190 and 209 us.
+    auto tiles = [&](int32_t r) { return (int64_t)((cols + kBuildCols - 1) / kBuildCols) * ((cols + r - 1) / r); };
+    const int32_t run = tiles(64) * chunks >= 2048 ? 64 : tiles(32) * chunks < 512 ? 16 : 32;
+    const dim3 grid((unsigned)(8 * tiles(run)), (unsigned)per_slice), block(kBuildWaves * kWave);
     const int sub = subst ? 1 : 0;
     clear_last_error();
-    if (four) hipLaunchKernelGGL(k_pair_bits<4>, grid, dim3(64), 0, s, X, rows, ld, cols, sub, fill, G, T);
-    else hipLaunchKernelGGL(k_pair_bits<2>, grid, dim3(64), 0, s, X, rows, ld, cols, sub, fill, G, T);
+    if (full) {
+        hipLaunchKernelGGL(k_pair_bits<true>, grid, block, 0, s, X, rows, ld, cols, sub, fill, run, 0, G, T);
+    } else {
+        hipLaunchKernelGGL(k_pair_bits<false>, grid, block, 0, s, X, rows, ld, cols, sub, fill, run, 0, G, T);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        // the chunks whose list has overflowed: both orientations
+        hipLaunchKernelGGL(k_pair_bits<true>, grid, block, 0, s, X, rows, ld, cols, sub, fill, run, kTieMax, G, T);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_prep_pairs(const ReqDesc &d, IndHead *heads, hipStream_t s)
 {
     const int threads = 256;
-    const int per_block = threads / kWave;  // one wave per individual
+    const int per_block = threads / 16;  // 16 lanes per individual
     clear_last_error();
     hipLaunchKernelGGL(k_prep_pairs, dim3((d.n + per_block - 1) / per_block), dim3(threads), 0, s, d, heads);
     return hipGetLastError();
@@ -495,48 +828,50 @@ static const void *pairs_batch_kernel(bool count)
 int pairs_batch_occupancy(int32_t W)
 {
     int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, pairs_batch_kernel(false), W * kWave, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, pairs_batch_kernel(false), W * kWave, W * kWaveLds) !=
+        hipSuccess)
         return 0;
     return blocks;
 }
 
 hipError_t launch_pairs_batch(const PairQueues *pq, const ReqDesc *descs, const PairSeg *segs,
-                              const int32_t *seg_req, const int32_t *seg_gstart, const IndHead *heads, int32_t W,
-                              int32_t grid, unsigned long long *step_counter, hipStream_t s)
+                              const int32_t *seg_req, const int32_t *seg_gstart, const IndHead *heads,
+                              uint32_t *next, int32_t W, int32_t grid, unsigned long long *step_counter, hipStream_t s)
 {
     if (W < 1 || W > 16 || grid < 8 || grid % 8 != 0) return hipErrorInvalidValue;
     const bool count = step_counter != nullptr;
     clear_last_error();
     if (count)
-        hipLaunchKernelGGL(k_eval_pairs_batch<true>, dim3(grid), dim3(W * kWave), 0, s, pq, descs, segs, seg_req,
-                           seg_gstart, heads, step_counter);
+        hipLaunchKernelGGL(k_eval_pairs_batch<true>, dim3(grid), dim3(W * kWave), W * kWaveLds, s, pq, descs, segs, seg_req,
+                           seg_gstart, heads, next, step_counter);
     else
-        hipLaunchKernelGGL(k_eval_pairs_batch<false>, dim3(grid), dim3(W * kWave), 0, s, pq, descs, segs, seg_req,
-                           seg_gstart, heads, step_counter);
+        hipLaunchKernelGGL(k_eval_pairs_batch<false>, dim3(grid), dim3(W * kWave), W * kWaveLds, s, pq, descs, segs, seg_req,
+                           seg_gstart, heads, next, step_counter);
     return hipGetLastError();
 }
 
-const void *pairs_kernel(uint32_t flags, bool count, int32_t P, int32_t W)
+hipError_t launch_pairs(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,
+                        unsigned long long *step_counter, hipStream_t s)
 {
-    const bool neg = (flags & kFlagNeg) != 0;
-    // Loading the next headers early pays once a wave takes four or more
-    // pairs of individuals per item; with fewer, the extra scalar registers
-    // cost more than the hidden latency.
-    const bool pipe = (P + W - 1) / W >= kPipeMin;
-    if (pipe) {
-        if (count) return neg ? (const void *)&k_eval_pairs<true, true, true> : (const void *)&k_eval_pairs<false, true, true>;
-        return neg ? (const void *)&k_eval_pairs<true, false, true> : (const void *)&k_eval_pairs<false, false, true>;
+    const int64_t groups = ((int64_t)d.n + P - 1) / P, per_slice = (pair_panels(d.rows) + 7) / 8;
+    const int32_t per = (P + W - 1) / W;
+    if (W < 1 || W > 16 || P < 1 || per > 64 || 8 * groups * W * kWave > 0xffffffffll) return hipErrorInvalidValue;
+    const bool neg = (d.flags & kFlagNeg) != 0;
+    // a slice's panels over y and z (65,535 of each are the grid's limit)
+    const unsigned y = (unsigned)(per_slice < 32768 ? per_slice : 32768), z = (unsigned)((per_slice + y - 1) / y);
+    const dim3 grid((unsigned)(8 * groups), y, z);
+    clear_last_error();
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(W * kWave), W * kWaveLds, s, d, heads, P, per, step_counter);
+    };
+    if (step_counter) {
+        if (neg) go(k_eval_pairs<true, true>);
+        else go(k_eval_pairs<false, true>);
+    } else {
+        if (neg) go(k_eval_pairs<true, false>);
+        else go(k_eval_pairs<false, false>);
     }
-    if (count) return neg ? (const void *)&k_eval_pairs<true, true, false> : (const void *)&k_eval_pairs<false, true, false>;
-    return neg ? (const void *)&k_eval_pairs<true, false, false> : (const void *)&k_eval_pairs<false, false, false>;
-}
-
-// The plain pairs launch's grid: (8 x groups, chunks / 8 rounded up).
-dim3 pairs_grid(int64_t rows, int32_t n, int32_t P)
-{
-    const int64_t groups = (n + P - 1) / P;
-    const int64_t per_slice = ((rows + kChunkRows - 1) / kChunkRows + 7) / 8;
-    return dim3((unsigned)(8 * groups), (unsigned)per_slice);
+    return hipGetLastError();
 }
 
 }  // namespace ebic

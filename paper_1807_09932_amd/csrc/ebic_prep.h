@@ -71,54 +71,110 @@ __device__ __forceinline__ PrepScan prep_scan(const ReqDesc &d, int32_t i, int l
     return sc;
 }
 
-// The pairs header (the IndHead storage, read differently) of the
-// pairwise-order-bitmap kernels.
-struct PairHead {
-    int32_t k;         // columns from begin (0: invalid)
-    int32_t begin;     // CSR start (the last leading repeat of the first column)
-    uint32_t fwd[7];   // byte offsets of the window's pairs of different columns (the last one repeated);
-                       // for k = 1, fwd[0] is the column's diagonal pair
-    uint32_t pad0;
-    uint32_t win[4];   // the window's eight columns, two per word (low half first)
-    uint32_t pad1[2];
-};
-static_assert(sizeof(PairHead) == sizeof(IndHead), "the pairs header reuses the header storage");
+// ---------------------------------------------------------------------------
+// The pairs headers of the pair-bitmap kernels: two arrays of 32 bytes per
+// individual in a request's header storage (64 bytes per individual).
+// The first, read by every evaluation step:
+//   words 0 .. 6   window pair u, (c_u, c_{u+1}): the byte offset in a panel
+//                  of its ascending orientation (bits 7 .. 26), and bit 31
+//                  set where c_u > c_{u+1}. A pair of equal columns is
+//                  implied by the pairs next to it and takes pair 0's place
+//                  (which is of two different columns, or the diagonal pair
+//                  of an individual of one column).
+//                  Word 0 also has bit 0 set for a valid individual and bit
+//                  1 for one of more than eight columns; words 1 .. 6 hold
+//                  k, the columns from the start on, six bits in each (the
+//                  lowest first).
+//   word 7         the CSR start (the last leading repeat of the first column)
+// The second, behind the first array, for panels with ties or missing cells:
+//   words 0 .. 6   the offsets of the descending orientations
+// ---------------------------------------------------------------------------
+constexpr uint32_t kHeadOffset = 0x07ffff80u;
+constexpr uint32_t kHeadValid = 1u, kHeadLonger = 2u;
 
-// One wave per individual: the scan, the outputs' initialisation, and the
-// pairs header. Lane u < 7 forms window pair (u, u + 1); the pairs of
-// different columns are packed to the front in order (a pair (c, c) is
-// implied by the pairs next to it), the last one repeating after them; an
-// individual of one column gets its diagonal pair ("present").
-__device__ __forceinline__ void prep_pairs_wave(const ReqDesc &d, int32_t i, IndHead *__restrict__ heads, int lane)
+// DPP moves within a row of 16 lanes: lane 0 to all of it; lane j + 1 to
+// lane j.
+__device__ __forceinline__ uint32_t row_first(uint32_t v)
 {
-    const PrepScan sc = prep_scan(d, i, lane);
-    if (lane == 0) {
-        d.matched[i] = sc.ok ? 0 : kInvalid;
-        if (d.negative) d.negative[i] = sc.ok ? 0 : kInvalid;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150, 0xf, 0xf, true);  // row_newbcast:0
+}
+__device__ __forceinline__ uint32_t row_next(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x101, 0xf, 0xf, false);  // row_shl:1
+}
+
+// Pair (a, b)'s bytes in a panel: a cache line.
+__device__ __forceinline__ uint32_t pair_offset(uint32_t cols, uint32_t a, uint32_t b)
+{
+    return (a * cols + b) << 7;
+}
+
+struct PairPrep {
+    uint32_t word, desc;  // lane j < 8 of the row: word j of the two headers
+    bool ok;              // a non-empty span of valid columns
+};
+
+// Four individuals per wave, one per row of 16 lanes: individual i of
+// request d (rows with !active do nothing). The row's lanes read its columns
+// 16 at a time, check them against the matrix width and find the leading run
+// of repeats; the window's pairs are formed in lanes 0 .. 6.
+__device__ __forceinline__ PairPrep prep_pairs_quad(const ReqDesc &d, int32_t i, bool active, int lane)
+{
+    const int j = lane & 15, base = lane & 48;
+    auto bits = [&](bool v) { return (uint32_t)(__ballot(v) >> base) & 0xffffu; };
+    int32_t b = 0, e = 0;
+    if (active) {
+        b = d.offsets[i];
+        e = d.offsets[i + 1];
     }
-    uint32_t *hd = reinterpret_cast<uint32_t *>(heads + d.head_base + i);
-    const uint32_t cb = (uint32_t)d.cols * 256u;  // a pair (a, b)'s byte offset: a * cb + b * 256
-    const uint32_t a = (uint32_t)__shfl(sc.win, 8 + min(lane, 7));
-    const uint32_t c = (uint32_t)__shfl(sc.win, 8 + min(lane + 1, 7));
-    const int q = (lane - 10) & 3;  // lanes 10..13: columns 2q, 2q + 1
-    const uint32_t pk = (uint32_t)__shfl(sc.win, 8 + 2 * q) | ((uint32_t)__shfl(sc.win, 9 + 2 * q) << 16);
-    const bool distinct = lane < 7 && a != c;
-    const uint64_t dm = __ballot(distinct);
-    const uint32_t off = a * cb + (c << 8);
-    const int nf = __popcll(dm);
-    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)a, 0);
-    const uint32_t last = nf == 0 ? w0 * cb + (w0 << 8)
-                                  : (uint32_t)__builtin_amdgcn_readlane((int)off, 63 - __clzll(dm));
-    if (!sc.ok) {
-        if (lane < 16) hd[lane] = 0u;
-        return;
+    const bool span = b >= 0 && e > b;
+    const int32_t len = span ? e - b : 1;
+    int32_t c = 0;
+    if (span) c = d.colidx[b + min(j, len - 1)];
+    const int32_t c0 = (int32_t)row_first((uint32_t)c);
+    bool bad = c < 0 || c >= d.cols;
+    uint32_t differ = bits(span && c != c0);
+    int32_t run = differ ? (int32_t)__builtin_ctz(differ) - 1 : len - 1;
+    for (int32_t r = 16; __ballot(span && r < len) != 0; r += 16) {
+        const int32_t x = span && r + j < len ? d.colidx[b + r + j] : c0;
+        bad |= x < 0 || x >= d.cols;
+        const uint32_t df = bits(span && x != c0);
+        if (!differ && df) run = r + (int32_t)__builtin_ctz(df) - 1;
+        differ |= df;
     }
-    if (distinct) hd[2 + __popcll(dm & ((1ull << lane) - 1))] = off;
-    if (lane >= nf && lane < 7) hd[2 + lane] = last;
-    if (lane == 0) hd[0] = (uint32_t)sc.k;
-    if (lane == 1) hd[1] = (uint32_t)sc.bb;
-    if (lane == 9 || lane == 14 || lane == 15) hd[lane] = 0u;
-    if (lane >= 10 && lane < 14) hd[lane] = pk;
+    PairPrep p;
+    p.ok = span && bits(bad) == 0;
+    const int32_t k = p.ok ? len - run : 0, bb = b + run;
+    // (past a leading run the window's columns are read again)
+    if (p.ok && run > 0) c = d.colidx[bb + min(j, k - 1)];
+    const uint32_t cols = (uint32_t)d.cols, a = (uint32_t)c, n = row_next(a);
+    uint32_t f = pair_offset(cols, a, n), r = pair_offset(cols, n, a);
+    const uint32_t f0 = row_first(f), r0 = row_first(r);
+    if (a == n) {
+        f = f0;
+        r = r0;
+    }
+    const uint32_t extra = j == 0 ? kHeadValid | (k > 8 ? kHeadLonger : 0u) : ((uint32_t)k >> (6 * (j - 1) & 31)) & 63u;
+    p.word = j < 7 ? min(f, r) | (f > r ? 0x80000000u : 0u) | extra : (uint32_t)bb;
+    p.desc = max(f, r);
+    if (!p.ok) p.word = p.desc = 0;
+    return p;
+}
+
+// The header and the outputs' initialisation.
+__device__ __forceinline__ void prep_pairs_store(const ReqDesc &d, int32_t i, const PairPrep &p,
+                                                 IndHead *__restrict__ heads, int lane)
+{
+    const int j = lane & 15;
+    if (j < 8) {
+        uint32_t *h = reinterpret_cast<uint32_t *>(heads + d.head_base) + 8 * (int64_t)i + j;
+        h[0] = p.word;
+        h[8 * (int64_t)d.n] = p.desc;
+    }
+    if (j == 0) {
+        d.matched[i] = p.ok ? 0 : kInvalid;
+        if (d.negative) d.negative[i] = p.ok ? 0 : kInvalid;
+    }
 }
 
 }  // namespace ebic

@@ -296,7 +296,8 @@ void build_pairs(ebic_ctx *ctx, Matrix &m, bool include)
         hip_check(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "hipStreamCreate");
         uint32_t *F = const_cast<uint32_t *>(pairs_marks(m, G));
         hip_check(hipMemsetAsync(F, 0, (size_t)pairs_mark_bytes(m), s), "hipMemsetAsync");
-        hip_check(launch_pair_bits(m.X, m.dev.rows, m.dev.ld, m.dev.cols, subst, m.dev.fill, G, w32, F, s),
+        hip_check(launch_pair_bits(m.X, m.dev.rows, m.dev.ld, m.dev.cols, m.has_missing != 0, subst, m.dev.fill, G, w32,
+                                   F, s),
                   "pair bitmaps kernel");
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
         hip_check(hipStreamDestroy(s), "hipStreamDestroy");
@@ -351,7 +352,7 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
         return st == STAGE_BYTES ? have_bytes : st == STAGE_HALVES ? have_halves : st == STAGE_T10 ? have_t10 : false;
     };
     // Pairwise order bitmaps (built on first use where they fit): no tile,
-    // one wave per individual and 2,048-row chunk.
+    // a wave per eight individuals and 1,024-row panel.
     if (cfg.staging == STAGE_PAIRS) {
         bool have_pairs = pairs_for(m, include) != nullptr;
         if (!have_pairs && codes != CODES_EXISTING && pairs_buildable(m) && !m.pairs_failed) {
@@ -371,13 +372,14 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
             cfg.L = 1;
             cfg.cnt16 = false;
             if (asked_P <= 0) {
-                // Individuals per wave: up to 8 where the chunks and
-                // individuals give at least two waves per resident slot,
-                // fewer (down to one) on smaller work.
-                const int64_t chunks = pair_words(m.dev.rows) / 64;
-                const int64_t slots = (int64_t)ctx->cu_count * 32;
-                const int64_t per_wave = std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)n * chunks / (2 * slots)));
-                cfg.P = (int32_t)(per_wave * cfg.W);
+                // Eight individuals per wave (one step); two and four steps
+                // where that leaves at least two waves per resident slot
+                // (436,444 x 64, 800 individuals: 34.0, 31.6 and 32.8 us
+                // with one, two and four steps; 20,000 x 200 12.8, 13.6 and
+                // 13.7 us).
+                const int64_t slots = (int64_t)ctx->cu_count * 28;
+                const int64_t steps = ((int64_t)n + 7) / 8 * pair_panels(m.dev.rows);
+                cfg.P = 8 * cfg.W * (steps >= 16 * slots ? 4 : steps >= 4 * slots ? 2 : 1);
             }
             cfg.P = std::max(1, std::min({cfg.P, 64 * cfg.W, std::max(1, n)}));
             cfg.blocks = (int32_t)(pair_words(m.dev.rows) / 64);  // (reported: the chunks)

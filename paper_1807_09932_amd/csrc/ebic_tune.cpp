@@ -52,12 +52,12 @@ static int32_t default_L(int32_t cols) { return cols <= 64 ? 4 : (cols <= 128 ? 
 LaunchCfg default_cfg(int64_t rows, int32_t cols, int32_t n)
 {
     // The pairwise order bitmaps up to 512 columns (cols / 32 times the
-    // FP32 matrix's bytes, built on first use): four waves per block, the
+    // FP32 matrix's bytes, built on first use): two waves per block, the
     // individuals per wave chosen at planning (P = 0).
     if (cols <= kDefaultPairCols) {
         LaunchCfg c;
         c.L = 1;
-        c.W = 4;
+        c.W = 2;
         c.P = 0;
         c.staging = STAGE_PAIRS;
         c.blocks = 0;
@@ -391,10 +391,10 @@ ebic_status ebic_autotune(ebic_ctx *ctx, const ebic_request *sample, int32_t n_r
                 std::vector<std::pair<float, LaunchCfg>> timed;
                 // The pairwise order bitmaps (built by the first of these
                 // evaluations where they fit): waves per block and
-                // individuals per wave, one chunk per block.
+                // individuals per wave, one panel per block.
                 if (cols <= kDefaultPairCols)
                     for (int W : {2, 4, 8})
-                        for (int per_wave : {1, 2, 4, 8, 16}) {
+                        for (int per_wave : {8, 16, 32, 64}) {
                             LaunchCfg c;
                             c.L = 1;
                             c.W = W;
@@ -459,7 +459,7 @@ ebic_status ebic_autotune(ebic_ctx *ctx, const ebic_request *sample, int32_t n_r
                     auto batch_once = [&] { return ebic_eval_batch(ctx, sample, n_reqs, s) == EBIC_OK; };
                     if (max_cols <= kDefaultPairCols)
                         for (int W : {2, 4, 8})
-                            for (int per_wave : {1, 2, 4, 8, 16}) {
+                            for (int per_wave : {8, 16, 32, 64}) {
                                 LaunchCfg c;
                                 c.L = 1;
                                 c.W = W;
