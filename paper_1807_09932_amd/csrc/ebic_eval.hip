@@ -2638,6 +2638,12 @@ hipError_t launch_eval(const ReqDesc &d, IndHead *heads, const LaunchCfg &cfg,
                        hipEvent_t ev1)
 {
     if (d.n <= 0) return hipSuccess;
+    if (cfg.staging == STAGE_PAIRS && cfg.few) {
+        hipError_t e;
+        if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;
+        if ((e = launch_pairs_few(d, cfg.W, step_counter, s)) != hipSuccess) return e;
+        return ev1 ? hipEventRecord(ev1, s) : hipSuccess;
+    }
     if (cfg.staging == STAGE_PAIRS) {
         hipError_t e = launch_prep_pairs(d, heads, s);
         if (e != hipSuccess) return e;

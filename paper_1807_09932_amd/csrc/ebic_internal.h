@@ -76,6 +76,7 @@ struct LaunchCfg {
     int32_t staging = STAGE_LDS;
     int32_t blocks = 0;   // plain: tile ranges per group; batch: persistent grid; 0 = derive
     bool cnt16 = false;   // plain: counts as 16-bit halves (16-bit codes; set by the planner)
+    bool few = false;     // plain, pair bitmaps: the one-kernel launch for few panels (set by the planner)
 };
 
 // A resident matrix as the kernels see it.
@@ -274,6 +275,11 @@ hipError_t launch_pair_bits(const float *X, int64_t rows, int64_t ld, int32_t co
 hipError_t launch_prep_pairs(const ReqDesc &d, IndHead *heads, hipStream_t s);
 hipError_t launch_pairs(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,
                         unsigned long long *step_counter, hipStream_t s);
+// The same for matrices of at most kFewPanels panels, prep included, in one
+// kernel of blocks of W waves (no headers).
+constexpr int32_t kFewPanels = 64;
+constexpr int32_t kPairDefaultW = 2;  // waves per block of the default plain shape
+hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, unsigned long long *step_counter, hipStream_t s);
 int64_t pair_panels(int64_t rows);  // 1,024-row panels (the evaluation's unit of rows)
 
 // The pair items of a batch: eight lists, one per XCD slice (a slice: the

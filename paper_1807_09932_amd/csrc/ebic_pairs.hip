@@ -91,6 +91,7 @@ constexpr int kGroup = 8;         // lanes per individual (16 bytes of a pair's 
 constexpr int kStep = kWave / kGroup;  // individuals per wave and step
 constexpr int kQueue = 2 * kStep - 1;  // individuals that wait for their columns past the window
 // LDS of a wave: a step's headers, and the queue's rows and (k, start, index).
+constexpr size_t kWaveLdsFew = kStep * (2 * 128 + 16);
 constexpr size_t kWaveLds = kStep * 32 + kQueue * (2 * 128 + 16);
 
 __global__ void __launch_bounds__(256) k_prep_pairs(ReqDesc d, IndHead *__restrict__ heads)
@@ -496,25 +497,67 @@ struct PairWave {
     // LDS of a wave: the step's headers, and the individuals with rows left
     // past the window: the two chains' rows and (k, CSR start, index). Eight
     // of them are finished together, whichever steps they come from.
+    template <int N>
+    struct Queue {
+        Bits p[N][kGroup], n[N][kGroup];
+        int4 who[N];
+    };
     struct Shared {
         uint32_t head[kStep][8];
-        Bits p[kQueue][kGroup], n[kQueue][kGroup];
-        int4 who[kQueue];
+        Queue<kQueue> queue;
     };
+    // What a wave knows of its panel.
+    struct Panel {
+        int64_t at;
+        bool dirty, last;    // both orientations are needed; the matrix's last panel
+        uint32_t n_tied, tie;  // the chunk's listed pairs: their number, entry e in lane e
+    };
+    __device__ __forceinline__ Panel panel_of(int64_t at, uint32_t n_ties, uint32_t nan) const
+    {
+        Panel p;
+        p.at = at;
+        p.dirty = n_ties > (uint32_t)kTieMax || nan != 0;
+        p.last = (at + 1) * kPanelRows > d.rows;
+        p.n_tied = p.dirty ? 0u : n_ties;
+        return p;
+    }
+    __device__ __forceinline__ Panel panel_of(int64_t at) const
+    {
+        const uint32_t *tl = ties(at);
+        Panel p = panel_of(at, __builtin_amdgcn_readfirstlane(tl[0]), __builtin_amdgcn_readfirstlane(tl[1]));
+        p.tie = p.n_tied ? tl[kTieList + (lane & (kTieMax - 1))] : 0u;
+        return p;
+    }
+    // The same from a word loaded before: in lanes 0 .. 31 the list, in lane
+    // 32 the count, in 33 the NaN flag.
+    __device__ __forceinline__ uint32_t panel_word(int64_t at) const
+    {
+        return ties(at)[lane < kTieMax ? kTieList + lane : lane & 1];
+    }
+    __device__ __forceinline__ Panel panel_from(int64_t at, uint32_t word) const
+    {
+        Panel p = panel_of(at, __builtin_amdgcn_readlane(word, kTieMax), __builtin_amdgcn_readlane(word, kTieMax + 1));
+        p.tie = word;
+        return p;
+    }
     // The group's header, from LDS each time that it is needed (not kept in
     // registers in between).
-    __device__ __forceinline__ void read_head(const Shared *q, uint32_t (&w)[8]) const
+    __device__ __forceinline__ void read_head(const uint32_t (*head)[8], uint32_t (&w)[8]) const
     {
         int32_t at = g;
         asm volatile("" : "+v"(at));
-        const uint4 *p = reinterpret_cast<const uint4 *>(q->head[at]);
+        const uint4 *p = reinterpret_cast<const uint4 *>(head[at]);
         const uint4 x = p[0], y = p[1];
         w[0] = x.x, w[1] = x.y, w[2] = x.z, w[3] = x.w;
         w[4] = y.x, w[5] = y.y, w[6] = y.z, w[7] = y.w;
     }
-    __device__ __forceinline__ void finish_queued(Shared *q, int32_t from, int32_t count, int64_t panel, bool dirty,
-                                                  uint32_t n_tied, uint32_t tie)
+    // out(individual, counts) in one lane of each.
+    template <class Queue, class Out>
+    __device__ __forceinline__ void finish_queued(Queue *q, int32_t from, int32_t count, const Panel &pn, Out &&out)
     {
+        const int64_t panel = pn.at;
+        const bool dirty = pn.dirty;
+        const uint32_t n_tied = pn.n_tied, tie = pn.tie;
         const bool mine = g < count;
         const int32_t at = from + (mine ? g : 0);
         const int4 who = q->who[at];
@@ -555,22 +598,97 @@ struct PairWave {
         }
         put_masks(o, panel, who.z, mine);
         const uint32_t c = counts(o);
-        if (mine && j == 0) add(who.z, c);
+        if (mine && j == 0) out(who.z, c);
+    }
+
+    // One step on a panel: the individuals of the headers at `head` (group g:
+    // individual ind of the request, if `there`). Returns the group's counts
+    // and queues the individuals with columns and rows left (their counts
+    // are 0 here). window(w8, w) gives the seven words of the headers'
+    // ascending lines, desc() the lane's word of the second headers.
+    template <class Queue, class Window, class Desc>
+    __device__ __forceinline__ uint32_t step(const uint32_t (*head)[8], Queue *q, int32_t &queued, const Panel &pn,
+                                             int32_t ind, bool there, Window &&window, Desc &&desc)
+    {
+        const int64_t panel = pn.at;
+        const uint32_t flags = head[g][0];
+        Rows o;
+        bool exact = pn.dirty, both = pn.dirty;
+        if (!pn.dirty) {
+            uint32_t w8[8];
+            read_head(head, w8);
+            Bits w[7];
+            window(w8, w);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                uint32_t a = ~0u, b = 0;
+#pragma unroll
+                for (int u = 0; u < 7; ++u) {
+                    const uint32_t m = (uint32_t)((int32_t)w8[u] >> 31);
+                    a &= w[u].w[x] ^ m;
+                    if (NEG) b |= w[u].w[x] ^ m;
+                }
+                o.p.w[x] = a;
+                o.n.w[x] = NEG ? ~b : 0u;
+                asm volatile("" : "+v"(o.p.w[x]), "+v"(o.n.w[x]));
+            }
+            if (pn.n_tied) exact = listed(j < 7 ? head[g][j] : kNoPair, pn.tie, pn.n_tied, both);
+        }
+        if (exact) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) o.p.w[x] = ~0u, o.n.w[x] = NEG ? ~0u : 0u;
+            both_ways<7, false>(o, panel, head[g][j], desc(), 0, both);
+        }
+        const bool live = there && (flags & kHeadValid) != 0;
+        if (pn.last || __ballot(live) != ~0ull) {  // the matrix's rows, the valid individuals
+            int32_t rows = (int32_t)min(d.rows - panel * kPanelRows, (int64_t)kPanelRows);
+            asm volatile("" : "+s"(rows));
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int32_t c = rows - (128 * j + 32 * x);
+                const uint32_t v = !live ? 0u : c >= 32 ? ~0u : c <= 0 ? 0u : ((1u << c) - 1u);
+                o.p.w[x] &= v;
+                o.n.w[x] &= v;
+            }
+        }
+        if (COUNT && j == 0 && live) steps += 7;
+        const uint64_t any = __ballot(o.any());
+        const bool wait = (flags & kHeadLonger) != 0 && group_bits(any, lane) != 0;
+        const uint64_t waiting = __ballot(wait), leads = waiting & 0x0101010101010101ull;
+        if (waiting) {
+            if (wait) {
+                // (the leading lanes of the groups before this one)
+                const int32_t to = queued - (j > 0 ? 1 : 0) +
+                                   (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(leads >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)leads, 0));
+                q->p[to][j] = o.p;
+                q->n[to][j] = o.n;
+                if (j == 0) {
+                    uint32_t w8[8], k = 0;  // (six bits in each of words 1 .. 6)
+                    read_head(head, w8);
+#pragma unroll
+                    for (int u = 1; u < 7; ++u) k |= (w8[u] & 63u) << (6 * (u - 1));
+                    q->who[to] = make_int4((int32_t)k, (int32_t)w8[7], ind, 0);
+                }
+            }
+            queued += (int32_t)__popcll(leads);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        put_masks(o, panel, ind, there && !wait);
+        if ((any & ~waiting) == 0) return 0u;
+        const uint32_t c = counts(o);
+        return wait ? 0u : c;
     }
 
     // Individuals [first, first + n) of the request (at most 64), eight per
     // step, on one panel.
     __device__ __forceinline__ void item(const IndHead *__restrict__ heads, int32_t first, int32_t n, int64_t panel, Shared *q)
     {
-        const uint32_t *tl = ties(panel);
-        const uint32_t nt = __builtin_amdgcn_readfirstlane(tl[0]), nan = __builtin_amdgcn_readfirstlane(tl[1]);
-        const bool dirty = nt > (uint32_t)kTieMax || nan != 0;
-        const uint32_t n_tied = dirty ? 0u : nt, tie = n_tied ? tl[kTieList + (lane & (kTieMax - 1))] : 0u;
+        const Panel pn = panel_of(panel);
         // headers of 8 words; the descending orientations' offsets past them
         const uint32_t *hw = reinterpret_cast<const uint32_t *>(heads + d.head_base) + 8 * (int64_t)first;
         const uint32_t *hd = hw + 8 * (int64_t)d.n;
         auto at = [&](int32_t i) { return (uint32_t)(8 * min(i + g, n - 1) + j); };
-        const bool last = (panel + 1) * kPanelRows > d.rows;
         uint32_t h = __builtin_nontemporal_load(hw + at(0));
         uint32_t acc = 0;
         int32_t queued = 0;
@@ -581,86 +699,23 @@ struct PairWave {
                 // to all of its lanes
                 q->head[g][j] = h;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                const uint32_t flags = q->head[g][0];
-                Rows o;
-                bool exact = dirty, both = dirty;
-                if (!dirty) {
-                    const auto rs = rsrc(panel);
-                    uint32_t head[8];
-                    read_head(q, head);
-                    Bits w[7];
+                const uint32_t c = step(
+                    q->head, &q->queue, queued, pn, first + i + g, i + g < n,
+                    [&](const uint32_t (&w8)[8], Bits (&w)[7]) {
+                        const auto rs = rsrc(panel);
 #pragma unroll
-                    for (int u = 0; u < 7; ++u) w[u] = load(rs, line(head[u]));
-                    h = __builtin_nontemporal_load(hw + at(i + kStep));
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        uint32_t a = ~0u, b = 0;
-#pragma unroll
-                        for (int u = 0; u < 7; ++u) {
-                            const uint32_t m = (uint32_t)((int32_t)head[u] >> 31);
-                            a &= w[u].w[x] ^ m;
-                            if (NEG) b |= w[u].w[x] ^ m;
-                        }
-                        o.p.w[x] = a;
-                        o.n.w[x] = NEG ? ~b : 0u;
-                        asm volatile("" : "+v"(o.p.w[x]), "+v"(o.n.w[x]));
-                    }
-                    if (n_tied) exact = listed(j < 7 ? q->head[g][j] : kNoPair, tie, n_tied, both);
-                } else {
-                    h = __builtin_nontemporal_load(hw + at(i + kStep));
-                }
-                if (exact) {
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) o.p.w[x] = ~0u, o.n.w[x] = NEG ? ~0u : 0u;
-                    both_ways<7, false>(o, panel, q->head[g][j], __builtin_nontemporal_load(hd + at(i)), 0, both);
-                }
-                const bool there = i + g < n;
-                const bool live = there && (flags & kHeadValid) != 0;
-                if (last || __ballot(live) != ~0ull) {  // the matrix's rows, the valid individuals
-                    int32_t rows = (int32_t)min(d.rows - panel * kPanelRows, (int64_t)kPanelRows);
-                    asm volatile("" : "+s"(rows));
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        const int32_t c = rows - (128 * j + 32 * x);
-                        const uint32_t v = !live ? 0u : c >= 32 ? ~0u : c <= 0 ? 0u : ((1u << c) - 1u);
-                        o.p.w[x] &= v;
-                        o.n.w[x] &= v;
-                    }
-                }
-                if (COUNT && j == 0 && live) steps += 7;
-                const uint64_t any = __ballot(o.any());
-                const bool wait = (flags & kHeadLonger) != 0 && group_bits(any, lane) != 0;
-                const uint64_t waiting = __ballot(wait), leads = waiting & 0x0101010101010101ull;
-                if (waiting) {
-                    if (wait) {
-                        // (the leading lanes of the groups before this one)
-                        const int32_t to = queued - (j > 0 ? 1 : 0) +
-                                           (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(leads >> 32),
-                                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)leads, 0));
-                        q->p[to][j] = o.p;
-                        q->n[to][j] = o.n;
-                        if (j == 0) {
-                            uint32_t head[8], k = 0;  // (six bits in each of words 1 .. 6)
-                            read_head(q, head);
-#pragma unroll
-                            for (int u = 1; u < 7; ++u) k |= (head[u] & 63u) << (6 * (u - 1));
-                            q->who[to] = make_int4((int32_t)k, (int32_t)head[7], first + i + g, 0);
-                        }
-                    }
-                    queued += (int32_t)__popcll(leads);
-                }
-                put_masks(o, panel, first + i + g, there && !wait);
-                if (any & ~waiting) {
-                    const uint32_t c = counts(o);
-                    if (j == i / kStep && !wait) acc = c;
-                }
+                        for (int u = 0; u < 7; ++u) w[u] = load(rs, line(w8[u]));
+                        h = __builtin_nontemporal_load(hw + at(i + kStep));
+                    },
+                    [&] { return __builtin_nontemporal_load(hd + at(i)); });
+                if (pn.dirty) h = __builtin_nontemporal_load(hw + at(i + kStep));
+                if (j == i / kStep) acc = c;
             }
             // eight that wait, or the last ones
             if (queued >= kStep || (i + kStep >= n && queued > 0)) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 const int32_t now = min(queued, kStep);
                 queued -= now;
-                finish_queued(q, queued, now, panel, dirty, n_tied, tie);
+                finish_queued(&q->queue, queued, now, pn, [&](int32_t ind, uint32_t c) { add(ind, c); });
             }
         }
         if (kStep * j + g < n) add(first + kStep * j + g, acc);
@@ -690,6 +745,92 @@ k_eval_pairs(ReqDesc d, const IndHead *__restrict__ heads, int32_t P, int32_t pe
     using Wave = PairWave<NEG, COUNT>;
     Wave w(d, lane);
     w.item(heads, first, n, panel, reinterpret_cast<typename Wave::Shared *>(lds) + wave);
+    if (COUNT && w.steps) atomicAdd(step_counter, (unsigned long long)w.steps);
+}
+
+// The launch for matrices of few panels: the whole evaluation in one kernel.
+// A block takes eight individuals on every panel: its first two waves make
+// the headers (as the prep kernel does, into LDS), each wave works on the
+// panels wave, wave + W, ..., and the counts are summed in LDS and written
+// once, so that neither headers nor zeroed outputs come from a kernel
+// before. Bound by the launch and by a wave's chain of loads, so the next
+// panel's window is loaded while one is worked on (128 VGPRs at four waves
+// per SIMD are there for it); individuals that wait are finished on each
+// panel, and the launcher's rule holds the panels per wave to two. The
+// whole call, one after the other: 11.0 us with two kernels and 8.9 so
+// (5,000 x 100, 800 individuals).
+template <bool NEG, bool COUNT>
+__global__ void __launch_bounds__(1024) k_eval_few(ReqDesc d, int32_t n_panels, unsigned long long *step_counter)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ __align__(16) uint32_t head[kStep][8], desc[kStep][8];
+    __shared__ int32_t matched[kStep], negative[kStep];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int W = blockDim.x / kWave;
+    const int32_t i0 = (int32_t)blockIdx.x * kStep;
+    for (int32_t t = wave; t < 2; t += W) {
+        const int32_t own = 4 * t + (lane >> 4), j = lane & 15;
+        const PairPrep p = prep_pairs_quad(d, i0 + own, i0 + own < d.n, lane);
+        if (j < 8) {
+            head[own][j] = p.word;
+            desc[own][j] = p.desc;
+        }
+        if (j == 0) matched[own] = negative[own] = 0;
+    }
+    __syncthreads();
+    using Wave = PairWave<NEG, COUNT>;
+    Wave w(d, lane);
+    using Queue = typename Wave::template Queue<kStep>;
+    Queue *q = reinterpret_cast<Queue *>(lds) + wave;
+    const bool there = i0 + w.g < d.n;
+    uint32_t m = 0, e = 0;
+    // (the next panel's loads in flight while one is worked on)
+    Bits next[7];
+    uint32_t word = 0;
+    auto fetch = [&](int32_t r) {
+        uint32_t w8[8];
+        w.read_head(head, w8);
+        word = w.panel_word(r);
+        const auto rs = w.rsrc(r);
+#pragma unroll
+        for (int u = 0; u < 7; ++u) next[u] = w.load(rs, w.line(w8[u]));
+    };
+    if (wave < n_panels) fetch(wave);
+#pragma unroll 1
+    for (int32_t r = wave; r < n_panels; r += W) {
+        Bits now[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) now[u] = next[u];
+        const auto pn = w.panel_from(r, word);
+        if (r + W < n_panels) fetch(r + W);
+        int32_t queued = 0;
+        const uint32_t c = w.step(
+            head, q, queued, pn, i0 + w.g, there,
+            [&](const uint32_t (&)[8], Bits (&x)[7]) {
+#pragma unroll
+                for (int u = 0; u < 7; ++u) x[u] = now[u];
+            },
+            [&] { return desc[w.g][w.j]; });
+        m += c & 0xffffu;
+        e += c >> 16;
+        if (queued > 0)
+            w.finish_queued(q, 0, queued, pn, [&](int32_t ind, uint32_t x) {
+                atomicAdd(&matched[ind - i0], (int32_t)(x & 0xffffu));
+                if (NEG) atomicAdd(&negative[ind - i0], (int32_t)(x >> 16));
+            });
+    }
+    if (w.j == 0) {
+        if (m) atomicAdd(&matched[w.g], (int32_t)m);
+        if (NEG && e) atomicAdd(&negative[w.g], (int32_t)e);
+    }
+    __syncthreads();
+    const int32_t i = (int32_t)threadIdx.x;
+    if (i < kStep && i0 + i < d.n) {
+        const bool ok = (head[i][0] & kHeadValid) != 0;
+        d.matched[i0 + i] = ok ? matched[i] : kInvalid;
+        if (d.negative) d.negative[i0 + i] = ok ? negative[i] : kInvalid;
+    }
     if (COUNT && w.steps) atomicAdd(step_counter, (unsigned long long)w.steps);
 }
 
@@ -848,6 +989,21 @@ hipError_t launch_pairs_batch(const PairQueues *pq, const ReqDesc *descs, const 
         hipLaunchKernelGGL(k_eval_pairs_batch<false>, dim3(grid), dim3(W * kWave), W * kWaveLds, s, pq, descs, segs, seg_req,
                            seg_gstart, heads, next, step_counter);
     return hipGetLastError();
+}
+
+hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, unsigned long long *step_counter, hipStream_t s)
+{
+    const int64_t panels = pair_panels(d.rows);
+    if (W < 1 || W > 16 || panels > kFewPanels) return hipErrorInvalidValue;
+    const bool neg = (d.flags & kFlagNeg) != 0;
+    const dim3 grid((unsigned)((d.n + kStep - 1) / kStep));
+    clear_last_error();
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(W * kWave), W * kWaveLdsFew, s, d, (int32_t)panels, step_counter);
+        return hipGetLastError();
+    };
+    if (step_counter) return neg ? go(k_eval_few<true, true>) : go(k_eval_few<false, true>);
+    return neg ? go(k_eval_few<true, false>) : go(k_eval_few<false, false>);
 }
 
 hipError_t launch_pairs(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,

@@ -380,6 +380,29 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
                 const int64_t slots = (int64_t)ctx->cu_count * 28;
                 const int64_t steps = ((int64_t)n + 7) / 8 * pair_panels(m.dev.rows);
                 cfg.P = 8 * cfg.W * (steps >= 16 * slots ? 4 : steps >= 4 * slots ? 2 : 1);
+                // The default shape on few panels: one kernel for the whole
+                // call, blocks of eight individuals and a wave per panel (up
+                // to 16), while all its blocks are resident at once (four
+                // waves per SIMD) and a wave has two panels at most, with
+                // 16 waves or, on up to 16 panels, with eight. In one call
+                // after the other, the two kernels and this one take
+                // 11.0 and 8.9 us at 5,000 x 100 and 800 individuals, 11.3
+                // and 9.0 at 20,000 x 200, 11.9 and 11.4 at 30,000 x 150
+                // and 1,600; 10.9 and 9.5 with blocks of eight at 12,483 x
+                // 150 and 2,400 (10.9 with 13 waves). Beyond: 11.4 and 12.8
+                // at 50,000 x 178 and 800, 12.0 and 12.2 at 20,000 x 200 and
+                // 2,400; with missing values there 11.8 and 11.3 at 800.
+                if (cfg.W == kPairDefaultW) {
+                    const int64_t panels = pair_panels(m.dev.rows), blocks = ((int64_t)n + 7) / 8;
+                    const int64_t all = std::min<int64_t>(16, panels), half = std::min<int64_t>(8, panels);
+                    auto resident = [&](int64_t W) { return blocks <= ctx->cu_count * (16 / W); };
+                    const int64_t W = panels <= 32 && resident(all) ? all : panels <= 16 && resident(half) ? half : 0;
+                    if (W > 0) {
+                        cfg.few = true;
+                        cfg.W = (int32_t)W;
+                        cfg.P = 8;
+                    }
+                }
             }
             cfg.P = std::max(1, std::min({cfg.P, 64 * cfg.W, std::max(1, n)}));
             cfg.blocks = (int32_t)(pair_words(m.dev.rows) / 64);  // (reported: the chunks)
@@ -635,8 +658,12 @@ hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &cfg
         mode = ctx->prof_mode;
         if (mode & 2) counter = ctx->d_step_counter;
     }
-    std::lock_guard<std::mutex> lkl(ctx->launch_mu);
-    IndHead *heads = static_cast<IndHead *>(stream_scratch(ctx, s, (size_t)d.n * sizeof(IndHead)));
+    std::unique_lock<std::mutex> lkl(ctx->launch_mu, std::defer_lock);
+    IndHead *heads = nullptr;
+    if (!cfg.few) {
+        lkl.lock();
+        heads = static_cast<IndHead *>(stream_scratch(ctx, s, (size_t)d.n * sizeof(IndHead)));
+    }
     fault_point_launch(ctx, "evaluation launch");
     if (log_level() >= 3)
         log_msg(3, "eval n=" + std::to_string(d.n) + " rows=" + std::to_string(d.rows) + " cols=" +

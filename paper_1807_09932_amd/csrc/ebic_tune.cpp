@@ -57,7 +57,7 @@ LaunchCfg default_cfg(int64_t rows, int32_t cols, int32_t n)
     if (cols <= kDefaultPairCols) {
         LaunchCfg c;
         c.L = 1;
-        c.W = 2;
+        c.W = kPairDefaultW;
         c.P = 0;
         c.staging = STAGE_PAIRS;
         c.blocks = 0;
@@ -199,7 +199,8 @@ static void read_cache(std::map<TuneKey, LaunchCfg> &out, const std::string &pat
             const bool stg_ok = c.staging == STAGE_LDS || c.staging == STAGE_DIRECT || c.staging == STAGE_CODES ||
                                 c.staging == STAGE_BYTES || c.staging == STAGE_HALVES || c.staging == STAGE_T10 ||
                                 c.staging == STAGE_PAIRS;
-            if ((k.kind == 0 || k.kind == 1) && L_ok && c.W >= 1 && c.W <= 16 && c.P >= 1 && stg_ok) out[k] = c;
+            if ((k.kind == 0 || k.kind == 1) && L_ok && c.W >= 1 && c.W <= 16 &&
+                (c.P >= 1 || (c.P == 0 && k.kind == 0 && c.staging == STAGE_PAIRS)) && stg_ok) out[k] = c;
         }
     }
 }
@@ -391,8 +392,17 @@ ebic_status ebic_autotune(ebic_ctx *ctx, const ebic_request *sample, int32_t n_r
                 std::vector<std::pair<float, LaunchCfg>> timed;
                 // The pairwise order bitmaps (built by the first of these
                 // evaluations where they fit): waves per block and
-                // individuals per wave, one panel per block.
-                if (cols <= kDefaultPairCols)
+                // individuals per wave, one panel per block; first the default
+                // shape, which leaves the split to the planner.
+                if (cols <= kDefaultPairCols) {
+                    LaunchCfg c;
+                    c.L = 1;
+                    c.W = kPairDefaultW;
+                    c.P = 0;
+                    c.staging = STAGE_PAIRS;
+                    set_override(c);
+                    const float ms = time_ms(eval_once, 3, s);
+                    if (std::isfinite(ms)) timed.emplace_back(ms, c);
                     for (int W : {2, 4, 8})
                         for (int per_wave : {8, 16, 32, 64}) {
                             LaunchCfg c;
@@ -405,6 +415,7 @@ ebic_status ebic_autotune(ebic_ctx *ctx, const ebic_request *sample, int32_t n_r
                             const float ms = time_ms(eval_once, 3, s);
                             if (std::isfinite(ms)) timed.emplace_back(ms, c);
                         }
+                }
                 for (int L : {1, 2, 3, 4, 6, 8, 16})
                     for (int W : {4, 8, 16})
                         for (int P : {200, 400, 800, 1600})
