@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ebic_internal.h"
 
 namespace ebic {
@@ -61,118 +63,150 @@ k_layout(const float *__restrict__ src, int64_t ld_src, int32_t src_col_major, i
 
 // ---------------------------------------------------------------------------
 // Rank codes: for every cell, the number of cells of its row that are
-// smaller (IEEE <, so NaN is never smaller and -0 is not smaller than +0),
-// as an FP16 integer; a missing cell gets NaN. A block stages 64 rows of all
-// columns in LDS; thread (lane, wave) counts, for its row, the columns wave,
-// wave + 4, ... Padding rows get code 0.
+// smaller (IEEE <, so NaN is never smaller and -0 is not smaller than +0).
+// A block stages 32 rows of all columns in LDS; the half-waves (lane & 31 =
+// row) each count for an even run of the columns. Bound by the comparisons,
+// cols x cols a row: a compare and an add of its carry each, so a half-wave
+// counts for 16 columns per value read (then eight, then four), and equal
+// values are found without a comparison of their own: the counts of a row
+// of distinct values add up to cols x (cols - 1) / 2, and each pair of equal
+// values takes one off. Blocks of 32 rows rather than 64 even out the last
+// wave of blocks. 10-bit codes at 54,675 x 178: 330 us with a column at a
+// time and equality counted beside it, 128 us so (the comparisons alone take
+// 88); 436,444 x 310 6.8 and 2.4 ms.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-k_codes(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols, uint16_t *__restrict__ C)
+constexpr int kCodeRows = 32;
+
+template <int R>
+__device__ __forceinline__ void count_smaller(const float *t, int32_t cols, int32_t c0, int row, uint32_t (&n)[R])
 {
-    extern __shared__ float t[];  // [cols][64]
-    const int64_t r0 = (int64_t)blockIdx.x * 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int32_t c = wave; c < cols; c += 4) t[c * 64 + lane] = X[(int64_t)c * ld + r0 + lane];
-    __syncthreads();
-    const bool live = r0 + lane < rows;
-    for (int32_t c = wave; c < cols; c += 4) {
-        const float v = t[c * 64 + lane];
-        int32_t n = 0;
-        for (int32_t j = 0; j < cols; ++j) n += t[j * 64 + lane] < v ? 1 : 0;
-        uint16_t code = __half_as_ushort(__int2half_rn(n));  // exact: n < 2048
-        if (v != v) code = kCodeNaN;
-        C[(int64_t)c * ld + r0 + lane] = live ? code : (uint16_t)0;
+    float v[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        v[k] = t[min(c0 + k, cols - 1) * kCodeRows + row];
+        n[k] = 0;
+    }
+#pragma unroll 4
+    for (int32_t j = 0; j < cols; ++j) {
+        const float u = t[j * kCodeRows + row];
+#pragma unroll
+        for (int k = 0; k < R; ++k) n[k] += u < v[k] ? 1u : 0u;
     }
 }
 
+// put(column, count) for every column of this half-wave.
+template <class Put>
+__device__ __forceinline__ void rank_columns(const float *t, int32_t cols, Put &&put)
+{
+    const int halves = blockDim.x / kCodeRows, row = threadIdx.x & (kCodeRows - 1);
+    const int32_t per = (cols + halves - 1) / halves, first = (int32_t)(threadIdx.x / kCodeRows) * per;
+    const int32_t mine = min(per, cols - first);
+    auto run = [&](auto size, int32_t o) {
+        constexpr int R = decltype(size)::value;
+        uint32_t n[R];
+        count_smaller<R>(t, cols, first + o, row, n);
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            if (o + k < mine) put(first + o + k, n[k]);
+    };
+    int32_t o = 0;  // (the same in every half-wave)
+    for (; o + 12 < per; o += 16) run(std::integral_constant<int, 16>(), o);
+    for (; o + 4 < per; o += 8) run(std::integral_constant<int, 8>(), o);
+    for (; o < per; o += 4) run(std::integral_constant<int, 4>(), o);
+}
+
+// The codes as FP16 integers; a missing cell gets NaN. Padding rows get 0.
+__global__ void __launch_bounds__(1024)
+k_codes(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols, uint16_t *__restrict__ C)
+{
+    extern __shared__ float t[];  // [cols][kCodeRows]
+    const int row = threadIdx.x & (kCodeRows - 1);
+    const int64_t r = (int64_t)blockIdx.x * kCodeRows + row;
+    for (int32_t c = threadIdx.x / kCodeRows; c < cols; c += blockDim.x / kCodeRows)
+        t[c * kCodeRows + row] = X[(int64_t)c * ld + r];
+    __syncthreads();
+    const bool live = r < rows;
+    rank_columns(t, cols, [&](int32_t c, uint32_t n) {
+        const float v = t[c * kCodeRows + row];
+        uint16_t code = __half_as_ushort(__int2half_rn((int32_t)n));  // exact: n < 2048
+        if (v != v) code = kCodeNaN;
+        C[(int64_t)c * ld + r] = live ? code : (uint16_t)0;
+    });
+}
+
+// The fill-substituted values of row r into t, a missing cell noted; then
+// put(column, count) for every column, and *tie = 1 if the row is below
+// `rows` and holds two equal values.
+template <class Put>
+__device__ __forceinline__ void rank_filled(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols,
+                                            int64_t r, float fill, float *t, int32_t *__restrict__ has_nan,
+                                            int32_t *__restrict__ tie, Put &&put)
+{
+    __shared__ uint32_t sum[kCodeRows];
+    const int row = threadIdx.x & (kCodeRows - 1);
+    const bool live = r < rows;
+    bool missing = false;
+    if (threadIdx.x < kCodeRows) sum[row] = 0;
+    for (int32_t c = threadIdx.x / kCodeRows; c < cols; c += blockDim.x / kCodeRows) {
+        float v = live ? X[(int64_t)c * ld + r] : 0.f;
+        if (v != v) {
+            missing = true;
+            v = fill;
+        }
+        t[c * kCodeRows + row] = v;
+    }
+    if (missing) *has_nan = 1;
+    __syncthreads();
+    uint32_t total = 0;
+    rank_columns(t, cols, [&](int32_t c, uint32_t n) {
+        total += n;
+        put(c, live ? n : 0u);
+    });
+    atomicAdd(&sum[row], total);
+    __syncthreads();
+    // (cols at most 512: the sum of a row's counts stays below 2^17)
+    if (threadIdx.x < kCodeRows && live && sum[row] != (uint32_t)cols * (uint32_t)(cols - 1) / 2) *tie = 1;
+}
+
 // ---------------------------------------------------------------------------
-// Byte or 16-bit rank codes: as above, of the fill-substituted values, in
-// the interleaved order of the SWAR evaluation. Bytes: within each 256-row
+// Byte or 16-bit rank codes: of the fill-substituted values, in the
+// interleaved order of the SWAR evaluation. Bytes: within each 256-row
 // group the word of lane l holds rows l, 64 + l, 128 + l, 192 + l; 16 bits:
 // within each 128-row group it holds rows l and 64 + l. Rows past the
 // matrix get 0. Also flags any missing cell, and each 512-row group with a
 // row that holds two equal values.
 // ---------------------------------------------------------------------------
 template <typename C>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 k_swar_codes(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols, float fill,
              C *__restrict__ out, int64_t ld_out, int32_t *__restrict__ has_nan, int32_t *__restrict__ ties)
 {
-    extern __shared__ float t[];  // [cols][64]
-    const int64_t r0 = (int64_t)blockIdx.x * 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t r = r0 + lane;
-    const bool live = r < rows;
-    bool missing = false;
-    for (int32_t c = wave; c < cols; c += 4) {
-        float v = live ? X[(int64_t)c * ld + r] : 0.f;
-        if (v != v) {
-            missing = true;
-            v = fill;
-        }
-        t[c * 64 + lane] = v;
-    }
-    if (missing) *has_nan = 1;
-    __syncthreads();
+    extern __shared__ float t[];  // [cols][kCodeRows]
+    const int64_t r = (int64_t)blockIdx.x * kCodeRows + (threadIdx.x & (kCodeRows - 1));
     // Position of row r (in elements of C) inside its interleaved group.
     const int64_t pos = sizeof(C) == 1 ? (r & ~(int64_t)255) + 4 * (r & 63) + ((r >> 6) & 3)
                                        : (r & ~(int64_t)127) + 2 * (r & 63) + ((r >> 6) & 1);
-    bool tie = false;
-    for (int32_t c = wave; c < cols; c += 4) {
-        const float v = t[c * 64 + lane];
-        int32_t n = 0, e = 0;
-        for (int32_t j = 0; j < cols; ++j) {
-            const float u = t[j * 64 + lane];
-            n += u < v ? 1 : 0;
-            e += u == v ? 1 : 0;
-        }
-        tie |= e > 1;  // another cell of the row has the same value (and code)
-        out[(int64_t)c * ld_out + pos] = live ? (C)n : (C)0;
-    }
-    if (live && tie) ties[r >> 9] = 1;
+    rank_filled(X, rows, ld, cols, r, fill, t, has_nan, ties + (r >> 9),
+                [&](int32_t c, uint32_t n) { out[(int64_t)c * ld_out + pos] = (C)n; });
 }
 
-// 10-bit rank codes: the same counts, three rows per 32-bit word. Block b
-// holds rows [64 b, 64 b + 64), which are field b mod 3 of 192-row group
-// b / 3: each code is OR-ed into its word (the three blocks of a group
-// write disjoint fields of the same words). Flags a missing cell, and each
-// 192-row group with a row that holds two equal values.
-__global__ void __launch_bounds__(256)
+// 10-bit rank codes: the same counts, three rows per 32-bit word. Rows
+// [64 b, 64 b + 64) are field b mod 3 of 192-row group b / 3: each code is
+// OR-ed into its word (the blocks of a group write disjoint fields of the
+// same words). Flags a missing cell, and each 192-row group with a row that
+// holds two equal values.
+__global__ void __launch_bounds__(1024)
 k_t10_codes(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols, float fill,
             uint32_t *__restrict__ out, int64_t ld_words, int32_t *__restrict__ has_nan,
             int32_t *__restrict__ ties)
 {
-    extern __shared__ float t[];  // [cols][64]
-    const int64_t r0 = (int64_t)blockIdx.x * 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t r = r0 + lane;
-    const bool live = r < rows;
-    bool missing = false;
-    for (int32_t c = wave; c < cols; c += 4) {
-        float v = live ? X[(int64_t)c * ld + r] : 0.f;
-        if (v != v) {
-            missing = true;
-            v = fill;
-        }
-        t[c * 64 + lane] = v;
-    }
-    if (missing) *has_nan = 1;
-    __syncthreads();
-    const int64_t group = blockIdx.x / 3;
-    const int field = blockIdx.x % 3;
-    bool tie = false;
-    for (int32_t c = wave; c < cols; c += 4) {
-        const float v = t[c * 64 + lane];
-        uint32_t n = 0, e = 0;
-        for (int32_t j = 0; j < cols; ++j) {
-            const float u = t[j * 64 + lane];
-            n += u < v ? 1u : 0u;
-            e += u == v ? 1u : 0u;
-        }
-        tie |= e > 1;
-        if (live && n) atomicOr(out + (int64_t)c * ld_words + group * 64 + lane, n << (10 * field));
-    }
-    if (live && tie) ties[group] = 1;
+    extern __shared__ float t[];  // [cols][kCodeRows]
+    const int64_t r = (int64_t)blockIdx.x * kCodeRows + (threadIdx.x & (kCodeRows - 1));
+    const int32_t b = (int32_t)(blockIdx.x / (64 / kCodeRows)), group = b / 3, shift = 10 * (b % 3);
+    uint32_t *words = out + (int64_t)group * 64 + (r & 63);
+    rank_filled(X, rows, ld, cols, r, fill, t, has_nan, ties + group, [&](int32_t c, uint32_t n) {
+        if (n) atomicOr(words + (int64_t)c * ld_words, n << shift);
+    });
 }
 
 __global__ void k_zero_pad(float *__restrict__ dst, int64_t rows, int64_t ld, int32_t cols)
@@ -186,16 +220,25 @@ __global__ void k_zero_pad(float *__restrict__ dst, int64_t rows, int64_t ld, in
 
 }  // namespace
 
+// Threads of a code block: with its LDS (128 bytes per column) they leave
+// room for 28 waves per CU or more, and a half-wave counts for 16 columns or
+// so: 20,000 x 500 takes 569, 393 and 374 us with four, eight and 16 waves,
+// 54,675 x 178 takes 134, 128 and 164, 436,444 x 64 (bytes) 133, 137 and 267.
+static unsigned code_threads(int32_t cols)
+{
+    return 64u * (cols <= 128 ? 4 : cols <= 320 ? 8 : 16);
+}
+
 hipError_t launch_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, uint16_t *C,
                         hipStream_t s)
 {
     if (cols > kMaxCodeCols) return hipErrorInvalidValue;
-    const size_t lds = (size_t)cols * 64 * sizeof(float);
+    const size_t lds = (size_t)cols * kCodeRows * sizeof(float);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_codes),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     clear_last_error();
-    hipLaunchKernelGGL(k_codes, dim3((unsigned)(ld / 64)), dim3(256), lds, s, X, rows, ld, cols, C);
+    hipLaunchKernelGGL(k_codes, dim3((unsigned)(ld / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows, ld, cols, C);
     return hipGetLastError();
 }
 
@@ -203,12 +246,12 @@ hipError_t launch_byte_codes(const float *X, int64_t rows, int64_t ld, int32_t c
                              uint8_t *B, int64_t ldb, int32_t *has_nan, int32_t *ties, hipStream_t s)
 {
     if (cols > kMaxByteCols || ldb % 512 != 0 || ldb < rows) return hipErrorInvalidValue;
-    const size_t lds = (size_t)cols * 64 * sizeof(float);
+    const size_t lds = (size_t)cols * kCodeRows * sizeof(float);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_swar_codes<uint8_t>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     clear_last_error();
-    hipLaunchKernelGGL(k_swar_codes<uint8_t>, dim3((unsigned)(ldb / 64)), dim3(256), lds, s, X, rows, ld,
+    hipLaunchKernelGGL(k_swar_codes<uint8_t>, dim3((unsigned)(ldb / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows, ld,
                        cols, fill, B, ldb, has_nan, ties);
     return hipGetLastError();
 }
@@ -217,12 +260,12 @@ hipError_t launch_half_codes(const float *X, int64_t rows, int64_t ld, int32_t c
                              uint8_t *Hc, int64_t ldh, int32_t *has_nan, int32_t *ties, hipStream_t s)
 {
     if (cols > kMaxCodeCols || ldh % 512 != 0 || ldh / 2 < rows) return hipErrorInvalidValue;
-    const size_t lds = (size_t)cols * 64 * sizeof(float);
+    const size_t lds = (size_t)cols * kCodeRows * sizeof(float);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_swar_codes<uint16_t>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     clear_last_error();
-    hipLaunchKernelGGL(k_swar_codes<uint16_t>, dim3((unsigned)(ldh / 2 / 64)), dim3(256), lds, s, X, rows,
+    hipLaunchKernelGGL(k_swar_codes<uint16_t>, dim3((unsigned)(ldh / 2 / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows,
                        ld, cols, fill, reinterpret_cast<uint16_t *>(Hc), ldh / 2, has_nan, ties);
     return hipGetLastError();
 }
@@ -233,14 +276,14 @@ hipError_t launch_t10_codes(const float *X, int64_t rows, int64_t ld, int32_t co
     const int64_t groups = (rows + kT10Rows - 1) / kT10Rows;
     if (cols > kMaxT10Cols || ld10 < groups * 256 || ld10 % 256 != 0 || ld / 64 < (rows + 63) / 64)
         return hipErrorInvalidValue;
-    const size_t lds = (size_t)cols * 64 * sizeof(float);
+    const size_t lds = (size_t)cols * kCodeRows * sizeof(float);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_t10_codes),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    // one block per 64 rows up to the last group's end; X is read only for
+    // one block per 32 rows up to the last group's end; X is read only for
     // rows below `rows`
     clear_last_error();
-    hipLaunchKernelGGL(k_t10_codes, dim3((unsigned)(groups * 3)), dim3(256), lds, s, X, rows, ld, cols, fill,
+    hipLaunchKernelGGL(k_t10_codes, dim3((unsigned)(groups * kT10Rows / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows, ld, cols, fill,
                        reinterpret_cast<uint32_t *>(T10), ld10 / 4, has_nan, ties);
     return hipGetLastError();
 }
