@@ -234,22 +234,27 @@ hipError_t launch_layout(const float *src, int64_t ld_src, bool src_col_major, i
 hipError_t launch_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, uint16_t *C,
                         hipStream_t s);
 
-// Byte rank codes of rows [0, rows) of a column-major matrix (cols <=
-// kMaxByteCols), with missing cells replaced by `fill`, into B (ldb bytes
+// Rows in whole groups of every kind of code (64, 192 and 512 rows).
+constexpr int64_t kUploadUnit = 1536;
+
+// Byte rank codes of rows [r0, r1) of a column-major matrix (cols <=
+// kMaxByteCols; r0 a multiple of kUploadUnit, r1 too or ldb), with missing cells replaced by `fill`, into B (ldb bytes
 // per column, ldb a multiple of 512, the interleaved order above; padding
 // rows get 0). *has_nan (device int, zeroed by the caller) is set to 1 if
 // any cell is missing; ties[g] (ldb / 512 device ints, zeroed by the
 // caller) is set to 1 if some row of rows [512 g, 512 g + 512) holds two
 // equal values.
 hipError_t launch_byte_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
-                             uint8_t *B, int64_t ldb, int32_t *has_nan, int32_t *ties, hipStream_t s);
+                             uint8_t *B, int64_t ldb, int32_t *has_nan, int32_t *ties, int64_t r0, int64_t r1,
+                             hipStream_t s);
 
-// The same for 16-bit codes (cols <= kMaxCodeCols) into Hc, ldh bytes per
+// The same for 16-bit codes of all rows (cols <= kMaxCodeCols) into Hc, ldh bytes per
 // column (a multiple of 512), in their interleaved order.
 hipError_t launch_half_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
                              uint8_t *Hc, int64_t ldh, int32_t *has_nan, int32_t *ties, hipStream_t s);
 
-// The same for 10-bit codes (cols <= kMaxT10Cols) into T10, ld10 bytes per
+// The same for 10-bit codes (cols <= kMaxT10Cols; r1 up to the last group's
+// end) into T10, ld10 bytes per
 // column (256 per 192-row group; T10 zeroed by the caller, the fields are
 // OR-ed in), and one tie flag per 192-row group.
 // Clears the calling thread's last HIP error before a launch, so that the
@@ -310,7 +315,8 @@ hipError_t launch_pairs_batch(const PairQueues *pq, const ReqDesc *descs, const 
                               uint32_t *next, int32_t W, int32_t grid, unsigned long long *step_counter, hipStream_t s);
 int pairs_batch_occupancy(int32_t W);  // blocks per CU of the batched pairs kernel
 hipError_t launch_t10_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
-                            uint8_t *T10, int64_t ld10, int32_t *has_nan, int32_t *ties, hipStream_t s);
+                            uint8_t *T10, int64_t ld10, int32_t *has_nan, int32_t *ties, int64_t r0, int64_t r1,
+                            hipStream_t s);
 
 // Zero rows [rows, ld) of every column of a column-major matrix.
 hipError_t launch_zero_pad(float *dst, int64_t rows, int64_t ld, int32_t cols, hipStream_t s);

@@ -179,10 +179,10 @@ __device__ __forceinline__ void rank_filled(const float *__restrict__ X, int64_t
 template <typename C>
 __global__ void __launch_bounds__(1024)
 k_swar_codes(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols, float fill,
-             C *__restrict__ out, int64_t ld_out, int32_t *__restrict__ has_nan, int32_t *__restrict__ ties)
+             C *__restrict__ out, int64_t ld_out, int32_t *__restrict__ has_nan, int32_t *__restrict__ ties, int64_t r0)
 {
     extern __shared__ float t[];  // [cols][kCodeRows]
-    const int64_t r = (int64_t)blockIdx.x * kCodeRows + (threadIdx.x & (kCodeRows - 1));
+    const int64_t r = r0 + (int64_t)blockIdx.x * kCodeRows + (threadIdx.x & (kCodeRows - 1));
     // Position of row r (in elements of C) inside its interleaved group.
     const int64_t pos = sizeof(C) == 1 ? (r & ~(int64_t)255) + 4 * (r & 63) + ((r >> 6) & 3)
                                        : (r & ~(int64_t)127) + 2 * (r & 63) + ((r >> 6) & 1);
@@ -198,11 +198,11 @@ k_swar_codes(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols
 __global__ void __launch_bounds__(1024)
 k_t10_codes(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols, float fill,
             uint32_t *__restrict__ out, int64_t ld_words, int32_t *__restrict__ has_nan,
-            int32_t *__restrict__ ties)
+            int32_t *__restrict__ ties, int64_t r0)
 {
     extern __shared__ float t[];  // [cols][kCodeRows]
-    const int64_t r = (int64_t)blockIdx.x * kCodeRows + (threadIdx.x & (kCodeRows - 1));
-    const int32_t b = (int32_t)(blockIdx.x / (64 / kCodeRows)), group = b / 3, shift = 10 * (b % 3);
+    const int64_t first = r0 + (int64_t)blockIdx.x * kCodeRows, r = first + (threadIdx.x & (kCodeRows - 1));
+    const int32_t b = (int32_t)(first / 64), group = b / 3, shift = 10 * (b % 3);
     uint32_t *words = out + (int64_t)group * 64 + (r & 63);
     rank_filled(X, rows, ld, cols, r, fill, t, has_nan, ties + group, [&](int32_t c, uint32_t n) {
         if (n) atomicOr(words + (int64_t)c * ld_words, n << shift);
@@ -243,16 +243,19 @@ hipError_t launch_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, 
 }
 
 hipError_t launch_byte_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
-                             uint8_t *B, int64_t ldb, int32_t *has_nan, int32_t *ties, hipStream_t s)
+                             uint8_t *B, int64_t ldb, int32_t *has_nan, int32_t *ties, int64_t r0, int64_t r1,
+                             hipStream_t s)
 {
-    if (cols > kMaxByteCols || ldb % 512 != 0 || ldb < rows) return hipErrorInvalidValue;
+    if (cols > kMaxByteCols || ldb % 512 != 0 || ldb < rows || r0 % kUploadUnit != 0 || r0 >= r1 || r1 % kCodeRows != 0 ||
+        r1 > ldb)
+        return hipErrorInvalidValue;
     const size_t lds = (size_t)cols * kCodeRows * sizeof(float);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_swar_codes<uint8_t>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     clear_last_error();
-    hipLaunchKernelGGL(k_swar_codes<uint8_t>, dim3((unsigned)(ldb / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows, ld,
-                       cols, fill, B, ldb, has_nan, ties);
+    hipLaunchKernelGGL(k_swar_codes<uint8_t>, dim3((unsigned)((r1 - r0) / kCodeRows)), dim3(code_threads(cols)), lds, s, X,
+                       rows, ld, cols, fill, B, ldb, has_nan, ties, r0);
     return hipGetLastError();
 }
 
@@ -266,25 +269,26 @@ hipError_t launch_half_codes(const float *X, int64_t rows, int64_t ld, int32_t c
     if (e != hipSuccess) return e;
     clear_last_error();
     hipLaunchKernelGGL(k_swar_codes<uint16_t>, dim3((unsigned)(ldh / 2 / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows,
-                       ld, cols, fill, reinterpret_cast<uint16_t *>(Hc), ldh / 2, has_nan, ties);
+                       ld, cols, fill, reinterpret_cast<uint16_t *>(Hc), ldh / 2, has_nan, ties, (int64_t)0);
     return hipGetLastError();
 }
 
 hipError_t launch_t10_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
-                            uint8_t *T10, int64_t ld10, int32_t *has_nan, int32_t *ties, hipStream_t s)
+                            uint8_t *T10, int64_t ld10, int32_t *has_nan, int32_t *ties, int64_t r0, int64_t r1,
+                            hipStream_t s)
 {
     const int64_t groups = (rows + kT10Rows - 1) / kT10Rows;
-    if (cols > kMaxT10Cols || ld10 < groups * 256 || ld10 % 256 != 0 || ld / 64 < (rows + 63) / 64)
+    if (cols > kMaxT10Cols || ld10 < groups * 256 || ld10 % 256 != 0 || ld / 64 < (rows + 63) / 64 ||
+        r0 % kUploadUnit != 0 || r0 >= r1 || r1 % 64 != 0 || r1 > groups * kT10Rows)
         return hipErrorInvalidValue;
     const size_t lds = (size_t)cols * kCodeRows * sizeof(float);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_t10_codes),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    // one block per 32 rows up to the last group's end; X is read only for
-    // rows below `rows`
+    // (X is read only for rows below `rows`)
     clear_last_error();
-    hipLaunchKernelGGL(k_t10_codes, dim3((unsigned)(groups * kT10Rows / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows, ld, cols, fill,
-                       reinterpret_cast<uint32_t *>(T10), ld10 / 4, has_nan, ties);
+    hipLaunchKernelGGL(k_t10_codes, dim3((unsigned)((r1 - r0) / kCodeRows)), dim3(code_threads(cols)), lds, s, X, rows, ld,
+                       cols, fill, reinterpret_cast<uint32_t *>(T10), ld10 / 4, has_nan, ties, r0);
     return hipGetLastError();
 }
 

@@ -4,16 +4,20 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
 #include <new>
+#include <optional>
 #include <stdexcept>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -168,6 +172,14 @@ Matrix &ctx_matrix_mut(ebic_ctx *ctx, int32_t id)
     return it->second;
 }
 
+hipStream_t aux_stream(ebic_ctx *ctx)
+{
+    // Kept with the context: creating and destroying one took 130 us of
+    // every layout built on first use.
+    if (!ctx->aux) hip_check(hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking), "hipStreamCreate");
+    return ctx->aux;
+}
+
 bool codes_buildable(const Matrix &m, bool include)
 {
     return m.dev.cols <= kMaxCodeCols && (!include || m.Xfill != nullptr);
@@ -182,16 +194,11 @@ void build_fp16_codes(ebic_ctx *ctx, Matrix &m, bool include)
     uint16_t *C = static_cast<uint16_t *>(ctx_alloc(ctx, cbytes));
     hipStream_t s = nullptr;
     try {
-        hip_check(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "hipStreamCreate");
+        s = aux_stream(ctx);
         hip_check(launch_codes(include ? m.Xfill : m.X, m.dev.rows, m.dev.ld, m.dev.cols, C, s), "codes kernel");
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-        hip_check(hipStreamDestroy(s), "hipStreamDestroy");
-        s = nullptr;
     } catch (...) {
-        if (s) {
-            (void)hipStreamSynchronize(s);
-            (void)hipStreamDestroy(s);
-        }
+        if (s) (void)hipStreamSynchronize(s);
         ctx_free(ctx, C);
         throw;
     }
@@ -225,19 +232,14 @@ void build_half_codes(ebic_ctx *ctx, Matrix &m)
     int32_t has_nan = 1;
     hipStream_t s = nullptr;
     try {
-        hip_check(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "hipStreamCreate");
+        s = aux_stream(ctx);
         hip_check(hipMemsetAsync(flag, 0, 256 + tbytes, s), "hipMemsetAsync");
         hip_check(launch_half_codes(m.X, rows, m.dev.ld, cols, m.dev.fill, Hc, ldh, flag, ties, s),
                   "16-bit codes kernel");
         hip_check(hipMemcpyAsync(&has_nan, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-        hip_check(hipStreamDestroy(s), "hipStreamDestroy");
-        s = nullptr;
     } catch (...) {
-        if (s) {
-            (void)hipStreamSynchronize(s);
-            (void)hipStreamDestroy(s);
-        }
+        if (s) (void)hipStreamSynchronize(s);
         ctx_free(ctx, Hc);
         throw;
     }
@@ -293,20 +295,15 @@ void build_pairs(ebic_ctx *ctx, Matrix &m, bool include)
     uint32_t *G = static_cast<uint32_t *>(ctx_alloc(ctx, gbytes));
     hipStream_t s = nullptr;
     try {
-        hip_check(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "hipStreamCreate");
+        s = aux_stream(ctx);
         uint32_t *F = const_cast<uint32_t *>(pairs_marks(m, G));
         hip_check(hipMemsetAsync(F, 0, (size_t)pairs_mark_bytes(m), s), "hipMemsetAsync");
         hip_check(launch_pair_bits(m.X, m.dev.rows, m.dev.ld, m.dev.cols, m.has_missing != 0, subst, m.dev.fill, G, w32,
                                    F, s),
                   "pair bitmaps kernel");
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-        hip_check(hipStreamDestroy(s), "hipStreamDestroy");
-        s = nullptr;
     } catch (...) {
-        if (s) {
-            (void)hipStreamSynchronize(s);
-            (void)hipStreamDestroy(s);
-        }
+        if (s) (void)hipStreamSynchronize(s);
         ctx_free(ctx, G);
         throw;
     }
@@ -574,54 +571,138 @@ void upload_pinned(ebic_ctx *ctx, size_t bytes)
 {
     // (called under ctx->mu)
     if (ctx->up_pin_bytes < bytes) {
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < kUploadSlots; ++b) {
             if (ctx->up_done[b]) hip_check(hipEventSynchronize(ctx->up_done[b]), "hipEventSynchronize");
             if (ctx->up_pin[b]) (void)hipHostFree(ctx->up_pin[b]);
             ctx->up_pin[b] = nullptr;
         }
         ctx->up_pin_bytes = 0;
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < kUploadSlots; ++b)
             hip_check(hipHostMalloc(&ctx->up_pin[b], bytes, hipHostMallocDefault), "hipHostMalloc");
         ctx->up_pin_bytes = bytes;
     }
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < kUploadSlots; ++b) {
         if (!ctx->up_done[b])
             hip_check(hipEventCreateWithFlags(&ctx->up_done[b], hipEventDisableTiming), "hipEventCreate");
+        if (!ctx->up_laid[b])
+            hip_check(hipEventCreateWithFlags(&ctx->up_laid[b], hipEventDisableTiming), "hipEventCreate");
+    }
 }
 
-void pack_rows(const float *src, int64_t ld_src, bool col_major, int64_t r0, int64_t nr, int32_t cols, float *dst)
-{
-    // Row-major: rows r0 .. r0+nr of cols floats each -> dst[nr][cols].
-    // Column-major: column c's entries r0 .. r0+nr -> dst[c][nr].
-    const int64_t units = col_major ? cols : nr;
-    const size_t unit_bytes = (size_t)(col_major ? nr : cols) * sizeof(float);
-    const bool contiguous = col_major ? (ld_src == nr || cols == 1) : (ld_src == cols || nr == 1);
-    const size_t total = (size_t)units * unit_bytes;
-    unsigned nt = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
-    if (total < (4u << 20)) nt = 1;
-    auto work = [&](unsigned t) {
-        if (contiguous) {
-            const char *from = reinterpret_cast<const char *>(col_major ? src + r0 : src + r0 * ld_src);
-            const size_t lo = total * t / nt, hi = total * (t + 1) / nt;
-            std::memcpy(reinterpret_cast<char *>(dst) + lo, from + lo, hi - lo);
-            return;
+namespace {
+
+// Packs the chunks of a host matrix into pinned buffers: chunk i's rows
+// [r0, r0 + nr) -> buffer i % kUploadSlots, row-major nr x cols, column-major
+// cols x nr. The caller and a few threads take pieces of a chunk in turn; the
+// threads go on to the next chunks by themselves as far as open() has given
+// them free. (One thread copies 33 GB/s, the link takes 57.)
+class Packer {
+  public:
+    Packer(const float *src, int64_t ld_src, bool col_major, int32_t cols, const std::vector<int64_t> &begins,
+           void *const *slots)
+        : src_(src), ld_(ld_src), col_major_(col_major), cols_(cols), begins_(begins), slots_(slots),
+          state_(begins.size() - 1)
+    {
+        for (size_t i = 0; i + 1 < begins.size(); ++i) {
+            const int64_t nr = begins[i + 1] - begins[i];
+            const int64_t units = col_major ? cols : nr, unit = (col_major ? nr : cols) * (int64_t)sizeof(float);
+            state_[i].per_piece = std::max<int64_t>(1, kPiece / unit);
+            state_[i].pieces = (units + state_[i].per_piece - 1) / state_[i].per_piece;
         }
-        const int64_t lo = units * t / nt, hi = units * (t + 1) / nt;
-        for (int64_t u = lo; u < hi; ++u) {
-            const float *from = col_major ? src + u * ld_src + r0 : src + (r0 + u) * ld_src;
-            std::memcpy(reinterpret_cast<char *>(dst) + (size_t)u * unit_bytes, from, unit_bytes);
-        }
-    };
-    if (nt == 1) {
-        work(0);
-        return;
     }
-    std::vector<std::thread> th;
-    th.reserve(nt - 1);
-    for (unsigned t = 1; t < nt; ++t) th.emplace_back(work, t);
-    work(0);
-    for (auto &x : th) x.join();
-}
+    ~Packer()
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            stop_ = true;
+        }
+        opened_cv_.notify_all();
+        for (auto &t : threads_) t.join();
+    }
+    Packer(const Packer &) = delete;
+    Packer &operator=(const Packer &) = delete;
+    void start(int threads)
+    {
+        threads_.reserve((size_t)threads);
+        try {
+            for (int t = 0; t < threads; ++t) threads_.emplace_back([this] { run(); });
+        } catch (const std::system_error &) {
+            // (fewer threads; the caller packs what they do not)
+        }
+    }
+    // Chunks below `n` may be packed: their buffers are free.
+    void open(int64_t n)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (n <= open_) return;
+            open_ = n;
+        }
+        opened_cv_.notify_all();
+    }
+    // Help to pack chunk i (opened) and wait for the others' pieces.
+    void pack(int64_t i)
+    {
+        help(i);
+        std::unique_lock<std::mutex> lk(mu_);
+        done_cv_.wait(lk, [&] { return state_[i].done == state_[i].pieces; });
+    }
+
+  private:
+    static constexpr int64_t kPiece = 256 << 10;
+    struct Chunk {
+        int64_t pieces = 0, per_piece = 0;  // (units: rows, or columns of a column-major source)
+        std::atomic<int64_t> next{0};
+        int64_t done = 0;  // (under mu_)
+    };
+    void run()
+    {
+        for (int64_t i = 0; i < (int64_t)state_.size(); ++i) {
+            {
+                std::unique_lock<std::mutex> lk(mu_);
+                opened_cv_.wait(lk, [&] { return stop_ || open_ > i; });
+                if (stop_) return;
+            }
+            help(i);
+        }
+    }
+    void help(int64_t i)
+    {
+        Chunk &c = state_[i];
+        const int64_t r0 = begins_[i], nr = begins_[i + 1] - r0;
+        const int64_t units = col_major_ ? cols_ : nr;
+        const size_t unit_bytes = (size_t)(col_major_ ? nr : cols_) * sizeof(float);
+        const bool contiguous = col_major_ ? (ld_ == nr || cols_ == 1) : (ld_ == cols_ || nr == 1);
+        char *dst = static_cast<char *>(slots_[i % kUploadSlots]);
+        int64_t mine = 0;
+        for (int64_t k; (k = c.next.fetch_add(1, std::memory_order_relaxed)) < c.pieces; ++mine) {
+            const int64_t lo = k * c.per_piece, hi = std::min(units, lo + c.per_piece);
+            auto from = [&](int64_t u) { return col_major_ ? src_ + u * ld_ + r0 : src_ + (r0 + u) * ld_; };
+            if (contiguous) std::memcpy(dst + (size_t)lo * unit_bytes, from(lo), (size_t)(hi - lo) * unit_bytes);
+            else
+                for (int64_t u = lo; u < hi; ++u) std::memcpy(dst + (size_t)u * unit_bytes, from(u), unit_bytes);
+        }
+        if (mine == 0) return;
+        std::lock_guard<std::mutex> lk(mu_);
+        c.done += mine;
+        if (c.done == c.pieces) done_cv_.notify_one();
+    }
+
+    const float *src_;
+    const int64_t ld_;
+    const bool col_major_;
+    const int32_t cols_;
+    const std::vector<int64_t> begins_;  // the chunks' first rows, and the end
+    void *const *slots_;
+    std::vector<Chunk> state_;
+    std::mutex mu_;
+    std::condition_variable opened_cv_, done_cv_;
+    int64_t open_ = 0;
+    bool stop_ = false;
+    std::vector<std::thread> threads_;
+};
+
+}  // namespace
 
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes)
 {
@@ -757,12 +838,15 @@ ebic_status ebic_destroy(ebic_ctx *ctx)
             ctx->d_step_counter = nullptr;
             for (auto &kv : ctx->scratch) ctx_free(ctx, kv.second.ptr);
             ctx->scratch.clear();
-            for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < kUploadSlots; ++b) {
                 if (ctx->up_done[b]) (void)hipEventDestroy(ctx->up_done[b]);
+                if (ctx->up_laid[b]) (void)hipEventDestroy(ctx->up_laid[b]);
                 if (ctx->up_pin[b]) (void)hipHostFree(ctx->up_pin[b]);
-                ctx->up_done[b] = nullptr;
+                ctx->up_done[b] = ctx->up_laid[b] = nullptr;
                 ctx->up_pin[b] = nullptr;
             }
+            if (ctx->aux) (void)hipStreamDestroy(ctx->aux);
+            ctx->aux = nullptr;
         }
         delete ctx;
     });
@@ -817,57 +901,19 @@ ebic_status ebic_upload_matrix(ebic_ctx *ctx, const float *src, int64_t rows, in
         m.X = static_cast<float *>(ctx_alloc(ctx, bytes));
         m.bytes = bytes;
         float *staging = nullptr;
+        hipStream_t aux = nullptr;
         try {
             if (flags & EBIC_KEEP_FILL_COPY) {
                 m.Xfill = static_cast<float *>(ctx_alloc(ctx, bytes));
                 m.bytes += bytes;
             }
             m.value_bytes = m.bytes;
-            // Rows are laid out chunk by chunk through a bounded device
-            // staging buffer. A host source is first packed (by several
-            // threads) into one of two pinned buffers, so each chunk crosses
-            // as one 1-D copy and the packing of a chunk overlaps the copy
-            // and layout of the previous one.
-            const int64_t chunk_bytes = 64ll << 20;
-            int64_t chunk = std::max<int64_t>(64, chunk_bytes / ((int64_t)cols * 4) / 64 * 64);
-            chunk = std::min<int64_t>(chunk, (rows + 63) / 64 * 64);
-            const size_t stage_bytes = (size_t)chunk * cols * 4;
-            if (!on_device) {
-                staging = static_cast<float *>(ctx_alloc(ctx, stage_bytes));
-                upload_pinned(ctx, stage_bytes);
-            }
-            int64_t ci = 0;
-            for (int64_t r0 = 0; r0 < rows; r0 += chunk, ++ci) {
-                const int64_t nr = std::min<int64_t>(chunk, rows - r0);
-                const float *dsrc;
-                int64_t dld;
-                if (on_device) {
-                    dsrc = col_major ? src + r0 : src + r0 * ld_src;
-                    dld = ld_src;
-                } else {
-                    const int b = (int)(ci & 1);
-                    // The copy that last read this pinned buffer has completed.
-                    hip_check(hipEventSynchronize(ctx->up_done[b]), "hipEventSynchronize");
-                    float *pin = static_cast<float *>(ctx->up_pin[b]);
-                    pack_rows(src, ld_src, col_major, r0, nr, cols, pin);
-                    hip_check(hipMemcpyAsync(staging, pin, (size_t)nr * cols * 4, hipMemcpyHostToDevice, s),
-                              "hipMemcpyAsync");
-                    hip_check(hipEventRecord(ctx->up_done[b], s), "hipEventRecord");
-                    dsrc = staging;
-                    dld = col_major ? nr : cols;
-                }
-                // (the next chunk's copy into `staging` follows this kernel on the stream)
-                hip_check(launch_layout(dsrc, dld, col_major, nr, cols, r0, m.X, m.dev.ld,
-                                        missing_sentinel, m.Xfill, missing_fill, s),
-                          "layout kernel");
-            }
-            if (!on_device) hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-            hip_check(launch_zero_pad(m.X, rows, m.dev.ld, cols, s), "zero-pad kernel");
-            if (m.Xfill) hip_check(launch_zero_pad(m.Xfill, rows, m.dev.ld, cols, s), "zero-pad kernel");
             // Byte rank codes for matrices of at most 128 columns: four rows
             // per 32-bit word. They encode the fill-substituted values, so
             // exclude mode may use them only if no cell is missing.
-            int32_t has_nan = 1;
+            // (16-bit codes, two rows per 32-bit word, are built on first use:
+            // the 10-bit codes serve the same widths with three.)
+            int32_t *flag = nullptr, *ties = nullptr;
             if (cols <= kMaxByteCols) {
                 // whole 512-row units plus one: a chunk of four 256-row groups
                 // may start at any multiple of 512 rows
@@ -877,21 +923,11 @@ ebic_status ebic_upload_matrix(ebic_ctx *ctx, const float *src, int64_t rows, in
                 const size_t tbytes = (size_t)(m.dev.ldb / 512) * sizeof(int32_t);
                 m.B = static_cast<uint8_t *>(ctx_alloc(ctx, bbytes + 256 + tbytes));
                 m.bytes += bbytes + 256 + tbytes;
-                int32_t *flag = reinterpret_cast<int32_t *>(m.B + bbytes);
-                int32_t *ties = reinterpret_cast<int32_t *>(m.B + bbytes + 256);
+                flag = reinterpret_cast<int32_t *>(m.B + bbytes);
+                m.dev.T = ties = reinterpret_cast<int32_t *>(m.B + bbytes + 256);
                 hip_check(hipMemsetAsync(flag, 0, 256 + tbytes, s), "hipMemsetAsync");
-                hip_check(launch_byte_codes(m.X, rows, m.dev.ld, cols, missing_fill, m.B, m.dev.ldb, flag, ties,
-                                            s),
-                          "byte codes kernel");
-                m.dev.T = ties;
-                hip_check(hipMemcpyAsync(&has_nan, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s),
-                          "hipMemcpyAsync");
             }
-            // (16-bit codes, two rows per 32-bit word, are built on first use:
-            // the 10-bit codes serve the same widths with three.)
-            int32_t has_nan_h = 1;
             // 10-bit codes (three rows per 32-bit word) for 129..512 columns.
-            int32_t has_nan_t = 1;
             if (cols > kMaxByteCols && cols <= kMaxT10Cols) {
                 // an even number of 192-row groups: a chunk of two groups
                 // starts on an even one (the padding group stays zero)
@@ -901,22 +937,98 @@ ebic_status ebic_upload_matrix(ebic_ctx *ctx, const float *src, int64_t rows, in
                 const size_t fbytes = (size_t)groups * sizeof(int32_t);
                 m.T10 = static_cast<uint8_t *>(ctx_alloc(ctx, tb + 256 + fbytes));
                 m.bytes += tb + 256 + fbytes;
-                int32_t *flag = reinterpret_cast<int32_t *>(m.T10 + tb);
-                int32_t *ties = reinterpret_cast<int32_t *>(m.T10 + tb + 256);
+                flag = reinterpret_cast<int32_t *>(m.T10 + tb);
+                m.dev.Tt = ties = reinterpret_cast<int32_t *>(m.T10 + tb + 256);
                 hip_check(hipMemsetAsync(m.T10, 0, tb + 256 + fbytes, s), "hipMemsetAsync");
-                hip_check(launch_t10_codes(m.X, rows, m.dev.ld, cols, missing_fill, m.T10, m.dev.ld10, flag, ties, s),
-                          "10-bit codes kernel");
-                hip_check(hipMemcpyAsync(&has_nan_t, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s),
-                          "hipMemcpyAsync");
-                m.dev.Tt = ties;
             }
+            // Rows are laid out, and their codes made, chunk by chunk; those
+            // of a host source through bounded staging: some threads pack
+            // into pinned buffers, each chunk crosses as one 1-D copy on a
+            // stream of its own, and the kernels of a chunk run while the
+            // next ones cross. The link bounds it (57 GB/s): 54,675 x 178 (39
+            // MB) takes 1.06 ms, 436,444 x 310 11.1; with chunks of 4 MB 1.09
+            // and 12.0 (a copy's start costs some 10 us), with chunks of 64
+            // MB packed ahead and the kernels between the copies 1.28 and
+            // 13.4.
+            const int64_t chunk_bytes = (on_device ? 64ll : 8ll) << 20;
+            const int64_t unit = flag ? kUploadUnit : 64;  // (whole groups of the codes)
+            int64_t chunk = std::max<int64_t>(1, chunk_bytes / ((int64_t)cols * 4) / unit) * unit;
+            chunk = std::min<int64_t>(chunk, (rows + 63) / 64 * 64);
+            // (a smaller first one, so that the link has work soon)
+            std::vector<int64_t> begins = {0};
+            if (!on_device && rows > chunk)
+                begins.push_back(std::max<int64_t>(1, chunk / 4 / unit) * unit);
+            while (begins.back() + chunk < rows) begins.push_back(begins.back() + chunk);
+            begins.push_back(rows);
+            const int64_t chunks = (int64_t)begins.size() - 1;
+            const size_t stage_bytes = ((size_t)chunk * cols * 4 + 255) / 256 * 256;
+            const int slots = (int)std::min<int64_t>(chunks, kUploadSlots);
+            hipStream_t cs = s;  // the copies' stream
+            std::optional<Packer> packer;
+            if (!on_device) {
+                staging = static_cast<float *>(ctx_alloc(ctx, stage_bytes * slots));
+                upload_pinned(ctx, stage_bytes);
+                packer.emplace(src, ld_src, col_major, cols, begins, ctx->up_pin);
+                if (chunks > 1) {
+                    // (the staging may be used on s until here)
+                    cs = aux = aux_stream(ctx);
+                    hip_check(hipEventRecord(ctx->up_laid[0], s), "hipEventRecord");
+                    hip_check(hipStreamWaitEvent(cs, ctx->up_laid[0], 0), "hipStreamWaitEvent");
+                }
+            }
+            int64_t opened = 0;
+            for (int64_t i = 0; i < chunks; ++i) {
+                const int64_t r0 = begins[i], nr = begins[i + 1] - r0;
+                const int b = (int)(i % kUploadSlots);
+                const float *dsrc = col_major ? src + r0 : src + r0 * ld_src;
+                int64_t dld = ld_src;
+                if (!on_device) {
+                    // Pinned buffers that no copy reads any more are packed:
+                    // this chunk's, and those ahead that are free already.
+                    for (; opened < chunks && opened < i + kUploadSlots; ++opened) {
+                        hipEvent_t e = ctx->up_done[opened % kUploadSlots];
+                        if (opened == i) hip_check(hipEventSynchronize(e), "hipEventSynchronize");
+                        else if (hipEventQuery(e) != hipSuccess) break;
+                    }
+                    packer->open(opened);
+                    if (i == 0 && (size_t)rows * cols * sizeof(float) >= (4u << 20))
+                        packer->start((int)std::min(4u, std::max(1u, std::thread::hardware_concurrency()) - 1));
+                    packer->pack(i);
+                    float *to = staging + (size_t)b * (stage_bytes / sizeof(float));
+                    if (i >= kUploadSlots)
+                        hip_check(hipStreamWaitEvent(cs, ctx->up_laid[b], 0), "hipStreamWaitEvent");
+                    hip_check(hipMemcpyAsync(to, ctx->up_pin[b], (size_t)nr * cols * 4, hipMemcpyHostToDevice, cs),
+                              "hipMemcpyAsync");
+                    hip_check(hipEventRecord(ctx->up_done[b], cs), "hipEventRecord");
+                    if (cs != s) hip_check(hipStreamWaitEvent(s, ctx->up_done[b], 0), "hipStreamWaitEvent");
+                    dsrc = to;
+                    dld = col_major ? nr : cols;
+                }
+                hip_check(launch_layout(dsrc, dld, col_major, nr, cols, r0, m.X, m.dev.ld,
+                                        missing_sentinel, m.Xfill, missing_fill, s),
+                          "layout kernel");
+                if (cs != s) hip_check(hipEventRecord(ctx->up_laid[b], s), "hipEventRecord");
+                const bool last = i + 1 == chunks;
+                if (m.B)
+                    hip_check(launch_byte_codes(m.X, rows, m.dev.ld, cols, missing_fill, m.B, m.dev.ldb, flag,
+                                                ties, r0, last ? m.dev.ldb : r0 + nr, s),
+                              "byte codes kernel");
+                if (m.T10)
+                    hip_check(launch_t10_codes(m.X, rows, m.dev.ld, cols, missing_fill, m.T10, m.dev.ld10, flag,
+                                               ties, r0, last ? (rows + kT10Rows - 1) / kT10Rows * kT10Rows : r0 + nr,
+                                               s),
+                              "10-bit codes kernel");
+            }
+            packer.reset();
+            hip_check(launch_zero_pad(m.X, rows, m.dev.ld, cols, s), "zero-pad kernel");
+            if (m.Xfill) hip_check(launch_zero_pad(m.Xfill, rows, m.dev.ld, cols, s), "zero-pad kernel");
+            int32_t has_nan = 1;
+            if (flag)
+                hip_check(hipMemcpyAsync(&has_nan, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
             hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
             m.dev.b_exclude = m.B && has_nan == 0;
-            m.dev.h_exclude = m.Hc && has_nan_h == 0;
-            m.dev.t_exclude = m.T10 && has_nan_t == 0;
-            if (m.B) m.has_missing = has_nan != 0;
-            if (m.Hc) m.has_missing = has_nan_h != 0;
-            if (m.T10) m.has_missing = has_nan_t != 0;
+            m.dev.t_exclude = m.T10 && has_nan == 0;
+            if (flag) m.has_missing = has_nan != 0;
             // FP16 rank codes (half the bytes of a staged FP32 tile, missing
             // cells kept as NaN) serve exclude mode where the SWAR codes
             // cannot: on a matrix with missing cells. Other uses (a shape
@@ -930,6 +1042,7 @@ ebic_status ebic_upload_matrix(ebic_ctx *ctx, const float *src, int64_t rows, in
                 hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
             }
         } catch (...) {
+            if (aux) (void)hipStreamSynchronize(aux);
             (void)hipStreamSynchronize(s);  // nothing in flight reads what is freed
             ctx_free(ctx, staging);
             ctx_free(ctx, m.X);

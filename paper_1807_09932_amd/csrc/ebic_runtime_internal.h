@@ -56,6 +56,8 @@ struct TuneKey {
 
 struct BatchState;  // ebic_batch.cpp
 
+constexpr int kUploadSlots = 4;  // chunks of an upload in flight
+
 // Host-side fault injection plan (see parse_fault_plan).
 struct FaultPlan {
     int64_t alloc_after = -1;   // -1: off
@@ -98,11 +100,15 @@ struct ebic_ctx {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
     unsigned long long *d_step_counter = nullptr;
     // Fault injection (tests of the error paths; see FaultPlan).
-    // Pinned host staging of uploads (two buffers used alternately, and the
-    // events of the copies that last read them; under mu).
-    void *up_pin[2] = {nullptr, nullptr};
-    hipEvent_t up_done[2] = {nullptr, nullptr};
+    // Pinned host staging of uploads (buffers used in turn, the events of the
+    // copies that last read them and of the kernels that last read the device
+    // staging they fill; under mu).
+    void *up_pin[ebic::kUploadSlots] = {};
+    hipEvent_t up_done[ebic::kUploadSlots] = {}, up_laid[ebic::kUploadSlots] = {};
     size_t up_pin_bytes = 0;
+    // The stream of upload copies and of layouts built on first use (under
+    // mu; whoever uses it leaves it empty).
+    hipStream_t aux = nullptr;
     std::mutex fault_mu;
     ebic::FaultPlan fault;
     int64_t allocs_done = 0, launches_done = 0;
@@ -250,13 +256,11 @@ ReqDesc make_desc(const Matrix &m, int32_t n, const int32_t *offsets, const int3
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes);
 // Whether stream_scratch(ctx, s, bytes) would allocate.
 bool stream_scratch_grows(ebic_ctx *ctx, hipStream_t s, size_t bytes);
-// The upload's two pinned host buffers, at least `bytes` each (under mu).
+// The context's auxiliary stream (under mu).
+hipStream_t aux_stream(ebic_ctx *ctx);
+// The upload's pinned host buffers, at least `bytes` each (under mu), and
+// the events of their use.
 void upload_pinned(ebic_ctx *ctx, size_t bytes);
-// Copy rows [r0, r0 + nr) of a host matrix (row-major with row stride
-// ld_src, or column-major with column stride ld_src) into dst, packed
-// (row-major: nr x cols; column-major: cols x nr), with a few threads.
-void pack_rows(const float *src, int64_t ld_src, bool col_major, int64_t r0, int64_t nr, int32_t cols,
-               float *dst);
 // Launch one evaluation with the context's diagnostics applied.
 hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &cfg, hipStream_t s);
 
