@@ -2635,13 +2635,13 @@ int batch_occupancy(int32_t L, int32_t set, int32_t W, size_t lds)
 
 hipError_t launch_eval(const ReqDesc &d, IndHead *heads, const LaunchCfg &cfg,
                        unsigned long long *step_counter, hipStream_t s, hipEvent_t ev0,
-                       hipEvent_t ev1)
+                       hipEvent_t ev1, const FewSums &sums)
 {
     if (d.n <= 0) return hipSuccess;
     if (cfg.staging == STAGE_PAIRS && cfg.few) {
         hipError_t e;
         if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;
-        if ((e = launch_pairs_few(d, cfg.W, step_counter, s)) != hipSuccess) return e;
+        if ((e = launch_pairs_few(d, cfg.few_W, cfg.few, sums, step_counter, s)) != hipSuccess) return e;
         return ev1 ? hipEventRecord(ev1, s) : hipSuccess;
     }
     if (cfg.staging == STAGE_PAIRS) {

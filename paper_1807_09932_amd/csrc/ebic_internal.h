@@ -76,7 +76,11 @@ struct LaunchCfg {
     int32_t staging = STAGE_LDS;
     int32_t blocks = 0;   // plain: tile ranges per group; batch: persistent grid; 0 = derive
     bool cnt16 = false;   // plain: counts as 16-bit halves (16-bit codes; set by the planner)
-    bool few = false;     // plain, pair bitmaps: the one-kernel launch for few panels (set by the planner)
+    // Plain, pair bitmaps: the slices and waves per block of the one-kernel
+    // launch (few = 0: two kernels of the shape above), and its waves with
+    // one slice where there are no accumulators (0: the two kernels); set by
+    // the planner.
+    int32_t few = 0, few_W = 0, alone_W = 0;
 };
 
 // A resident matrix as the kernels see it.
@@ -187,12 +191,21 @@ inline int32_t batch_tiles(int32_t staging, int32_t L)
 }
 int batch_occupancy(int32_t L, int32_t set, int32_t W, size_t lds_bytes);
 
+// Accumulators of a one-kernel launch in slices: acc holds a zero per
+// individual, and the call zeroes used[0, n_used) (another buffer, which an
+// earlier call on the stream summed in).
+struct FewSums {
+    uint64_t *acc = nullptr;
+    uint64_t *used = nullptr;
+    int32_t n_used = 0;
+};
+
 // Plain evaluation: prep (validation, output initialisation, headers) then
 // the evaluation kernel over G groups x cfg.blocks tile ranges. ev0/ev1, if
 // not null, are recorded right before and after the evaluation kernel.
 hipError_t launch_eval(const ReqDesc &d, IndHead *heads, const LaunchCfg &cfg,
                        unsigned long long *step_counter, hipStream_t s,
-                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const FewSums &sums = FewSums());
 
 // The evaluation kernel on direct reads (ebic_direct.hip): groups of P
 // individuals over blocks of W waves, 256-row chunks.
@@ -281,8 +294,12 @@ hipError_t launch_prep_pairs(const ReqDesc &d, IndHead *heads, hipStream_t s);
 hipError_t launch_pairs(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,
                         unsigned long long *step_counter, hipStream_t s);
 // The same for matrices of at most kFewPanels panels, prep included, in one
-// kernel of blocks of W waves (no headers).
-constexpr int32_t kFewPanels = 64;
+// kernel of blocks of W waves (no headers), the panels cut into S slices
+// (with more than one, of at most kFewInd individuals and with sums).
+constexpr int32_t kFewPanels = 512;
+constexpr int32_t kFewInd = 4096;
+hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, int32_t S, const FewSums &sums,
+                            unsigned long long *step_counter, hipStream_t s);
 constexpr int32_t kPairDefaultW = 2;  // waves per block of the default plain shape
 hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, unsigned long long *step_counter, hipStream_t s);
 int64_t pair_panels(int64_t rows);  // 1,024-row panels (the evaluation's unit of rows)

@@ -749,18 +749,24 @@ k_eval_pairs(ReqDesc d, const IndHead *__restrict__ heads, int32_t P, int32_t pe
 }
 
 // The launch for matrices of few panels: the whole evaluation in one kernel.
-// A block takes eight individuals on every panel: its first two waves make
-// the headers (as the prep kernel does, into LDS), each wave works on the
-// panels wave, wave + W, ..., and the counts are summed in LDS and written
-// once, so that neither headers nor zeroed outputs come from a kernel
-// before. Bound by the launch and by a wave's chain of loads, so the next
-// panel's window is loaded while one is worked on (128 VGPRs at four waves
-// per SIMD are there for it); individuals that wait are finished on each
-// panel, and the launcher's rule holds the panels per wave to two. The
-// whole call, one after the other: 11.0 us with two kernels and 8.9 so
-// (5,000 x 100, 800 individuals).
-template <bool NEG, bool COUNT>
-__global__ void __launch_bounds__(1024) k_eval_few(ReqDesc d, int32_t n_panels, unsigned long long *step_counter)
+// A block takes eight individuals on the panels slice, slice + S, ... of one
+// of S slices: its first two waves make the headers (as the prep kernel
+// does, into LDS), each wave works on every W-th of those panels, and the
+// counts are summed in LDS, so that neither headers nor zeroed outputs come
+// from a kernel before. With one slice a block writes its counts; with more,
+// each adds them to an accumulator per individual (negative and matched 26
+// bits each, the slices added above them) and the one that adds last writes
+// them. A call zeroes the accumulators that the call before it used.
+// Bound by the launch and by a wave's chain of loads. AHEAD: the next panel's
+// window is loaded while one is worked on (at four waves per SIMD); without
+// it six waves fit, for slices of a panel per wave. Individuals that wait
+// are finished on each panel. The whole call, one after the other, with two
+// kernels and with one: 54,675 x 178 with masks, 200 individuals 14.4 and 11.9
+// us; 20,000 x 200 with missing values, 800 individuals 11.8 and 8.8 (11.2 in
+// one slice of 16 waves).
+template <bool NEG, bool COUNT, bool AHEAD>
+__global__ void __launch_bounds__(1024) k_eval_few(ReqDesc d, int32_t n_panels, int32_t S, FewSums sums,
+                                                   unsigned long long *step_counter)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ __align__(16) uint32_t head[kStep][8], desc[kStep][8];
@@ -768,7 +774,9 @@ __global__ void __launch_bounds__(1024) k_eval_few(ReqDesc d, int32_t n_panels, 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int W = blockDim.x / kWave;
-    const int32_t i0 = (int32_t)blockIdx.x * kStep;
+    const int32_t slice = (int32_t)blockIdx.x % S, i0 = (int32_t)blockIdx.x / S * kStep;
+    for (int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); i < sums.n_used; i += (int32_t)(gridDim.x * blockDim.x))
+        sums.used[i] = 0;
     for (int32_t t = wave; t < 2; t += W) {
         const int32_t own = 4 * t + (lane >> 4), j = lane & 15;
         const PairPrep p = prep_pairs_quad(d, i0 + own, i0 + own < d.n, lane);
@@ -785,7 +793,6 @@ __global__ void __launch_bounds__(1024) k_eval_few(ReqDesc d, int32_t n_panels, 
     Queue *q = reinterpret_cast<Queue *>(lds) + wave;
     const bool there = i0 + w.g < d.n;
     uint32_t m = 0, e = 0;
-    // (the next panel's loads in flight while one is worked on)
     Bits next[7];
     uint32_t word = 0;
     auto fetch = [&](int32_t r) {
@@ -796,14 +803,16 @@ __global__ void __launch_bounds__(1024) k_eval_few(ReqDesc d, int32_t n_panels, 
 #pragma unroll
         for (int u = 0; u < 7; ++u) next[u] = w.load(rs, w.line(w8[u]));
     };
-    if (wave < n_panels) fetch(wave);
+    const int32_t first = slice + wave * S, stride = W * S;
+    if (AHEAD && first < n_panels) fetch(first);
 #pragma unroll 1
-    for (int32_t r = wave; r < n_panels; r += W) {
+    for (int32_t r = first; r < n_panels; r += stride) {
+        if (!AHEAD) fetch(r);
         Bits now[7];
 #pragma unroll
         for (int u = 0; u < 7; ++u) now[u] = next[u];
         const auto pn = w.panel_from(r, word);
-        if (r + W < n_panels) fetch(r + W);
+        if (AHEAD && r + stride < n_panels) fetch(r + stride);
         int32_t queued = 0;
         const uint32_t c = w.step(
             head, q, queued, pn, i0 + w.g, there,
@@ -827,9 +836,13 @@ __global__ void __launch_bounds__(1024) k_eval_few(ReqDesc d, int32_t n_panels, 
     __syncthreads();
     const int32_t i = (int32_t)threadIdx.x;
     if (i < kStep && i0 + i < d.n) {
-        const bool ok = (head[i][0] & kHeadValid) != 0;
-        d.matched[i0 + i] = ok ? matched[i] : kInvalid;
-        if (d.negative) d.negative[i0 + i] = ok ? negative[i] : kInvalid;
+        uint64_t total = (uint64_t)(uint32_t)matched[i] | (uint64_t)(uint32_t)negative[i] << 26 | 1ull << 52;
+        if (S > 1) total += atomicAdd(reinterpret_cast<unsigned long long *>(sums.acc + i0 + i), (unsigned long long)total);
+        if (S == 1 || (int32_t)(total >> 52) == S) {
+            const bool ok = (head[i][0] & kHeadValid) != 0;
+            d.matched[i0 + i] = ok ? (int32_t)(total & 0x3ffffffu) : kInvalid;
+            if (d.negative) d.negative[i0 + i] = ok ? (int32_t)(total >> 26 & 0x3ffffffu) : kInvalid;
+        }
     }
     if (COUNT && w.steps) atomicAdd(step_counter, (unsigned long long)w.steps);
 }
@@ -991,19 +1004,26 @@ hipError_t launch_pairs_batch(const PairQueues *pq, const ReqDesc *descs, const 
     return hipGetLastError();
 }
 
-hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, unsigned long long *step_counter, hipStream_t s)
+hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, int32_t S, const FewSums &sums,
+                            unsigned long long *step_counter, hipStream_t s)
 {
-    const int64_t panels = pair_panels(d.rows);
-    if (W < 1 || W > 16 || panels > kFewPanels) return hipErrorInvalidValue;
+    const int64_t panels = pair_panels(d.rows), groups = ((int64_t)d.n + kStep - 1) / kStep;
+    if (W < 1 || W > 16 || panels > kFewPanels || S < 1 || S > panels || (S > 1 && (!sums.acc || d.n > kFewInd)) ||
+        groups * S * W * kWave > 0xffffffffll)
+        return hipErrorInvalidValue;
     const bool neg = (d.flags & kFlagNeg) != 0;
-    const dim3 grid((unsigned)((d.n + kStep - 1) / kStep));
     clear_last_error();
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(W * kWave), W * kWaveLdsFew, s, d, (int32_t)panels, step_counter);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(groups * S)), dim3(W * kWave), W * kWaveLdsFew, s, d, (int32_t)panels, S,
+                           sums, step_counter);
         return hipGetLastError();
     };
-    if (step_counter) return neg ? go(k_eval_few<true, true>) : go(k_eval_few<false, true>);
-    return neg ? go(k_eval_few<true, false>) : go(k_eval_few<false, false>);
+    if ((int64_t)W * S >= panels) {
+        if (step_counter) return neg ? go(k_eval_few<true, true, false>) : go(k_eval_few<false, true, false>);
+        return neg ? go(k_eval_few<true, false, false>) : go(k_eval_few<false, false, false>);
+    }
+    if (step_counter) return neg ? go(k_eval_few<true, true, true>) : go(k_eval_few<false, true, true>);
+    return neg ? go(k_eval_few<true, false, true>) : go(k_eval_few<false, false, true>);
 }
 
 hipError_t launch_pairs(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,

@@ -378,26 +378,41 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
                 const int64_t steps = ((int64_t)n + 7) / 8 * pair_panels(m.dev.rows);
                 cfg.P = 8 * cfg.W * (steps >= 16 * slots ? 4 : steps >= 4 * slots ? 2 : 1);
                 // The default shape on few panels: one kernel for the whole
-                // call, blocks of eight individuals and a wave per panel (up
-                // to 16), while all its blocks are resident at once (four
-                // waves per SIMD) and a wave has two panels at most, with
-                // 16 waves or, on up to 16 panels, with eight. In one call
-                // after the other, the two kernels and this one take
-                // 11.0 and 8.9 us at 5,000 x 100 and 800 individuals, 11.3
-                // and 9.0 at 20,000 x 200, 11.9 and 11.4 at 30,000 x 150
-                // and 1,600; 10.9 and 9.5 with blocks of eight at 12,483 x
-                // 150 and 2,400 (10.9 with 13 waves). Beyond: 11.4 and 12.8
-                // at 50,000 x 178 and 800, 12.0 and 12.2 at 20,000 x 200 and
-                // 2,400; with missing values there 11.8 and 11.3 at 800.
+                // call, eight individuals per block, a wave per panel, in
+                // slices of two to four panels, up to 8,192 steps (32 per CU;
+                // 24 waves of them are resident). In one call after the
+                // other, the two kernels and this one take 10.8 and 8.6 us
+                // at 5,000 x 100 and 800 individuals, 11.6 and 10.5 at
+                // 54,675 x 178 and 800 (5,400 steps), 26.7 and 12.1 at
+                // 436,444 x 64 and 120 (6,405), 13.3 and 12.9 at 54,675 x
+                // 178 and 1,200 (8,100), but 15.1 and 15.3 at 1,600 (10,800)
+                // and 31.4 and 40 or more at 436,444 x 64 and 800 (42,700).
+                // The slices' size: as little as possible of its waves
+                // without a panel (2,400 individuals on 20 panels: 11.2 us
+                // with eight slices of three, 12.2 with 16 of two), four
+                // past 128 panels (427: 12.1, and 13.8 with two).
+                // Without accumulators (see ctx_launch_eval) one slice of up
+                // to two panels per wave, while all blocks are resident
+                // (30,000 x 150 and 1,600: 11.9 and 11.4 us; 50,000 x 178
+                // and 800: 11.4 and 12.8).
+                const int64_t panels = pair_panels(m.dev.rows), blocks = ((int64_t)n + 7) / 8;
                 if (cfg.W == kPairDefaultW) {
-                    const int64_t panels = pair_panels(m.dev.rows), blocks = ((int64_t)n + 7) / 8;
                     const int64_t all = std::min<int64_t>(16, panels), half = std::min<int64_t>(8, panels);
                     auto resident = [&](int64_t W) { return blocks <= ctx->cu_count * (16 / W); };
-                    const int64_t W = panels <= 32 && resident(all) ? all : panels <= 16 && resident(half) ? half : 0;
-                    if (W > 0) {
-                        cfg.few = true;
-                        cfg.W = (int32_t)W;
-                        cfg.P = 8;
+                    cfg.alone_W = (int32_t)(panels <= 32 && resident(all) ? all : panels <= 16 && resident(half) ? half : 0);
+                    if (panels <= 4) {
+                        cfg.few = cfg.alone_W ? 1 : 0;
+                        cfg.few_W = cfg.alone_W;
+                    } else if (n <= kFewInd && panels <= kFewPanels && blocks * panels <= 32 * ctx->cu_count) {
+                        int64_t least = INT64_MAX;
+                        for (int64_t w = panels > 128 ? 4 : 2; w <= 4; ++w) {
+                            const int64_t S = std::min(panels, ((panels + w - 1) / w + 7) / 8 * 8);
+                            const int64_t W = (panels + S - 1) / S;
+                            if (S * W >= least) continue;
+                            least = S * W;
+                            cfg.few = (int32_t)S;
+                            cfg.few_W = (int32_t)W;
+                        }
                     }
                 }
             }
@@ -730,7 +745,44 @@ bool stream_scratch_grows(ebic_ctx *ctx, hipStream_t s, size_t bytes)
     return it == ctx->scratch.end() || !it->second.ptr || it->second.bytes < bytes;
 }
 
-hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &cfg, hipStream_t s)
+// The stream's accumulators for a call in slices (under launch_mu), or NULL
+// if it has none: where they cannot be had, in a capture (its replays could
+// run beside the stream's own calls) and on the per-thread stream (one handle,
+// many streams).
+static Scratch *few_sums(ebic_ctx *ctx, hipStream_t s, FewSums &sums)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s == hipStreamPerThread || hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)
+        return nullptr;
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    Scratch &sc = ctx->scratch[s];
+    if (!sc.sums) {
+        const size_t bytes = 2 * (size_t)kFewInd * sizeof(uint64_t);
+        void *p = nullptr;
+        try {
+            p = ctx_alloc(ctx, bytes);
+        } catch (const Error &) {
+            return nullptr;  // (the two kernels)
+        }
+        if (hipMemsetAsync(p, 0, bytes, s) != hipSuccess) {
+            ctx_free(ctx, p);
+            return nullptr;
+        }
+        sc.sums = static_cast<uint64_t *>(p);
+    }
+    sums.acc = sc.sums + (size_t)sc.sums_at * kFewInd;
+    sums.used = sc.sums + (size_t)(sc.sums_at ^ 1) * kFewInd;
+    sums.n_used = sc.sums_used[sc.sums_at ^ 1];
+    return &sc;
+}
+
+static void without_sums(LaunchCfg &cfg)
+{
+    cfg.few = cfg.alone_W > 0 ? 1 : 0;
+    cfg.few_W = cfg.alone_W;
+}
+
+hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &planned, hipStream_t s)
 {
     int32_t mode;
     unsigned long long *counter = nullptr;
@@ -740,18 +792,29 @@ hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &cfg
         if (mode & 2) counter = ctx->d_step_counter;
     }
     std::unique_lock<std::mutex> lkl(ctx->launch_mu, std::defer_lock);
+    LaunchCfg cfg = planned;
     IndHead *heads = nullptr;
-    if (!cfg.few) {
-        lkl.lock();
-        heads = static_cast<IndHead *>(stream_scratch(ctx, s, (size_t)d.n * sizeof(IndHead)));
-    }
+    FewSums sums;
+    Scratch *used = nullptr;
+    if (cfg.few != 1) lkl.lock();
+    if (cfg.few > 1 && !(used = few_sums(ctx, s, sums))) without_sums(cfg);
+    if (cfg.few == 0) heads = static_cast<IndHead *>(stream_scratch(ctx, s, (size_t)d.n * sizeof(IndHead)));
     fault_point_launch(ctx, "evaluation launch");
     if (log_level() >= 3)
         log_msg(3, "eval n=" + std::to_string(d.n) + " rows=" + std::to_string(d.rows) + " cols=" +
                        std::to_string(d.cols) + " L=" + std::to_string(cfg.L) + " W=" + std::to_string(cfg.W) +
                        " P=" + std::to_string(cfg.P) + " staging=" + std::to_string(cfg.staging) +
                        " blocks=" + std::to_string(cfg.blocks));
-    if (!(mode & 1)) return launch_eval(d, heads, cfg, counter, s);
+    auto launch = [&](hipEvent_t e0, hipEvent_t e1) {
+        const hipError_t e = launch_eval(d, heads, cfg, counter, s, e0, e1, sums);
+        if (used && e == hipSuccess) {
+            used->sums_used[used->sums_at] = d.n;
+            used->sums_at ^= 1;
+            used->sums_used[used->sums_at] = 0;
+        }
+        return e;
+    };
+    if (!(mode & 1)) return launch(nullptr, nullptr);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e != hipSuccess) return e;
@@ -759,7 +822,7 @@ hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &cfg
         (void)hipEventDestroy(e0);
         return e;
     }
-    e = launch_eval(d, heads, cfg, counter, s, e0, e1);
+    e = launch(e0, e1);
     if (e != hipSuccess) {
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
@@ -836,7 +899,10 @@ ebic_status ebic_destroy(ebic_ctx *ctx)
             ctx->prof_events.clear();
             ctx_free(ctx, ctx->d_step_counter);
             ctx->d_step_counter = nullptr;
-            for (auto &kv : ctx->scratch) ctx_free(ctx, kv.second.ptr);
+            for (auto &kv : ctx->scratch) {
+                ctx_free(ctx, kv.second.ptr);
+                ctx_free(ctx, kv.second.sums);
+            }
             ctx->scratch.clear();
             for (int b = 0; b < kUploadSlots; ++b) {
                 if (ctx->up_done[b]) (void)hipEventDestroy(ctx->up_done[b]);
@@ -1205,6 +1271,7 @@ ebic_status ebic_eval_population_noalloc(ebic_ctx *ctx, int32_t matrix, int32_t 
         }
         DeviceGuard g(ctx->device);
         fault_point_launch(ctx, "evaluation launch");
+        if (cfg.few > 1) without_sums(cfg);
         IndHead *heads = noalloc_scratch(ctx->device);
         if (!heads) fail(EBIC_EHIP, "the no-allocation header buffer is not set up on this device");
         hip_check(launch_eval(d, heads, cfg, nullptr, reinterpret_cast<hipStream_t>(hip_stream)),

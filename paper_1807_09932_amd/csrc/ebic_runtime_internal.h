@@ -69,6 +69,11 @@ struct FaultPlan {
 struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
+    // Accumulators of the one-kernel evaluation in slices: two buffers of
+    // kFewInd each, the one the next call sums in (all zero), and how much
+    // the calls before may have left in each.
+    uint64_t *sums = nullptr;
+    int32_t sums_at = 0, sums_used[2] = {0, 0};
 };
 
 }  // namespace ebic

@@ -1,9 +1,11 @@
 """The one-kernel evaluation of matrices of few panels (its blocks of eight
 individuals take every panel), bit-exact against the oracle at its edges:
-one panel and up to two per wave, the counts of individuals where the rule
-changes the block's waves or leaves for the two kernels, ragged last steps,
-listed ties and more ties than are listed, missing values in both modes,
-malformed individuals, and a captured call replayed on changed inputs."""
+one panel and up to several slices, the counts of individuals and panels
+where the rule changes the slices or leaves for the two kernels, ragged last
+steps, listed ties and more ties than are listed, missing values in both
+modes, malformed individuals, a captured call replayed on changed inputs, and
+calls of different sizes on two streams that take turns with the slices'
+accumulators."""
 import numpy as np
 import pytest
 
@@ -53,7 +55,9 @@ def _population(rng, cols, order, n, malformed=False):
 @pytest.mark.parametrize("rows,cols,n,kind", [
     (1, 9, 1, "plain"), (1024, 16, 7, "listed"), (1025, 17, 9, "tied"), (5_000, 41, 4_097, "listed"),
     (12_483, 30, 2_048, "plain"), (12_483, 30, 2_057, "listed"), (16_385, 25, 65, "missing"),
-    (32_767, 33, 130, "listed"), (32_768, 12, 33, "tied"), (32_769, 12, 33, "plain"), (20_011, 64, 257, "missing")])
+    (32_767, 33, 130, "listed"), (32_768, 12, 33, "tied"), (32_769, 12, 33, "plain"), (20_011, 64, 257, "missing"),
+    (4_096, 20, 300, "listed"), (4_097, 20, 300, "tied"), (8_193, 20, 4_096, "plain"), (54_675, 20, 1_201, "listed"),
+    (131_072, 15, 120, "tied"), (131_073, 15, 120, "missing"), (524_288, 9, 9, "listed"), (524_289, 9, 9, "plain")])
 def test_few_panels(ctx, rows, cols, n, kind):
     rng = np.random.default_rng(rows + n)
     X, order = _matrix(rng, rows, cols, kind)
@@ -103,5 +107,46 @@ def test_few_panels_captured(ctx):
             got = tuple(t.cpu().numpy() for t in out)
             got = got[:2] + tuple(t.view(np.uint64) for t in got[2:])
             assert_same(got, oracle_eval(X, o, c), "replay")
+    finally:
+        ctx.release(mat)
+
+
+def test_few_panels_in_turn(ctx):
+    """Calls of different sizes one after the other, on two streams, with a
+    captured one between: each call's counts start from zero."""
+    import torch
+    rng = np.random.default_rng(4)
+    rows, cols = 6_001, 30
+    X, order = _matrix(rng, rows, cols, "listed")
+    sizes = (4_096, 8, 100, 4_000, 1, 333)
+    pops = [_population(rng, cols, order, n, malformed=n > 50) for n in sizes]
+    want = [oracle_eval(X, o, c, masks=False) for o, c in pops]
+    mat = ctx.upload(X)
+    try:
+        dev = [ctx.population(offsets=o, cols=c) for o, c in pops]
+        streams = [torch.cuda.Stream() for _ in range(2)]
+        torch.cuda.synchronize()
+        out = ctx.outputs(mat, sizes[2])
+        ctx.eval(mat, dev[1])  # (what a first call builds cannot be built in a capture)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=streams[0]):
+            ctx.eval(mat, dev[2], out=out, stream=streams[0])
+        for turn in range(3):
+            got = []
+            for i in range(len(sizes)):
+                for k, s in enumerate(streams):
+                    q = (i * (k + 1) + turn) % len(sizes)
+                    announce("few panels in turn", turn, k, sizes[q])
+                    with torch.cuda.stream(s):
+                        got.append((q, ctx.eval(mat, dev[q], stream=s)))
+            torch.cuda.synchronize()
+            for t in out[:2]:
+                t.fill_(-7)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            for q, o in got + [(2, out)]:
+                assert_same((o[0].cpu().numpy(), o[1].cpu().numpy(), None, None), want[q], f"turn {turn} {sizes[q]}")
     finally:
         ctx.release(mat)
