@@ -50,8 +50,9 @@ SWAR_STAGES = (STAGE_BYTES, STAGE_HALVES, STAGE_T10)
 # The L2 the pair bitmaps come through: per XCD 16 channels x 128 B per
 # clock, eight XCDs at 2.4 GHz: 39.3 TB/s.
 L2_PEAK_GBS = 8 * 16 * 128 * 2.4e9 / 1e9
-PAIR_CHUNK_ROWS = 2048  # rows of one 32-bit word per lane of a wave
-PAIR_WORD_BYTES = 256   # one pair's words on one chunk (64 lanes x 4 B)
+PAIR_PANEL_ROWS = 1024  # rows of one pair's line (eight lanes x 16 B)
+PAIR_LINE_BYTES = 128
+PAIR_TIE_ROWS = 2048    # rows of one 512-byte list of tied pairs
 ROWS_PER_OP = {STAGE_BYTES: 4, STAGE_HALVES: 2, STAGE_T10: 3}
 
 
@@ -68,9 +69,10 @@ def alu_roofline(steps, k_ms, staging):
             "frac": ach / CMP_PEAK_TOPS}
 
 
-def pair_window_pairs(offs, cols, ncols):
-    """The distinct ordered column pairs the pair-bitmap kernel reads for
-    every chunk: per individual, the pairs of different columns among its
+def pair_window_pairs(offs, cols, ncols, ordered=True):
+    """The distinct column pairs the pair-bitmap kernel reads for every
+    panel (ordered=False: as it reads them, one line for both orders): per
+    individual, the pairs of different columns among its
     first eight (after a leading run of repeats of the first column), or
     the one column's diagonal pair."""
     seen = set()
@@ -86,30 +88,30 @@ def pair_window_pairs(offs, cols, ncols):
         w += [w[-1]] * (8 - len(w))
         pairs = {(w[u], w[u + 1]) for u in range(7) if w[u] != w[u + 1]}
         seen |= pairs or {(w[0], w[0])}
-    return len(seen)
+    return len(seen if ordered else {(min(p), max(p)) for p in seen})
 
 
 def pairs_roofline(offs, cols, rows, ncols, steps, k_ms):
     """The HBM roofline of the pair-bitmap kernel: its algorithmic bytes are
-    the words of the distinct window pairs on every 2,048-row chunk (each
-    read once per launch), the chunks' tie lists, the individuals' headers
-    and the counts, over the kernel time."""
+    the lines of the distinct window pairs on every 1,024-row panel (each
+    read once per launch), the tie lists, the individuals' headers and the
+    counts, over the kernel time."""
     n = offs.size - 1
-    chunks = -(-rows // PAIR_CHUNK_ROWS)
-    d = pair_window_pairs(offs, cols, ncols)
-    nbytes = d * PAIR_WORD_BYTES * chunks + 512 * chunks + 64 * n + 8 * n
+    panels = -(-rows // PAIR_PANEL_ROWS)
+    d = pair_window_pairs(offs, cols, ncols, ordered=False)
+    nbytes = d * PAIR_LINE_BYTES * panels + 512 * (-(-rows // PAIR_TIE_ROWS)) + 64 * n + 8 * n
     t = k_ms * 1e-3
     ach = nbytes / t / 1e9
     return {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
-            "algorithmic_bytes": nbytes, "distinct_window_pairs": d, "chunks": chunks,
-            "frac_basis": "the bytes this formulation must read per launch (the window pairs' words on every "
-                          "chunk); roofline_views.hbm_min_bytes gives the fraction on the method's own minimum, "
-                          "the FP32 matrix read once",
-            "l2_view": {"bytes": steps * PAIR_WORD_BYTES, "achieved": steps * PAIR_WORD_BYTES / t / 1e9,
+            "algorithmic_bytes": nbytes, "distinct_window_pairs": d, "panels": panels,
+            "frac_basis": "the bytes this formulation must read per launch (the window pairs' lines, one for "
+                          "both orders of a pair, on every panel); roofline_views.hbm_min_bytes gives the "
+                          "fraction on the method's own minimum, the FP32 matrix read once",
+            "l2_view": {"bytes": steps * PAIR_LINE_BYTES, "achieved": steps * PAIR_LINE_BYTES / t / 1e9,
                         "peak": L2_PEAK_GBS, "unit": "GB/s",
-                        "frac": steps * PAIR_WORD_BYTES / t / 1e9 / L2_PEAK_GBS,
-                        "note": "pair-word loads executed (window and tail, counted by the "
-                                "measurement variant) x 256 B, against the L2's 16 channels x "
+                        "frac": steps * PAIR_LINE_BYTES / t / 1e9 / L2_PEAK_GBS,
+                        "note": "pair-line loads executed (window and tail, counted by the "
+                                "measurement variant) x 128 B, against the L2's 16 channels x "
                                 "128 B per clock per XCD"}}
 
 
@@ -123,7 +125,8 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("ebic_eval.hip", "ebic_chain.inc", "ebic_internal.h", "ebic_pairs.hip", "ebic_prep.h")
+KERNEL_SOURCES = ("ebic_eval.hip", "ebic_chain.inc", "ebic_direct.hip", "ebic_internal.h", "ebic_pairs.hip",
+                  "ebic_prep.h")
 
 
 def kernel_sources_sha():
@@ -306,13 +309,13 @@ def roofline_views(executed_steps, k_ms, staging, matrix_bytes, n_ind):
             "individual written) over the kernel time; the bitmap kernel reads the words of the "
             "population's window pairs instead (the roofline above), a different byte count: "
             "this fraction is what the same time would give a kernel that read only the matrix")
-        # (a pair step ANDs one 32-bit word per lane: 2,048 rows of one
-        # column pair, the outcome of 2,048 FP32 compares made at the build)
+        # (a pair step ANDs one line, 16 bytes in each of eight lanes: 1,024
+        # rows of one column pair, FP32 compares made at the build)
         views["fp32_compare_issue"] = {
-            "bound": "alu", "achieved": executed_steps * PAIR_CHUNK_ROWS / t / 1e12, "peak": CMP_PEAK_TOPS,
+            "bound": "alu", "achieved": executed_steps * PAIR_PANEL_ROWS / t / 1e12, "peak": CMP_PEAK_TOPS,
             "unit": "T compare outcomes/s",
-            "frac": executed_steps * PAIR_CHUNK_ROWS / t / 1e12 / CMP_PEAK_TOPS,
-            "note": "executed pair steps x 2,048 rows: the FP32 compare outcomes the kernel "
+            "frac": executed_steps * PAIR_PANEL_ROWS / t / 1e12 / CMP_PEAK_TOPS,
+            "note": "executed pair steps x 1,024 rows: the FP32 compare outcomes the kernel "
                     "combines, as if each were a lane compare; above 1 because the bitmaps hold "
                     "32 outcomes per lane word"}
     elif staging not in SWAR_STAGES:
@@ -429,8 +432,8 @@ def bench_batched(ctx, args):
 
 def batched_roofline(steps, g_ms, stagings, shape, packed, rows, ncols):
     """The batched launch's roofline: on the pair bitmaps, their HBM roofline
-    over all populations together (the words of the distinct window pairs
-    of every population, once per chunk: the batch walks each chunk for all
+    over all populations together (the lines of the distinct window pairs
+    of every population, once per panel: the batch walks each panel for all
     of them); on rank codes, the compare-issue roofline."""
     one = len(set(stagings)) == 1
     if one and stagings[0] == STAGE_PAIRS:
@@ -441,8 +444,8 @@ def batched_roofline(steps, g_ms, stagings, shape, packed, rows, ncols):
         out = {**pairs_roofline(offs, cols, rows, ncols, steps, g_ms), "traffic": tr,
                "time": "the graph replay (descriptor copy, prep, the persistent pairs kernel)"}
         if tr:
-            # (each chunk's words of all the batch's pairs, ~16 MB at 256
-            # columns, outgrow an XCD's L2: words come in several times)
+            # (each panel's lines of all the batch's pairs, ~4 MB at 256
+            # columns, fill an XCD's L2: some come in several times)
             out["physical_gbs"] = tr / (g_ms * 1e-3) / 1e9
             out["physical_frac"] = out["physical_gbs"] / HBM_PEAK_GBS
             out["physical_note"] = ("the committed FETCH_SIZE + WRITE_SIZE bytes per launch over the "
@@ -1095,11 +1098,11 @@ def main():
                       "records around each evaluation kernel on its stream, over a second "
                       "pass of the same K steps (that pass took %.4f ms per step: the events "
                       "cost GPU time)" % (wall_events * 1e3 / args.steps),
-            "ops": (("pair bitmaps: per 2,048-row chunk, the words (256 B) of each of the "
+            "ops": (("pair bitmaps: per 1,024-row panel, the lines (128 B) of each of the "
                      "population's %d distinct window pairs, read once per launch, plus 512 B of "
-                     "tie list per chunk and 72 B per individual (header, counts); %d pair steps "
-                     "executed (a wave's AND of one pair word per lane over 2,048 rows, window "
-                     "and tail)" % (roof["distinct_window_pairs"], executed_steps))
+                     "tie list per 2,048 rows and 72 B per individual (headers, counts); %d pair "
+                     "steps executed (eight lanes' AND of one line over 1,024 rows, window and "
+                     "tail)" % (roof["distinct_window_pairs"], executed_steps))
                     if stg == STAGE_PAIRS else
                     ("row checks executed per launch: %d steps x 64 rows (one step = one column "
                      "of one 64-row sub-tile; the first pair counts one step; early exit per "
