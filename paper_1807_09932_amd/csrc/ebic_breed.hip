@@ -317,6 +317,15 @@ __global__ void __launch_bounds__(kThreads) k_breed_pack(int32_t n, int32_t k_ma
     const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x / kWave);
     const int32_t c0 = (int32_t)blockIdx.x * per, m = min(per, n - c0);
     const int32_t own = lane < m ? lens[c0 + lane] : 0;
+    // (a slot is read whole, before its length is known: the loads go out
+    // with those of the lengths)
+    constexpr int kAhead = 4;
+    int32_t ahead[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        const int32_t t = wave + u * waves;
+        ahead[u] = t < m && lane < k_max ? slots[(int64_t)(c0 + t) * k_max + lane] : 0;
+    }
     int32_t before = 0;
 #pragma unroll 4
     for (int32_t j = (int32_t)threadIdx.x; j < c0; j += kThreads) before += lens[j];
@@ -332,11 +341,16 @@ __global__ void __launch_bounds__(kThreads) k_breed_pack(int32_t n, int32_t k_ma
     for (int v = 0; v < waves; ++v) end += part[v];
     if (wave == 0 && lane < m) offsets[c0 + lane + 1] = end;
     if (blockIdx.x == 0 && threadIdx.x == 0) offsets[0] = 0;
-#pragma unroll 4
-    for (int32_t t = wave; t < m; t += waves) {
+    auto put = [&](int32_t t, int32_t col) {
         const int32_t len = __builtin_amdgcn_readlane(own, t), at = __builtin_amdgcn_readlane(end, t) - len;
-        if (lane < len) cols[at + lane] = slots[(int64_t)(c0 + t) * k_max + lane];
-    }
+        if (lane < len) cols[at + lane] = col;
+    };
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+        if (wave + u * waves < m) put(wave + u * waves, ahead[u]);
+#pragma unroll 4
+    for (int32_t t = wave + kAhead * waves; t < m; t += waves)
+        put(t, lane < k_max ? slots[(int64_t)(c0 + t) * k_max + lane] : 0);
 }
 
 // The whole breeding of a population of at most 1,024 in one workgroup of
