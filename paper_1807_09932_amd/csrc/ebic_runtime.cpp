@@ -463,8 +463,8 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
         if (!asked_direct || asked_P <= 0) {
             // Four waves per block; four individuals per wave where that
             // leaves a wave for every resident slot, else two (a wave loads
-            // two together): 20,000 x 900, 800 individuals 33.3 and 31.5 us
-            // with two and four, 100 individuals 12.1 and 12.6 us.
+            // two together): 20,000 x 900, 800 individuals 26.7 and 26.1 us
+            // with two and four, 3,200 81.7 and 73.7, 100 12.1 and 12.6.
             const int64_t slots = (int64_t)ctx->cu_count * 32;
             cfg.W = 4;
             cfg.P = std::min(cfg.W * ((int64_t)n * chunks >= 4 * slots ? 4 : 2), std::max(1, n));

@@ -77,3 +77,29 @@ def test_direct_reads(ctx, rows, keep):
     finally:
         ctx.set_launch_shape()
         ctx.release(mat)
+
+
+def test_columns_past_four_gigabytes(ctx):
+    """A matrix whose columns do not all start within 4 GB of the first takes
+    64-bit addresses; compared with the oracle on the columns that are used."""
+    import torch
+    rows, cols = 1_100_003, 1_000
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Xd = torch.empty(rows, cols, dtype=torch.float32, device="cuda").uniform_(-1, 1, generator=g)
+    used = np.array([0, 1, 500, 975, 976, 977, 998, 999], np.int32)
+    rng = np.random.default_rng(6)
+    picks = [rng.permutation(used.size)[: int(rng.integers(1, used.size + 1))] for _ in range(40)]
+    picks += [np.array([7]), np.array([0, 7]), np.arange(used.size)]
+    X = Xd[:, torch.from_numpy(used.astype(np.int64)).cuda()].cpu().numpy()
+    mat = ctx.upload(Xd)
+    del Xd
+    try:
+        for negative in (True, False):
+            announce("direct past 4 GB", rows, cols, negative)
+            offs, cc = gen.csr([used[p] for p in picks])
+            so, sc = gen.csr([p.astype(np.int32) for p in picks])
+            got = gpu_eval(ctx, mat, offs, cc, negative=negative, masks=True)
+            want = oracle_eval(np.ascontiguousarray(X), so, sc, negative=negative, masks=True)
+            assert_same(got, want, f"{rows}x{cols} negative={negative}")
+    finally:
+        ctx.release(mat)
