@@ -125,8 +125,7 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("ebic_eval.hip", "ebic_chain.inc", "ebic_direct.hip", "ebic_internal.h", "ebic_pairs.hip",
-                  "ebic_prep.h")
+KERNEL_SOURCES = ("ebic_eval.hip", "ebic_chain.inc", "ebic_internal.h", "ebic_pairs.hip", "ebic_prep.h")
 
 
 def kernel_sources_sha():
