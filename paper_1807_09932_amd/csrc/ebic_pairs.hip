@@ -111,25 +111,29 @@ __global__ void __launch_bounds__(256) k_prep_pairs(ReqDesc d, IndHead *__restri
 // (8 x tiles, chunks / 8): block (x, y) takes chunk 8 y + x mod 8 and tile
 // x / 8, so a chunk's blocks run on one XCD and its columns stay in its L2.
 //
-// A pair's word is built bit by bit: a compare into a scalar pair, and an
-// add with carry that shifts the word left and takes the bit. Without
-// missing cells (FULL false) only the ascending orientation's words are
-// written, and a second compare (equal, kept as one mask per word) finds the
-// pairs with a tie, whose reverse is then computed and written too and which
-// go to the chunk's list: three vector instructions per row and pair. With
-// missing cells (FULL), or on the chunks whose list has overflowed (a second
-// launch; `dirty` = the list's limit, chunks below it exit at once), both
-// orientations are built with four. The first version compared both ways
-// with about eight (a compare, its wait states, a select, half an or), read
-// each column with lanes 128 bytes apart (64 lines per load) and wrote both
-// orientations of every pair.
+// A pair's word is built bit by bit. Without missing cells (FULL false) only
+// the ascending orientation's words are written, from the signs of the
+// differences: a subtraction, a shift that takes the sign in, and half a
+// three-way minimum that finds the pairs with a tie, whose reverse is then
+// computed and written too and which go to the chunk's list: two and a half
+// vector instructions per row and pair. Once an infinity has been staged,
+// compares take their place: a compare into a scalar pair, an add with carry
+// that shifts the word left and takes the bit, and a second compare (equal,
+// kept as one mask per word). With missing cells (FULL), or on the chunks
+// whose list has overflowed (a second launch; `dirty` = the list's limit,
+// chunks below it exit at once), both orientations are built by compares
+// with four. The first version compared both ways with about eight (a
+// compare, its wait states, a select, half an or), read each column with
+// lanes 128 bytes apart (64 lines per load) and wrote both orientations of
+// every pair.
 //
-// Bound by the vector unit (114 instructions per pair and 2,048 rows) and,
-// with four waves per SIMD, by the waits for LDS and the barriers: 54,675 x
-// 178 507 -> 190 us, 436,444 x 64 330 -> 258 us, 436,444 x 310 5.0 -> 3.0
-// ms; 20,000 x 200 with 5% missing cells 476 -> 147 us, and 818 -> 156 us of
-// the substituted values, whose every pair ties: a block stops listing once
-// the list has overflowed.
+// Bound by the vector unit (some 100 instructions per pair and 2,048 rows)
+// and, with four waves per SIMD, by the waits for LDS and the barriers. The
+// first version, compares and differences: 54,675 x 178 507, 195 and 178 us,
+// 436,444 x 64 330, 257 and 232 us, 436,444 x 310 5.0, 3.05 and 2.77 ms,
+// 100,000 x 256 1.16, 0.82 and 0.71 ms; 20,000 x 200 with 5% missing cells
+// 476 and 147 us, and 818 and 156 us of the substituted values, whose every
+// pair ties: a block stops listing once the list has overflowed.
 // ---------------------------------------------------------------------------
 constexpr int kBuildWaves = 8;
 constexpr int kBuildA = 2;                          // columns a per wave
@@ -166,7 +170,25 @@ __device__ __forceinline__ void ge4_ties(uint32_t &word, uint64_t &tie, const fl
                  : "scc");
 }
 
-// The same bits alone.
+// The same from the differences, for 32 rows without infinities and negative
+// zeros: a difference's sign bit is the comparison (it is exact in its sign,
+// subnormal ones included), and it is +0, the smallest bit pattern, exactly
+// where the two are equal.
+__device__ __forceinline__ uint32_t ge32_ties(uint64_t &tie, const float *x, const float *y)
+{
+    uint32_t less = 0, least = ~0u;
+#pragma unroll
+    for (int r = 30; r >= 0; r -= 2) {
+        const uint32_t d1 = __float_as_uint(x[r + 1] - y[r + 1]), d0 = __float_as_uint(x[r] - y[r]);
+        less = __builtin_amdgcn_alignbit(less, d1, 31);
+        less = __builtin_amdgcn_alignbit(less, d0, 31);
+        asm volatile("v_min3_u32 %0, %0, %1, %2" : "+v"(least) : "v"(d1), "v"(d0));
+    }
+    tie = __ballot(least == 0);
+    return ~less;
+}
+
+// The comparisons' bits alone.
 __device__ __forceinline__ void ge4(uint32_t &word, const float *x, const float *y)
 {
     uint64_t g0, g1, g2, g3;
@@ -189,6 +211,7 @@ k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols,
             int32_t dirty, uint32_t *__restrict__ G, uint32_t *__restrict__ T)
 {
     __shared__ __align__(16) float tile[kBuildTile];
+    __shared__ int32_t infinite;  // an infinity has been staged
     const int64_t chunk = 8 * (int64_t)blockIdx.y + (blockIdx.x & 7);
     const int32_t runs = (cols + run - 1) / run;
     const int32_t a0 = (int32_t)(blockIdx.x >> 3) / runs * kBuildCols, b0 = (int32_t)(blockIdx.x >> 3) % runs * run;
@@ -215,6 +238,16 @@ k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols,
             f.z = f.z != f.z ? fill : f.z;
             f.w = f.w != f.w ? fill : f.w;
         }
+        if (!FULL) {
+            // (no negative zeros)
+            f.x += 0.f;
+            f.y += 0.f;
+            f.z += 0.f;
+            f.w += 0.f;
+            const float inf = __builtin_inff();
+            const bool some = (fabsf(f.x) == inf || fabsf(f.y) == inf) || (fabsf(f.z) == inf || fabsf(f.w) == inf);
+            if (some) infinite = 1;
+        }
         if (r + 3 >= rows) {
             if (r >= rows) f.x = pad;
             if (r + 1 >= rows) f.y = pad;
@@ -237,6 +270,10 @@ k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols,
         }
     };
     static_assert(kChunkRows == 4 * kBuildWaves * kWave, "a thread stages four rows of each column b");
+    if (!FULL) {
+        if (threadIdx.x == 0) infinite = 0;
+        __syncthreads();
+    }
     // The wave's columns a, through a part of the LDS of its own.
     float xa[kBuildA][32];
     {
@@ -247,7 +284,7 @@ k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols,
             for (int q = 0; q < kBuildWaves; ++q) {
                 const int f = q * kWave + lane;
                 *reinterpret_cast<float4 *>(own + place(f)) =
-                    fixed(fetch(a0 + kBuildA * wave + i, c0 + 4 * f), c0 + 4 * f, __builtin_inff());
+                    fixed(fetch(a0 + kBuildA * wave + i, c0 + 4 * f), c0 + 4 * f, 1.f);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             take(own, xa[i]);
@@ -278,6 +315,7 @@ k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols,
             if (b >= b1 || b < aw) continue;
             float xb[32];
             take(buf + q * kWave * kLaneFloats, xb);
+            const bool differ = !FULL && __builtin_amdgcn_readfirstlane(infinite) == 0;
 #pragma unroll
             for (int i = 0; i < kBuildA; ++i) {
                 const int32_t a = aw + i;
@@ -288,8 +326,12 @@ k_pair_bits(const float *__restrict__ X, int64_t rows, int64_t ld, int32_t cols,
                 const int64_t up = ((panel * cols + a) * cols + b) * kPanelWords + (lane & 31);
                 const int64_t down = ((panel * cols + b) * cols + a) * kPanelWords + (lane & 31);
                 if (!FULL) {
+                    if (differ) {
+                        ge = ge32_ties(tie, xb, xa[i]);
+                    } else {
 #pragma unroll
-                    for (int r = 28; r >= 0; r -= 4) ge4_ties(ge, tie, xb + r, xa[i] + r);
+                        for (int r = 28; r >= 0; r -= 4) ge4_ties(ge, tie, xb + r, xa[i] + r);
+                    }
                     G[up] = ge & vmask;
                     if (a == b || tie == 0) continue;
                 } else {

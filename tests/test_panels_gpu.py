@@ -92,3 +92,34 @@ def test_long_lists(ctx):
     finally:
         ctx.set_launch_shape()
         ctx.release(mat)
+
+
+@pytest.mark.parametrize("kind", ["finite", "infinite", "late"])
+def test_order_words_of_special_values(ctx, kind):
+    """The build compares by the sign of differences where no infinity has
+    been staged: signed zeros, subnormal neighbours, differences that
+    overflow, neighbouring floats; with infinities, from the first column on
+    or in the last one only, by comparisons."""
+    rng = np.random.default_rng(8)
+    rows, cols = 2_300, 37
+    big, tiny = np.finfo(np.float32).max, np.float32(1e-45)
+    values = np.array([0.0, -0.0, tiny, -tiny, 2 * tiny, np.finfo(np.float32).tiny, big, -big, 1.0,
+                       np.nextafter(np.float32(1), np.float32(2)), -1.0, 3e38], np.float32)
+    X = _tie_free(rng, rows, cols)
+    X[::7] = rng.choice(values, size=X[::7].shape)
+    X[5, :5] = (1.0, np.nextafter(np.float32(1), np.float32(2)), -0.0, 0.0, tiny)
+    if kind == "infinite":
+        X[::5, ::3] = np.inf
+        X[1::5, 1::4] = -np.inf
+    elif kind == "late":
+        X[::3, cols - 1] = np.inf
+        X[1::9, cols - 2] = np.inf
+    offs, cc = _population(rng, cols, rng.permutation(cols).astype(np.int32), 160)
+    mat = ctx.upload(X)
+    try:
+        for negative in (True, False):
+            announce("special order words", kind, negative)
+            got = gpu_eval(ctx, mat, offs, cc, negative=negative, masks=True)
+            assert_same(got, oracle_eval(X, offs, cc, negative=negative, masks=True), f"{kind} negative={negative}")
+    finally:
+        ctx.release(mat)
