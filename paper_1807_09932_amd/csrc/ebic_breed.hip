@@ -12,9 +12,9 @@
 // the elites. A second kernel (k_breed_pack) turns the lengths into offsets
 // and packs the slots into the CSR. Two things remain for the other calls:
 //   - k_breed_small, one workgroup that needs no scratch, for populations of
-//     up to 1,024 (whose arrays fit LDS) where the stream's scratch cannot
-//     be had: under a capture before the scratch exists, or when its
-//     allocation fails; and for those with k_max above 64;
+//     up to 1,024 (whose arrays fit LDS) where the stream's scratch is not
+//     to be used: under a capture, or when its allocation fails; and for
+//     those with k_max above 64;
 //   - five kernels for larger populations with k_max above 64: fitness; the
 //     elites' order; one thread per child breeding into its slot; one block
 //     turning the lengths into offsets; one thread per child copying its
@@ -469,9 +469,11 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
         std::lock_guard<std::mutex> lk(ctx->launch_mu);
         if (p.k_max <= kWave) {
             unsigned char *base = nullptr;
-            if (small && stream_scratch_grows(ctx, s, l_bytes + s_bytes)) {
-                // A capture cannot wait for the stream, and a population of
-                // this size never needed memory: without it, one workgroup.
+            if (small) {
+                // A population of this size needs no memory of the library's:
+                // a captured call takes none, so that its graph holds nothing
+                // that a later call on the stream may replace or write beside
+                // a replay, and without memory one workgroup breeds as well.
                 hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
                 const bool free = hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
                 clear_last_error();

@@ -738,13 +738,6 @@ void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes)
     return sc.ptr;
 }
 
-bool stream_scratch_grows(ebic_ctx *ctx, hipStream_t s, size_t bytes)
-{
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    auto it = ctx->scratch.find(s);
-    return it == ctx->scratch.end() || !it->second.ptr || it->second.bytes < bytes;
-}
-
 // The stream's accumulators for a call in slices (under launch_mu), or NULL
 // if it has none: where they cannot be had, in a capture (its replays could
 // run beside the stream's own calls) and on the per-thread stream (one handle,

@@ -259,8 +259,6 @@ ReqDesc make_desc(const Matrix &m, int32_t n, const int32_t *offsets, const int3
 // At least `bytes` of device scratch private to stream `s` (grown on demand;
 // a grown buffer replaces the old one after the stream has drained).
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes);
-// Whether stream_scratch(ctx, s, bytes) would allocate.
-bool stream_scratch_grows(ebic_ctx *ctx, hipStream_t s, size_t bytes);
 // The context's auxiliary stream (under mu).
 hipStream_t aux_stream(ebic_ctx *ctx);
 // The upload's pinned host buffers, at least `bytes` each (under mu), and

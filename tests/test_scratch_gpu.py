@@ -1,0 +1,94 @@
+"""The device memory that calls on a stream share (headers, children's slots):
+which calls keep out of it."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_1807_09932_amd import ebic, gen
+from tests.gpu_common import announce, assert_same, oracle_eval, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def ctx():
+    from paper_1807_09932_amd.ebic import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+class _Breeding:
+    """A generation of n individuals and the buffers of the next one."""
+
+    def __init__(self, ctx, n, seed, n_cols=120, k_max=30):
+        import torch
+        self.n, self.n_cols, self.k_max, self.seed = n, n_cols, k_max, seed
+        ea = ebic.EA(n_cols, n, 2, k_max, seed=seed)
+        offs, cols, _ = ea.population()
+        self.params = ea.params
+        ea.close()
+        self.pop = ctx.population(offsets=offs, cols=cols)
+        self.matched = torch.zeros(n, dtype=torch.int32, device=ctx.device)
+        self.out = (torch.zeros(n + 1, dtype=torch.int32, device=ctx.device),
+                    torch.zeros(n * k_max, dtype=torch.int32, device=ctx.device),
+                    torch.zeros(1, dtype=torch.int32, device=ctx.device))
+
+    def breed(self, ctx, stream):
+        ctx.breed(self.params, 1, self.pop, self.matched, stream=stream, out=self.out)
+
+    def set_counts(self, counts):
+        import torch
+        self.counts = counts
+        self.matched.copy_(torch.from_numpy(counts))
+
+    def check(self, what):
+        ea = ebic.EA(self.n_cols, self.n, 2, self.k_max, seed=self.seed)
+        best, _ = ea.step(self.counts)
+        offs, cols, _ = ea.population()
+        ea.close()
+        got = to_np(self.out[0])
+        assert int(self.out[2].cpu()[0]) == best, what
+        assert np.array_equal(offs, got) and np.array_equal(cols, to_np(self.out[1])[: int(got[-1])]), what
+
+
+def _graph_nodes(graph):
+    """The number of nodes of a captured graph."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    n = ctypes.c_size_t(0)
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("n", [2, 800, 1024])
+def test_captured_small_breeding_holds_no_scratch(ctx, n):
+    """A captured breeding of up to 1,024 individuals is one kernel on the
+    caller's buffers, though the stream has scratch: replays stay right when
+    the scratch has been replaced, and beside calls that write it."""
+    import torch
+    rng = np.random.default_rng(n)
+    b = _Breeding(ctx, n, seed=n)
+    large = _Breeding(ctx, 5000, seed=5)
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        b.breed(ctx, s)
+        s.synchronize()
+        announce("capture with scratch in place", n)
+        graph.capture_begin()
+        b.breed(ctx, s)
+        graph.capture_end()
+    assert _graph_nodes(graph) == 1
+    for rnd in range(3):
+        b.set_counts(rng.integers(-1, 50, size=n).astype(np.int32))
+        large.set_counts(rng.integers(-1, 50, size=5000).astype(np.int32))
+        torch.cuda.synchronize()
+        announce("replay beside a larger breeding", n, rnd)
+        large.breed(ctx, s)  # (the first one replaces the scratch)
+        with torch.cuda.stream(other):
+            graph.replay()
+        torch.cuda.synchronize()
+        b.check(rnd)
+        large.check(rnd)
