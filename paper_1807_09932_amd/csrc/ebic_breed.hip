@@ -13,8 +13,8 @@
 // and packs the slots into the CSR. Two things remain for the other calls:
 //   - k_breed_small, one workgroup that needs no scratch, for populations of
 //     up to 1,024 (whose arrays fit LDS) where the stream's scratch is not
-//     to be used: under a capture, or when its allocation fails; and for
-//     those with k_max above 64;
+//     to be used: under a capture, on the per-thread stream, or when its
+//     allocation fails; and for those with k_max above 64;
 //   - five kernels for larger populations with k_max above 64: fitness; the
 //     elites' order; one thread per child breeding into its slot; one block
 //     turning the lengths into offsets; one thread per child copying its
@@ -473,12 +473,15 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
                 // A population of this size needs no memory of the library's:
                 // a captured call takes none, so that its graph holds nothing
                 // that a later call on the stream may replace or write beside
-                // a replay, and without memory one workgroup breeds as well.
+                // a replay, nor does one on the per-thread stream (one handle,
+                // many streams), and without memory one workgroup breeds as
+                // well.
                 hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-                const bool free = hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+                const bool own = s != hipStreamPerThread && hipStreamIsCapturing(s, &st) == hipSuccess &&
+                                 st == hipStreamCaptureStatusNone;
                 clear_last_error();
                 try {
-                    if (free) base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes));
+                    if (own) base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes));
                 } catch (const Error &e) {
                     if (e.code != EBIC_ENOMEM) throw;
                 }

@@ -1,6 +1,7 @@
 """The device memory that calls on a stream share (headers, children's slots):
 which calls keep out of it."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -92,3 +93,63 @@ def test_captured_small_breeding_holds_no_scratch(ctx, n):
         torch.cuda.synchronize()
         b.check(rnd)
         large.check(rnd)
+
+
+class _Allocator:
+    """Device memory from torch, counted; `make` changes what is returned."""
+
+    def __init__(self, make=lambda address: address):
+        import torch
+        self.blocks, self.calls = {}, 0
+
+        def alloc(nbytes, _user):
+            self.calls += 1
+            t = torch.empty(int(nbytes) + 256, dtype=torch.uint8, device="cuda")
+            at = make(t.data_ptr())
+            self.blocks[at] = t
+            return at
+
+        def release(ptr, _user):
+            del self.blocks[ptr]
+
+        self.alloc, self.release = ebic.ALLOC_FN(alloc), ebic.RELEASE_FN(release)
+
+
+PER_THREAD = 2  # hipStreamPerThread
+
+
+def test_small_breeding_on_the_per_thread_stream():
+    """One handle stands for a stream of each thread: populations of up to
+    1,024 keep out of the memory that is kept by handle."""
+    import torch
+    ctx = ebic.Context(0, torch_allocator=False)
+    memory = _Allocator()
+    try:
+        ebic.ebic_set_allocator(ctx.handle, memory.alloc, memory.release)
+        rng = np.random.default_rng(1)
+        bs = [_Breeding(ctx, n, seed=n) for n in (700, 1024)]
+        for b in bs:
+            b.set_counts(rng.integers(-1, 50, size=b.n).astype(np.int32))
+        torch.cuda.synchronize()
+
+        def breed(b, times):
+            for _ in range(times):
+                ebic.ebic_ea_breed(ctx.handle, b.params, 1, b.n, b.pop.offsets.data_ptr(), b.pop.cols.data_ptr(),
+                                   b.matched.data_ptr(), *(t.data_ptr() for t in b.out), PER_THREAD)
+            # (a thread's stream goes with it: waited for by itself)
+            torch.cuda.ExternalStream(PER_THREAD).synchronize()
+
+        announce("per-thread stream, one thread")
+        breed(bs[0], 1)
+        assert memory.calls == 0
+        bs[0].check("one thread")
+        announce("per-thread stream, two threads")
+        threads = [threading.Thread(target=breed, args=(b, 50)) for b in bs]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for b in bs:
+            b.check("two threads")
+    finally:
+        ctx.close()
