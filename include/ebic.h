@@ -196,6 +196,9 @@ int64_t ebic_mask_words(int64_t rows);
  * Outputs are fully overwritten. An individual of length < 1 or with a
  * column outside [0, cols) gets matched = negative = -1 and zero mask words;
  * the call still returns EBIC_OK. Asynchronous on `hip_stream`.
+ * Captured into a graph, a call may use the scratch that the context keeps
+ * for the stream (which then stays until ebic_destroy): replay it on that
+ * stream, or while the stream runs no other call of the context.
  */
 ebic_status ebic_eval_population(ebic_ctx *ctx, int32_t matrix, int32_t n_ind,
                                  const int32_t *d_offsets, const int32_t *d_cols,
@@ -516,7 +519,9 @@ ebic_status ebic_ea_step(ebic_ea *ea, const int32_t *matched, int32_t *best_inde
  * stream without the population leaving the device); the input and output
  * populations must not overlap. A parent longer than k_max is read as its
  * first k_max columns; a parent without columns is replaced by a random
- * individual. Errors: EBIC_EINVAL (parameters as for ebic_ea_create,
+ * individual. Captured into a graph: as for ebic_eval_population (of
+ * populations of up to 1,024 whose children fit one workgroup's LDS, a
+ * captured call uses no scratch). Errors: EBIC_EINVAL (parameters as for ebic_ea_create,
  * n_ind != pop_size, generation < 1, a NULL required pointer), EBIC_ENOMEM,
  * EBIC_EHIP; nothing is enqueued on error.
  */

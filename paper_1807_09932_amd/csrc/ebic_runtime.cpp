@@ -721,17 +721,23 @@ class Packer {
 
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes)
 {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const bool captured = hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+    clear_last_error();
     std::lock_guard<std::mutex> lk(ctx->mu);
     Scratch &sc = ctx->scratch[s];
+    sc.captured |= captured;
     if (sc.bytes >= bytes && sc.ptr) return sc.ptr;
     size_t want = std::max<size_t>(bytes, 64 << 10);
     want = std::max(want, sc.bytes * 2);
     if (sc.ptr) {
         // Work already enqueued on this stream may still read the old buffer.
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-        ctx_free(ctx, sc.ptr);
+        if (sc.captured) ctx->captured_scratch.push_back(sc.ptr);
+        else ctx_free(ctx, sc.ptr);
         sc.ptr = nullptr;
         sc.bytes = 0;
+        sc.captured = captured;
     }
     sc.ptr = ctx_alloc(ctx, want);
     sc.bytes = want;
@@ -897,6 +903,8 @@ ebic_status ebic_destroy(ebic_ctx *ctx)
                 ctx_free(ctx, kv.second.sums);
             }
             ctx->scratch.clear();
+            for (void *p : ctx->captured_scratch) ctx_free(ctx, p);
+            ctx->captured_scratch.clear();
             for (int b = 0; b < kUploadSlots; ++b) {
                 if (ctx->up_done[b]) (void)hipEventDestroy(ctx->up_done[b]);
                 if (ctx->up_laid[b]) (void)hipEventDestroy(ctx->up_laid[b]);

@@ -69,6 +69,7 @@ struct FaultPlan {
 struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
+    bool captured = false;  // a graph may hold ptr
     // Accumulators of the one-kernel evaluation in slices: two buffers of
     // kFewInd each, the one the next call sums in (all zero), and how much
     // the calls before may have left in each.
@@ -97,6 +98,9 @@ struct ebic_ctx {
     std::mutex batch_mu;  // guards the batch graph cache (captures run outside it)
     bool batch_state_allocated = false;
     std::map<hipStream_t, ebic::Scratch> scratch;
+    // Outgrown scratch that graphs may hold, kept for their replays until the
+    // context goes (each at most half the next one of its stream).
+    std::vector<void *> captured_scratch;
     // Held while a call takes its stream's scratch and enqueues the kernels
     // that share it: calls of several threads on one stream do not mix.
     std::mutex launch_mu;
@@ -257,7 +261,8 @@ ReqDesc make_desc(const Matrix &m, int32_t n, const int32_t *offsets, const int3
                   uint32_t flags, int32_t *matched, int32_t *negative, uint64_t *mmask,
                   uint64_t *nmask, int32_t staging);
 // At least `bytes` of device scratch private to stream `s` (grown on demand;
-// a grown buffer replaces the old one after the stream has drained).
+// a grown buffer replaces the old one after the stream has drained; one that
+// a capture has been given stays until the context goes).
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes);
 // The context's auxiliary stream (under mu).
 hipStream_t aux_stream(ebic_ctx *ctx);

@@ -153,3 +153,61 @@ def test_small_breeding_on_the_per_thread_stream():
             b.check("two threads")
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("what", ["breeding", "evaluation"])
+def test_captured_scratch_outlives_its_replacement(what):
+    """The scratch that a captured call was given is not released when a
+    larger call on the stream replaces it: replays write it."""
+    import torch
+    rng = np.random.default_rng(2)
+    ctx = ebic.Context(0, torch_allocator=False)
+    memory = _Allocator()
+    try:
+        ebic.ebic_set_allocator(ctx.handle, memory.alloc, memory.release)
+        small, large = _Breeding(ctx, 1500, seed=3), _Breeding(ctx, 9000, seed=4)
+        for b in (small, large):
+            b.set_counts(rng.integers(-1, 50, size=b.n).astype(np.int32))
+        if what == "evaluation":  # (40 panels and no accumulators: two kernels with the headers between them)
+            X = rng.standard_normal((40_000, 20)).astype(np.float32)
+            offs, cols = gen.csr([rng.permutation(20)[:k].astype(np.int32) for k in rng.integers(1, 12, size=100)])
+            mat, pop = ctx.upload(X), ctx.population(offsets=offs, cols=cols)
+            out = ctx.outputs(mat, 100)
+            want = oracle_eval(X, offs, cols, masks=False)
+
+        def call(s):
+            if what == "evaluation":
+                ctx.eval(mat, pop, out=out, stream=s)
+            else:
+                small.breed(ctx, s)
+
+        s = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            call(s)  # (builds what a capture cannot)
+            small.breed(ctx, s)
+            s.synchronize()
+            announce("capture", what)
+            graph.capture_begin()
+            call(s)
+            graph.capture_end()
+        held = set(memory.blocks)
+        for rnd in range(3):
+            for b in (small, large):
+                b.set_counts(rng.integers(-1, 50, size=b.n).astype(np.int32))
+            torch.cuda.synchronize()
+            large.breed(ctx, s)  # (replaces the scratch the first time)
+            assert held < set(memory.blocks)
+            announce("replay on the replaced scratch", what, rnd)
+            with torch.cuda.stream(s):
+                graph.replay()
+            torch.cuda.synchronize()
+            large.check(rnd)
+            if what == "evaluation":
+                assert_same((to_np(out[0]), to_np(out[1]), None, None), want, "replay")
+            else:
+                small.check(rnd)
+    finally:
+        ctx.close()
+    assert not memory.blocks
