@@ -447,8 +447,9 @@ struct PairWave {
     }
 
     // The groups with one of their pairs among the chunk's n_tied listed
-    // ones (lane e of `tie`: entry e). asc: the header's word j in lane j < 7
-    // (kNoPair in lanes without a pair); hit: the lane's own pair is one.
+    // ones (lane e of `tie`: entry e, so that all lanes have to be active).
+    // asc: the header's word j in lane j < 7 (kNoPair in lanes without a
+    // pair); hit: the lane's own pair is one.
     __device__ __forceinline__ bool listed(uint32_t asc, uint32_t tie, uint32_t n_tied, bool &hit) const
     {
         asc &= kHeadOffset;
@@ -611,27 +612,29 @@ struct PairWave {
         bool left = mine;
 #pragma unroll 1
         for (int32_t u = 8; __ballot(left && u < k) != 0; u += 4) {
-            if (left && u < k) {
-                // lane j: column u - 1 + j and the next
-                const uint32_t a = (uint32_t)cc[min(u - 1 + j, k - 1)], b = row_next(a);
-                const uint32_t f = pair_offset(cols, a, b), r = pair_offset(cols, b, a);
-                const uint32_t asc = min(f, r) | (f > r ? 0x80000000u : 0u), sk = a == b ? ~0u : 0u;
-                bool exact = dirty, both = dirty;
-                if (!dirty) {
+            // lane j: column u - 1 + j and the next (a group that is done
+            // reads its individual's last column)
+            const bool now = left && u < k;
+            const uint32_t a = (uint32_t)cc[min(u - 1 + j, k - 1)], b = row_next(a);
+            const uint32_t f = pair_offset(cols, a, b), r = pair_offset(cols, b, a);
+            const uint32_t asc = min(f, r) | (f > r ? 0x80000000u : 0u), sk = a == b ? ~0u : 0u;
+            bool exact = dirty, both = dirty;
+            // (with every lane active: the list is spread over them)
+            if (n_tied) exact = listed(now && j < 4 ? asc : kNoPair, tie, n_tied, both);
+            if (now) {
+                if (!exact) {
                     const auto rs = rsrc(panel);
                     Bits w[4];
                     each<4>([&](auto e) { w[e] = load(rs, line(group_bcast<e>(asc))); });
-                    if (n_tied) exact = listed(j < 4 ? asc : kNoPair, tie, n_tied, both);
-                    if (!exact)
-                        each<4>([&](auto e) {
-                            const uint32_t m = (uint32_t)((int32_t)group_bcast<e>(asc) >> 31), s = group_bcast<e>(sk);
+                    each<4>([&](auto e) {
+                        const uint32_t m = (uint32_t)((int32_t)group_bcast<e>(asc) >> 31), s = group_bcast<e>(sk);
 #pragma unroll
-                            for (int x = 0; x < 4; ++x) {
-                                o.p.w[x] &= (w[e].w[x] ^ m) | s;
-                                if (NEG) o.n.w[x] &= ~(w[e].w[x] ^ m) | s;
-                                asm volatile("" : "+v"(o.p.w[x]), "+v"(o.n.w[x]));
-                            }
-                        });
+                        for (int x = 0; x < 4; ++x) {
+                            o.p.w[x] &= (w[e].w[x] ^ m) | s;
+                            if (NEG) o.n.w[x] &= ~(w[e].w[x] ^ m) | s;
+                            asm volatile("" : "+v"(o.p.w[x]), "+v"(o.n.w[x]));
+                        }
+                    });
                 }
                 if (exact) both_ways<4, true>(o, panel, asc, max(f, r), sk, both);
                 if (COUNT && j == 0) steps += (uint64_t)min(4, k - u);
