@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(1024) k_eval_direct(ReqDesc d, const IndHead *
     const int64_t words32 = 2 * ((d.rows + 63) / 64);
     uint64_t steps = 0;
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(d.X) + row0, (short)0, NEAR ? (int)(uint32_t)((int64_t)d.cols * d.ld - row0) * 4 : 0, 0x00020000);
+        const_cast<float *>(d.X) + row0, (short)0, NEAR ? (int)((uint32_t)((int64_t)d.cols * d.ld - row0) * 4u) : 0, 0x00020000);
     const uint32_t at = NEAR ? (uint32_t)(min(row, d.ld - 4) - row0) * 4u : 0u, stride = (uint32_t)d.ld * 4u;
     auto ld = [&](int32_t c) {
         float4 f;
