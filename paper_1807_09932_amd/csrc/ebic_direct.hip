@@ -303,8 +303,12 @@ int64_t direct_chunks(int64_t rows) { return (rows + kDirectRows - 1) / kDirectR
 hipError_t launch_direct(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,
                          unsigned long long *step_counter, hipStream_t s)
 {
-    const int64_t groups = (d.n + P - 1) / P, per_slice = (direct_chunks(d.rows) + 7) / 8;
-    if (W < 1 || W > 16 || P < 1 || d.ld % 4 != 0 || 8 * groups * W * kWave > 0xffffffffll) return hipErrorInvalidValue;
+    if (W < 1 || W > 16 || P < 1 || d.ld % 4 != 0) return hipErrorInvalidValue;
+    // (a grid's x has less than 2^32 threads: larger groups past that, from
+    // 33.5 million individuals on in the default shape)
+    auto threads = [&] { return 8 * (((int64_t)d.n + P - 1) / P) * W * kWave; };
+    while (threads() > 0xffffffffll) P *= 2;
+    const int64_t groups = ((int64_t)d.n + P - 1) / P, per_slice = (direct_chunks(d.rows) + 7) / 8;
     const bool neg = (d.flags & kFlagNeg) != 0;
     clear_last_error();
     // a slice's chunks over y and z (up to 2^31 rows: 32 z of 32,768)

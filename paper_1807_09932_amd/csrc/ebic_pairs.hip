@@ -1074,9 +1074,14 @@ hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, int32_t S, const FewSum
 hipError_t launch_pairs(const ReqDesc &d, const IndHead *heads, int32_t P, int32_t W,
                         unsigned long long *step_counter, hipStream_t s)
 {
+    if (W < 1 || W > 16 || P < 1 || P > 64 * W) return hipErrorInvalidValue;
+    // (a grid's x has less than 2^32 threads: larger groups past that, up to
+    // 64 individuals per wave)
+    auto threads = [&] { return 8 * (((int64_t)d.n + P - 1) / P) * W * kWave; };
+    while (threads() > 0xffffffffll && P < 64 * W) P = P * 2 < 64 * W ? P * 2 : 64 * W;
+    if (threads() > 0xffffffffll) return hipErrorInvalidValue;
     const int64_t groups = ((int64_t)d.n + P - 1) / P, per_slice = (pair_panels(d.rows) + 7) / 8;
     const int32_t per = (P + W - 1) / W;
-    if (W < 1 || W > 16 || P < 1 || per > 64 || 8 * groups * W * kWave > 0xffffffffll) return hipErrorInvalidValue;
     const bool neg = (d.flags & kFlagNeg) != 0;
     // a slice's panels over y and z (65,535 of each are the grid's limit)
     const unsigned y = (unsigned)(per_slice < 32768 ? per_slice : 32768), z = (unsigned)((per_slice + y - 1) / y);
