@@ -482,8 +482,8 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
                 clear_last_error();
                 try {
                     if (own) base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes));
-                } catch (const Error &e) {
-                    if (e.code != EBIC_ENOMEM) throw;
+                } catch (const Error &) {
+                    // (whatever kept the memory from being had)
                 }
             } else {
                 base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes));

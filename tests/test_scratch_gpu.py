@@ -211,3 +211,22 @@ def test_captured_scratch_outlives_its_replacement(what):
     finally:
         ctx.close()
     assert not memory.blocks
+
+
+@pytest.mark.parametrize("why,make", [("unaligned memory", lambda address: address + 8), ("no memory", lambda _: None)])
+def test_small_breeding_without_memory(why, make):
+    """A population of up to 1,024 is bred whatever the allocator does."""
+    import torch
+    ctx = ebic.Context(0, torch_allocator=False)
+    memory = _Allocator(make)
+    try:
+        ebic.ebic_set_allocator(ctx.handle, memory.alloc, memory.release)
+        b = _Breeding(ctx, 600, seed=6)
+        b.set_counts(np.random.default_rng(6).integers(-1, 50, size=600).astype(np.int32))
+        announce("breeding without memory", why)
+        b.breed(ctx, None)
+        torch.cuda.synchronize()
+        assert memory.calls >= 1
+        b.check(why)
+    finally:
+        ctx.close()
