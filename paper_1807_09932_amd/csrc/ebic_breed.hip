@@ -481,7 +481,7 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
                                  st == hipStreamCaptureStatusNone;
                 clear_last_error();
                 try {
-                    if (own) base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes));
+                    if (own) base = static_cast<unsigned char *>(stream_scratch(ctx, s, l_bytes + s_bytes, true));
                 } catch (const Error &) {
                     // (whatever kept the memory from being had)
                 }

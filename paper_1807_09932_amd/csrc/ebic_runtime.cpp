@@ -719,7 +719,7 @@ class Packer {
 
 }  // namespace
 
-void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes)
+void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes, bool spare)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     const bool captured = hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
@@ -727,6 +727,7 @@ void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes)
     std::lock_guard<std::mutex> lk(ctx->mu);
     Scratch &sc = ctx->scratch[s];
     sc.captured |= captured;
+    sc.spare &= spare;
     if (sc.bytes >= bytes && sc.ptr) return sc.ptr;
     size_t want = std::max<size_t>(bytes, 64 << 10);
     want = std::max(want, sc.bytes * 2);
@@ -755,6 +756,7 @@ static Scratch *few_sums(ebic_ctx *ctx, hipStream_t s, FewSums &sums)
         return nullptr;
     std::lock_guard<std::mutex> lk(ctx->mu);
     Scratch &sc = ctx->scratch[s];
+    sc.spare = false;
     if (!sc.sums) {
         const size_t bytes = 2 * (size_t)kFewInd * sizeof(uint64_t);
         void *p = nullptr;
@@ -926,10 +928,19 @@ ebic_status ebic_set_allocator(ebic_ctx *ctx, void *(*alloc)(size_t, void *),
         if (!ctx) fail(EBIC_EINVAL, "ctx is NULL");
         if ((alloc == nullptr) != (release == nullptr))
             fail(EBIC_EINVAL, "alloc and release must both be set or both be NULL");
+        std::lock_guard<std::mutex> lkl(ctx->launch_mu);  // (no call between taking scratch and its launches)
         std::lock_guard<std::mutex> lk(ctx->mu);
-        if (!ctx->matrices.empty() || ctx->batch_state_allocated || ctx->d_step_counter ||
-            !ctx->scratch.empty())
+        const bool in_use = std::any_of(ctx->scratch.begin(), ctx->scratch.end(),
+                                        [](const auto &kv) { return !kv.second.spare; });
+        if (!ctx->matrices.empty() || ctx->batch_state_allocated || ctx->d_step_counter || in_use)
             fail(EBIC_EBUSY, "allocator can only change while nothing is resident");
+        // (calls that could do without left the rest)
+        if (!ctx->scratch.empty()) {
+            DeviceGuard g(ctx->device);
+            hip_check(hipDeviceSynchronize(), "hipDeviceSynchronize");
+            for (auto &kv : ctx->scratch) ctx_free(ctx, kv.second.ptr);
+            ctx->scratch.clear();
+        }
         ctx->alloc = alloc;
         ctx->release = release;
         ctx->alloc_user = user;

@@ -70,6 +70,7 @@ struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
     bool captured = false;  // a graph may hold ptr
+    bool spare = true;      // every call that took it could do without
     // Accumulators of the one-kernel evaluation in slices: two buffers of
     // kFewInd each, the one the next call sums in (all zero), and how much
     // the calls before may have left in each.
@@ -262,8 +263,10 @@ ReqDesc make_desc(const Matrix &m, int32_t n, const int32_t *offsets, const int3
                   uint64_t *nmask, int32_t staging);
 // At least `bytes` of device scratch private to stream `s` (grown on demand;
 // a grown buffer replaces the old one after the stream has drained; one that
-// a capture has been given stays until the context goes).
-void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes);
+// a capture has been given stays until the context goes). spare: the call can
+// do without (scratch that only such calls have taken does not keep the
+// allocator from being changed).
+void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes, bool spare = false);
 // The context's auxiliary stream (under mu).
 hipStream_t aux_stream(ebic_ctx *ctx);
 // The upload's pinned host buffers, at least `bytes` each (under mu), and

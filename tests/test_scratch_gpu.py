@@ -1,6 +1,7 @@
 """The device memory that calls on a stream share (headers, children's slots):
 which calls keep out of it."""
 import ctypes
+import gc
 import threading
 
 import numpy as np
@@ -18,6 +19,13 @@ def ctx():
     c = Context(0)
     yield c
     c.close()
+
+
+@pytest.fixture(autouse=True)
+def _no_garbage():
+    """Device memory in reference cycles goes with the test that made it."""
+    yield
+    gc.collect()
 
 
 class _Breeding:
@@ -230,3 +238,35 @@ def test_small_breeding_without_memory(why, make):
         b.check(why)
     finally:
         ctx.close()
+
+
+def test_allocator_changes_after_a_small_breeding():
+    """With no matrix resident the allocator may change; the scratch of a
+    breeding that could do without goes back to the one that made it. One of a
+    larger population stays in use."""
+    import torch
+    ctx = ebic.Context(0, torch_allocator=False)
+    first, second = _Allocator(), _Allocator()
+    rng = np.random.default_rng(7)
+    try:
+        ebic.ebic_set_allocator(ctx.handle, first.alloc, first.release)
+        small, large = _Breeding(ctx, 1000, seed=8), _Breeding(ctx, 1500, seed=9)
+        for b in (small, large):
+            b.set_counts(rng.integers(-1, 50, size=b.n).astype(np.int32))
+        for memory in (first, second):
+            announce("breed, then change the allocator")
+            small.breed(ctx, None)
+            assert memory.calls == 1
+            ebic.ebic_set_allocator(ctx.handle, second.alloc, second.release)
+            assert not memory.blocks
+            torch.cuda.synchronize()
+            small.check("small")
+        large.breed(ctx, None)
+        with pytest.raises(ebic.EbicError) as e:
+            ebic.ebic_set_allocator(ctx.handle, first.alloc, first.release)
+        assert e.value.status == ebic.EBIC_EBUSY
+        torch.cuda.synchronize()
+        large.check("large")
+    finally:
+        ctx.close()
+    assert first.calls == 1 and not second.blocks
