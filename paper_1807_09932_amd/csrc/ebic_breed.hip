@@ -466,7 +466,7 @@ extern "C" ebic_status ebic_ea_breed(ebic_ctx *ctx, const ebic_ea_params *params
         const bool small = n <= 1024 && small_lds + 1024 * sizeof(int32_t) <= ctx->lds_per_block;
         // Scratch and launches go out together: the stream's scratch is
         // shared with the evaluations on it.
-        std::lock_guard<std::mutex> lk(ctx->launch_mu);
+        const std::unique_lock<std::mutex> lk = launch_lock(ctx, s);
         if (p.k_max <= kWave) {
             unsigned char *base = nullptr;
             if (small) {

@@ -719,6 +719,16 @@ class Packer {
 
 }  // namespace
 
+std::unique_lock<std::mutex> launch_lock(ebic_ctx *ctx, hipStream_t s)
+{
+    std::mutex *m;
+    {
+        std::lock_guard<std::mutex> lk(ctx->mu);
+        m = &ctx->launch_mu[s];
+    }
+    return std::unique_lock<std::mutex>(*m);
+}
+
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes, bool spare)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -745,7 +755,7 @@ void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes, bool spare)
     return sc.ptr;
 }
 
-// The stream's accumulators for a call in slices (under launch_mu), or NULL
+// The stream's accumulators for a call in slices (under its lock), or NULL
 // if it has none: where they cannot be had, in a capture (its replays could
 // run beside the stream's own calls) and on the per-thread stream (one handle,
 // many streams).
@@ -792,12 +802,12 @@ hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &pla
         mode = ctx->prof_mode;
         if (mode & 2) counter = ctx->d_step_counter;
     }
-    std::unique_lock<std::mutex> lkl(ctx->launch_mu, std::defer_lock);
+    std::unique_lock<std::mutex> lkl;
     LaunchCfg cfg = planned;
     IndHead *heads = nullptr;
     FewSums sums;
     Scratch *used = nullptr;
-    if (cfg.few != 1) lkl.lock();
+    if (cfg.few != 1) lkl = launch_lock(ctx, s);
     if (cfg.few > 1 && !(used = few_sums(ctx, s, sums))) without_sums(cfg);
     if (cfg.few == 0) heads = static_cast<IndHead *>(stream_scratch(ctx, s, (size_t)d.n * sizeof(IndHead)));
     fault_point_launch(ctx, "evaluation launch");
@@ -928,8 +938,20 @@ ebic_status ebic_set_allocator(ebic_ctx *ctx, void *(*alloc)(size_t, void *),
         if (!ctx) fail(EBIC_EINVAL, "ctx is NULL");
         if ((alloc == nullptr) != (release == nullptr))
             fail(EBIC_EINVAL, "alloc and release must both be set or both be NULL");
-        std::lock_guard<std::mutex> lkl(ctx->launch_mu);  // (no call between taking scratch and its launches)
-        std::lock_guard<std::mutex> lk(ctx->mu);
+        std::unique_lock<std::mutex> lk(ctx->mu);
+        // (no call is between taking scratch and its launches)
+        std::vector<std::unique_lock<std::mutex>> idle;
+        for (;;) {
+            for (auto &kv : ctx->launch_mu) {
+                idle.emplace_back(kv.second, std::try_to_lock);
+                if (!idle.back().owns_lock()) break;
+            }
+            if (idle.empty() || idle.back().owns_lock()) break;
+            idle.clear();
+            lk.unlock();  // (that call may be waiting for it)
+            std::this_thread::yield();
+            lk.lock();
+        }
         const bool in_use = std::any_of(ctx->scratch.begin(), ctx->scratch.end(),
                                         [](const auto &kv) { return !kv.second.spare; });
         if (!ctx->matrices.empty() || ctx->batch_state_allocated || ctx->d_step_counter || in_use)

@@ -103,8 +103,10 @@ struct ebic_ctx {
     // context goes (each at most half the next one of its stream).
     std::vector<void *> captured_scratch;
     // Held while a call takes its stream's scratch and enqueues the kernels
-    // that share it: calls of several threads on one stream do not mix.
-    std::mutex launch_mu;
+    // that share it: calls of several threads on one stream do not mix, and
+    // those on different streams do not wait for each other. Made on a
+    // stream's first call (under mu), kept until the context goes.
+    std::map<hipStream_t, std::mutex> launch_mu;
     // Diagnostics (ebic_set_profiling / ebic_read_profile).
     int32_t prof_mode = 0;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
@@ -261,6 +263,8 @@ LaunchCfg plan_eval(ebic_ctx *ctx, Matrix &m, int32_t n, int64_t nnz, uint32_t f
 ReqDesc make_desc(const Matrix &m, int32_t n, const int32_t *offsets, const int32_t *cols,
                   uint32_t flags, int32_t *matched, int32_t *negative, uint64_t *mmask,
                   uint64_t *nmask, int32_t staging);
+// The stream's lock, taken (not under mu).
+std::unique_lock<std::mutex> launch_lock(ebic_ctx *ctx, hipStream_t s);
 // At least `bytes` of device scratch private to stream `s` (grown on demand;
 // a grown buffer replaces the old one after the stream has drained; one that
 // a capture has been given stays until the context goes). spare: the call can
