@@ -260,7 +260,8 @@ ebic_status ebic_eval_batch(ebic_ctx *ctx, const ebic_request *reqs, int32_t n_r
  * Time the candidate launch shapes on `sample` (a representative batch whose
  * outputs are overwritten) and store the fastest for the sample's shape class
  * in the context; if cache_path is not NULL, also merge it into that JSON
- * file, which later contexts read at creation when EBIC_TUNE_CACHE names it.
+ * file, which later contexts read at creation when EBIC_TUNE_CACHE names it
+ * (entries that a build with other kernels saved are skipped).
  * Synchronises the device.
  */
 ebic_status ebic_autotune(ebic_ctx *ctx, const ebic_request *sample, int32_t n_reqs,

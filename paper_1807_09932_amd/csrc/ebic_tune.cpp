@@ -171,6 +171,13 @@ static bool read_int(const std::string &obj, const char *key, int32_t *out)
     return true;
 }
 
+// What the entries of a cache file mean and were compared with: counted up
+// when a shape's numbers or the kernels behind them change (2: the pair
+// bitmaps by eight individuals per wave step, direct reads by 256 rows). A
+// file of another number gives no entries: a shape that was the fastest of
+// other kernels is often several times slower than the default of these.
+constexpr int32_t kTuneShapes = 2;
+
 static void read_cache(std::map<TuneKey, LaunchCfg> &out, const std::string &path)
 {
     std::ifstream f(path);
@@ -179,7 +186,8 @@ static void read_cache(std::map<TuneKey, LaunchCfg> &out, const std::string &pat
     ss << f.rdbuf();
     const std::string s = ss.str();
     size_t pos = s.find("\"entries\"");
-    if (pos == std::string::npos) return;
+    int32_t shapes = 0;
+    if (pos == std::string::npos || !read_int(s.substr(0, pos), "shapes", &shapes) || shapes != kTuneShapes) return;
     while (true) {
         size_t a = s.find('{', pos);
         if (a == std::string::npos) break;
@@ -209,14 +217,15 @@ void load_tune_cache(ebic_ctx *ctx, const std::string &path) { read_cache(ctx->t
 
 static void save_tune_cache(ebic_ctx *ctx, const std::string &path)
 {
-    // Merge: entries already in the file stay unless re-tuned here.
+    // Merge: entries already in the file stay unless re-tuned here (or of
+    // other shapes).
     std::map<TuneKey, LaunchCfg> merged;
     read_cache(merged, path);
     for (auto &kv : ctx->tuned) merged[kv.first] = kv.second;
     const std::string tmp_path = path + ".tmp";
     FILE *f = std::fopen(tmp_path.c_str(), "w");
     if (!f) fail(EBIC_EINVAL, "cannot write " + tmp_path);
-    std::fprintf(f, "{\"arch\": \"%s\", \"entries\": [\n", ctx->arch.c_str());
+    std::fprintf(f, "{\"arch\": \"%s\", \"shapes\": %d, \"entries\": [\n", ctx->arch.c_str(), kTuneShapes);
     size_t i = 0;
     for (auto &kv : merged) {
         std::fprintf(f,
