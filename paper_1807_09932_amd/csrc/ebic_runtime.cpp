@@ -180,6 +180,16 @@ hipStream_t aux_stream(ebic_ctx *ctx)
     return ctx->aux;
 }
 
+// (a wait is refused while a capture runs that forbids it; the work to wait
+// for is outside that capture)
+static void drain(hipStream_t s)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    (void)hipStreamSynchronize(s);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
+
 bool codes_buildable(const Matrix &m, bool include)
 {
     return m.dev.cols <= kMaxCodeCols && (!include || m.Xfill != nullptr);
@@ -198,7 +208,7 @@ void build_fp16_codes(ebic_ctx *ctx, Matrix &m, bool include)
         hip_check(launch_codes(include ? m.Xfill : m.X, m.dev.rows, m.dev.ld, m.dev.cols, C, s), "codes kernel");
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
     } catch (...) {
-        if (s) (void)hipStreamSynchronize(s);
+        if (s) drain(s);
         ctx_free(ctx, C);
         throw;
     }
@@ -239,7 +249,7 @@ void build_half_codes(ebic_ctx *ctx, Matrix &m)
         hip_check(hipMemcpyAsync(&has_nan, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
     } catch (...) {
-        if (s) (void)hipStreamSynchronize(s);
+        if (s) drain(s);
         ctx_free(ctx, Hc);
         throw;
     }
@@ -303,7 +313,7 @@ void build_pairs(ebic_ctx *ctx, Matrix &m, bool include)
                   "pair bitmaps kernel");
         hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
     } catch (...) {
-        if (s) (void)hipStreamSynchronize(s);
+        if (s) drain(s);
         ctx_free(ctx, G);
         throw;
     }
@@ -1142,8 +1152,8 @@ ebic_status ebic_upload_matrix(ebic_ctx *ctx, const float *src, int64_t rows, in
                 hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
             }
         } catch (...) {
-            if (aux) (void)hipStreamSynchronize(aux);
-            (void)hipStreamSynchronize(s);  // nothing in flight reads what is freed
+            if (aux) drain(aux);
+            drain(s);  // nothing in flight reads what is freed
             ctx_free(ctx, staging);
             ctx_free(ctx, m.X);
             ctx_free(ctx, m.Xfill);
