@@ -1000,6 +1000,12 @@ ebic_status ebic_upload_matrix(ebic_ctx *ctx, const float *src, int64_t rows, in
 
         const auto t_start = std::chrono::steady_clock::now();
         DeviceGuard g(ctx->device);
+        // (an upload waits for its stream: refused before the copies' stream,
+        // which other calls use, would join the capture)
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone)
+            fail(EBIC_EHIP, "a matrix cannot be uploaded on a stream under capture");
+        clear_last_error();
         std::lock_guard<std::mutex> lk(ctx->mu);
         Matrix m;
         m.dev.rows = rows;

@@ -1,12 +1,13 @@
 """What a call under a stream capture cannot do, and how it leaves what it
-touched: a layout built on first use is waited for before its memory goes."""
+touched: a layout built on first use is waited for before its memory goes, and
+an upload is refused before anything joins the capture."""
 import ctypes
 
 import numpy as np
 import pytest
 
 from paper_1807_09932_amd import ebic, gen
-from tests.gpu_common import announce, assert_same, gpu_eval, oracle_eval
+from tests.gpu_common import announce, assert_same, gpu_eval, oracle_eval, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -81,5 +82,35 @@ def test_failed_first_use_is_waited_for():
             assert len(seen) == 1
             assert bool((copy == seen[0][:size]).all())
         assert_same(gpu_eval(ctx, mat, offs, cc, masks=False), oracle_eval(X, offs, cc, masks=False), "afterwards")
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("where", ["host", "device"])
+def test_upload_in_a_capture(where):
+    """Refused as ever, with the capture left intact; uploads and first uses
+    go on beside it and after it."""
+    import torch
+    rng = np.random.default_rng(2)
+    X = rng.random((60_000, 150), dtype=np.float32)  # (36 MB: several chunks)
+    offs, cc = gen.csr([rng.permutation(150)[:5].astype(np.int32) for _ in range(50)])
+    want = oracle_eval(X, offs, cc, masks=False)
+    src = torch.from_numpy(X).cuda() if where == "device" else X
+    ctx, s, side = ebic.Context(0), torch.cuda.Stream(), torch.cuda.Stream()
+    try:
+        first = ctx.upload(X)  # (its bitmaps are not built yet)
+        pop, out = ctx.population(offsets=offs, cols=cc), ctx.outputs(first, 50)
+        torch.cuda.synchronize()
+        announce("upload in a capture", where)
+        with _Capture(s, RELAXED) as c:
+            with pytest.raises(ebic.EbicError) as e:
+                ctx.upload(src, stream=s)
+            assert e.value.status == ebic.EBIC_EHIP
+            ctx.eval(first, pop, out=out, stream=side)
+        assert c.status == 0
+        torch.cuda.synchronize()
+        assert_same((to_np(out[0]), to_np(out[1]), None, None), want, "beside the capture")
+        second = ctx.upload(src, stream=s)
+        assert_same(gpu_eval(ctx, second, offs, cc, masks=False), want, "after it")
     finally:
         ctx.close()
