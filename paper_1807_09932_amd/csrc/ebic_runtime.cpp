@@ -741,9 +741,12 @@ std::unique_lock<std::mutex> launch_lock(ebic_ctx *ctx, hipStream_t s)
 
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes, bool spare)
 {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    const bool captured = hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
-    clear_last_error();
+    bool captured = false;
+    if (!spare) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        captured = hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+        clear_last_error();
+    }
     std::lock_guard<std::mutex> lk(ctx->mu);
     Scratch &sc = ctx->scratch[s];
     sc.captured |= captured;
@@ -807,17 +810,19 @@ hipError_t ctx_launch_eval(ebic_ctx *ctx, const ReqDesc &d, const LaunchCfg &pla
 {
     int32_t mode;
     unsigned long long *counter = nullptr;
+    std::mutex *launch_mu = nullptr;
     {
         std::lock_guard<std::mutex> lk(ctx->mu);
         mode = ctx->prof_mode;
         if (mode & 2) counter = ctx->d_step_counter;
+        if (planned.few != 1) launch_mu = &ctx->launch_mu[s];
     }
     std::unique_lock<std::mutex> lkl;
     LaunchCfg cfg = planned;
     IndHead *heads = nullptr;
     FewSums sums;
     Scratch *used = nullptr;
-    if (cfg.few != 1) lkl = launch_lock(ctx, s);
+    if (launch_mu) lkl = std::unique_lock<std::mutex>(*launch_mu);
     if (cfg.few > 1 && !(used = few_sums(ctx, s, sums))) without_sums(cfg);
     if (cfg.few == 0) heads = static_cast<IndHead *>(stream_scratch(ctx, s, (size_t)d.n * sizeof(IndHead)));
     fault_point_launch(ctx, "evaluation launch");

@@ -268,8 +268,8 @@ std::unique_lock<std::mutex> launch_lock(ebic_ctx *ctx, hipStream_t s);
 // At least `bytes` of device scratch private to stream `s` (grown on demand;
 // a grown buffer replaces the old one after the stream has drained; one that
 // a capture has been given stays until the context goes). spare: the call can
-// do without (scratch that only such calls have taken does not keep the
-// allocator from being changed).
+// do without, and is not captured (scratch that only such calls have taken
+// does not keep the allocator from being changed).
 void *stream_scratch(ebic_ctx *ctx, hipStream_t s, size_t bytes, bool spare = false);
 // The context's auxiliary stream (under mu).
 hipStream_t aux_stream(ebic_ctx *ctx);
