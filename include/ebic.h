@@ -248,7 +248,9 @@ typedef struct ebic_request {
  * lengths, from many concurrent EBIC runs, over one or several resident
  * matrices -- in one replay of a captured HIP graph: requests on matrices
  * that take the pair bitmaps (staging 6, built here on first use) in one
- * fixed-grid kernel, the others in one persistent tiled kernel. Each
+ * fixed-grid kernel, the others in one persistent tiled kernel (those of
+ * more than 512 columns among them: one population there is faster alone,
+ * in ebic_eval_population's own kernel for such widths). Each
  * request's outputs equal those of ebic_eval_population on the same inputs.
  * `reqs` is a host array of n_reqs entries (read before the call returns).
  * Asynchronous on `hip_stream`.
@@ -346,8 +348,10 @@ ebic_status ebic_plan_batch_shape(ebic_ctx *ctx, const ebic_request *reqs, int32
  * Measurement diagnostics. `mode` bit 0: record a HIP event pair on the
  * caller's stream around every evaluation kernel this context launches;
  * bit 1: count executed predicate steps (one step = one column of one
- * individual compared on one 64-row tile), using a counting variant of the
- * kernel that is slower and meant for an untimed run. 0 turns both off.
+ * individual compared on one 64-row tile; on the pair bitmaps, one pair of
+ * an individual's columns on 1,024 rows, seven of them for its window), using
+ * a counting variant of the kernel that is slower and meant for an untimed
+ * run. 0 turns both off.
  */
 ebic_status ebic_set_profiling(ebic_ctx *ctx, int32_t mode);
 

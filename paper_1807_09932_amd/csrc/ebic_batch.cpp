@@ -239,6 +239,9 @@ static Plan plan_batch(ebic_ctx *ctx, const ebic_request *reqs, int32_t n_reqs, 
         auto fits = [&](int32_t stg) {
             return tile_lds_bytes(batch_tiles(stg, c.L), m.dev.cols, stg) + count_lds_bytes(c.P) <= lds_max;
         };
+        // (Past 512 columns a request takes the FP32 tile where it fits, else
+        // one row per lane from memory: the kernel that one population takes
+        // there, ebic_direct.hip, has no batched form.)
         int32_t staging = STAGE_DIRECT;
         const bool codes_ok = have_codes && c.L >= 2 && fits(STAGE_CODES);
         const bool wants_swar = c.staging == STAGE_BYTES || c.staging == STAGE_HALVES || c.staging == STAGE_T10;
@@ -452,7 +455,7 @@ static std::unique_ptr<GraphEntry> capture_graph(ebic_ctx *ctx, const GraphSpec 
             check(hipEventCreateWithFlags(&g->done[i], hipEventDisableTiming), "hipEventCreate");
         }
         char *da = static_cast<char *>(g->d_arena);
-        const int prep_blocks = std::max(1, ctx->cu_count * 8);  // four waves each, one individual per wave
+        const int prep_blocks = std::max(1, ctx->cu_count * 8);  // four waves each, four individuals per wave and step
         unsigned long long *counter = count ? ctx->d_step_counter : nullptr;
         check(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking), "hipStreamCreate");
         check(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed), "hipStreamBeginCapture");

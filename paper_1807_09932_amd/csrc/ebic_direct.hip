@@ -95,7 +95,7 @@ __device__ __forceinline__ void first_columns(uint64_t &p, uint64_t &n, float x0
                      "v_cmpx_le_f32_e32 vcc, %[x5], %[x4]\n\t"
                      "s_mov_b64 %[n], exec\n\t"
                      "s_mov_b64 exec, %[all]\n\t"
-                     "s_nop 1"  // (four wait states from a VALU write of EXEC to a lane access)
+                     "s_nop 1"  // (four wait states from a VALU write of EXEC to a lane access; no DPP move follows)
                      : [p] "+s"(p), [n] "+s"(n), [all] "=&s"(all)
                      : [x0] "v"(x0), [x1] "v"(x1), [x2] "v"(x2), [x3] "v"(x3), [x4] "v"(x4), [x5] "v"(x5)
                      : "vcc");

@@ -251,9 +251,9 @@ hipError_t launch_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, 
 constexpr int64_t kUploadUnit = 1536;
 
 // Byte rank codes of rows [r0, r1) of a column-major matrix (cols <=
-// kMaxByteCols; r0 a multiple of kUploadUnit, r1 too or ldb), with missing cells replaced by `fill`, into B (ldb bytes
-// per column, ldb a multiple of 512, the interleaved order above; padding
-// rows get 0). *has_nan (device int, zeroed by the caller) is set to 1 if
+// kMaxByteCols; r0 a multiple of kUploadUnit, r1 too or ldb), with missing
+// cells replaced by `fill`, into B (ldb bytes per column, ldb a multiple of
+// 512, the interleaved order above; padding rows get 0). *has_nan (device int, zeroed by the caller) is set to 1 if
 // any cell is missing; ties[g] (ldb / 512 device ints, zeroed by the
 // caller) is set to 1 if some row of rows [512 g, 512 g + 512) holds two
 // equal values.
@@ -261,15 +261,19 @@ hipError_t launch_byte_codes(const float *X, int64_t rows, int64_t ld, int32_t c
                              uint8_t *B, int64_t ldb, int32_t *has_nan, int32_t *ties, int64_t r0, int64_t r1,
                              hipStream_t s);
 
-// The same for 16-bit codes of all rows (cols <= kMaxCodeCols) into Hc, ldh bytes per
-// column (a multiple of 512), in their interleaved order.
+// The same for 16-bit codes of all rows (cols <= kMaxCodeCols) into Hc, ldh
+// bytes per column (a multiple of 512), in their interleaved order.
 hipError_t launch_half_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
                              uint8_t *Hc, int64_t ldh, int32_t *has_nan, int32_t *ties, hipStream_t s);
 
-// The same for 10-bit codes (cols <= kMaxT10Cols; r1 up to the last group's
-// end) into T10, ld10 bytes per
-// column (256 per 192-row group; T10 zeroed by the caller, the fields are
-// OR-ed in), and one tie flag per 192-row group.
+// The same for 10-bit codes of rows [r0, r1) (cols <= kMaxT10Cols; r1 up to
+// the last group's end) into T10, ld10 bytes per column (256 per 192-row
+// group; T10 zeroed by the caller, the fields are OR-ed in), and one tie flag
+// per 192-row group.
+hipError_t launch_t10_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
+                            uint8_t *T10, int64_t ld10, int32_t *has_nan, int32_t *ties, int64_t r0, int64_t r1,
+                            hipStream_t s);
+
 // Clears the calling thread's last HIP error before a launch, so that the
 // hipGetLastError() after it reports that launch's own error (not one an
 // earlier call left, such as an ignored error of a release path).
@@ -278,7 +282,8 @@ inline void clear_last_error() { (void)hipGetLastError(); }
 // Pairwise order bitmaps (ebic_pairs.hip): words per pair for `rows`, the
 // build of every pair's words from a column-major matrix (subst: NaN takes
 // `fill` first; full: both orientations of every pair, needed where a cell
-// may be missing or has been substituted) with each 2,048-row chunk's list of tied pairs and NaN flag
+// may be missing or has been substituted) with each 2,048-row chunk's list
+// of tied pairs and NaN flag
 // in T (pair_tie_bytes, zeroed by the caller), the prep kernel writing the
 // pairs headers, and the evaluation kernel (ReqDesc: B = the words, T = the
 // tie lists).
@@ -301,7 +306,6 @@ constexpr int32_t kFewInd = 4096;
 hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, int32_t S, const FewSums &sums,
                             unsigned long long *step_counter, hipStream_t s);
 constexpr int32_t kPairDefaultW = 2;  // waves per block of the default plain shape
-hipError_t launch_pairs_few(const ReqDesc &d, int32_t W, unsigned long long *step_counter, hipStream_t s);
 int64_t pair_panels(int64_t rows);  // 1,024-row panels (the evaluation's unit of rows)
 
 // The pair items of a batch: eight lists, one per XCD slice (a slice: the
@@ -331,9 +335,6 @@ hipError_t launch_pairs_batch(const PairQueues *pq, const ReqDesc *descs, const 
                               const int32_t *seg_req, const int32_t *seg_gstart, const IndHead *heads,
                               uint32_t *next, int32_t W, int32_t grid, unsigned long long *step_counter, hipStream_t s);
 int pairs_batch_occupancy(int32_t W);  // blocks per CU of the batched pairs kernel
-hipError_t launch_t10_codes(const float *X, int64_t rows, int64_t ld, int32_t cols, float fill,
-                            uint8_t *T10, int64_t ld10, int32_t *has_nan, int32_t *ties, int64_t r0, int64_t r1,
-                            hipStream_t s);
 
 // Zero rows [rows, ld) of every column of a column-major matrix.
 hipError_t launch_zero_pad(float *dst, int64_t rows, int64_t ld, int32_t cols, hipStream_t s);

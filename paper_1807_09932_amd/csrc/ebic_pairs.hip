@@ -65,8 +65,8 @@
 //   - L2 misses. A panel of 256 columns in one orientation is 4.2 MB, about
 //     an XCD's L2; a chunk in both was 16.8 MB, read 3.6 times over.
 // 436,444 x 64, 800 individuals 38.6 -> 31.6 us an evaluation, x 310 51 ->
-// 49 us (there 266 MB of distinct words come from HBM at about 5.5 TB/s),
-// the batch 822 -> 383 us. Four individuals of 16 lanes (8-byte loads): 38,
+// 50 us (there 263 MB of distinct lines come from HBM at about 5.5 TB/s),
+// the batch 822 -> 379 us. Four individuals of 16 lanes (8-byte loads): 38,
 // 57 and 585 us.
 #include <hip/hip_runtime.h>
 
@@ -79,12 +79,14 @@
 namespace ebic {
 namespace {
 
-constexpr int kChunkRows = 2048;  // rows per wave step: 64 lanes x 32 rows
+constexpr int kChunkRows = 2048;  // rows of one tie list, and of a build wave: 64 lanes x 32 rows
 constexpr int kChunkWords = 64;
-constexpr int kTieWords = 128;    // per chunk: count, NaN flag, ..., 64 listed offsets
+constexpr int kTieWords = 128;    // per chunk: count, NaN flag, ..., up to 32 listed offsets
 constexpr int kTieList = 64;      // (the list's first word)
 constexpr int kTieMax = 32;       // pairs it holds
-constexpr uint32_t kNoPair = kHeadOffset;  // no pair's offset (1,024 columns end below it)
+// No listed pair's offset (of 1,024 columns the last diagonal pair has it,
+// and lists hold pairs a < b only).
+constexpr uint32_t kNoPair = kHeadOffset;
 constexpr int kPanelRows = 1024;  // rows of one step: 8 lanes x 128 rows
 constexpr int kPanelWords = 32;
 constexpr int kGroup = 8;         // lanes per individual (16 bytes of a pair's line each)
@@ -619,7 +621,8 @@ struct PairWave {
             const uint32_t f = pair_offset(cols, a, b), r = pair_offset(cols, b, a);
             const uint32_t asc = min(f, r) | (f > r ? 0x80000000u : 0u), sk = a == b ? ~0u : 0u;
             bool exact = dirty, both = dirty;
-            // (with every lane active: the list is spread over them)
+            // (with every lane active: the list is spread over them; before
+            // the loads, whose registers the lookup would have to share)
             if (n_tied) exact = listed(now && j < 4 ? asc : kNoPair, tie, n_tied, both);
             if (now) {
                 if (!exact) {

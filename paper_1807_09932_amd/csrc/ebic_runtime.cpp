@@ -1,6 +1,6 @@
 // ebic_runtime.cpp -- the C ABI declared in include/ebic.h: contexts, the
 // resident-matrix registry, argument validation, launch planning and error
-// reporting. Kernels live in ebic_kernels.hip.
+// reporting. Kernels live in the .hip files beside it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
