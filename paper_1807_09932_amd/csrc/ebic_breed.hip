@@ -213,8 +213,8 @@ __device__ __forceinline__ void wave_mutate(const ebic_ea_params &p, breed::Rng 
 // parents' columns in a second, and stores its slot. Bound by that chain of
 // loads and by the draws (a 64-bit multiply chain). At 1,600 individuals of
 // 2-30 columns ranks, elites and children took 4.6 + 97 + 63 us as three
-// launches (a thread per individual) and now take 7.5 us; at 800 the
-// one-workgroup kernel took 76-107 us against 5.6 us.
+// launches (a thread per individual) and now take 7.3 us; at 800 the
+// one-workgroup kernel took 76-107 us against 5.3 us.
 template <int I>
 __global__ void __launch_bounds__(kThreads) k_breed_waves(ebic_ea_params p, int64_t generation, int32_t n,
                                                           const int32_t *__restrict__ offsets,
@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(kThreads) k_breed_waves(ebic_ea_params p, int6
 // most 64) children; its threads sum the lengths before them, each wave
 // scans the block's own, and the waves copy the children in turn. Every
 // block sums the lengths from the start (6 KB at 1,600 individuals): one
-// launch of 3.9 us instead of a scan and a copy (4.8 + 6.1 us) at 1,600.
+// launch of 3.2 us instead of a scan and a copy (4.8 + 6.1 us) at 1,600.
 __global__ void __launch_bounds__(kThreads) k_breed_pack(int32_t n, int32_t k_max, int32_t per,
                                                          const int32_t *__restrict__ slots,
                                                          const int32_t *__restrict__ lens,

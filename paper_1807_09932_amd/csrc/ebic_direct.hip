@@ -15,10 +15,10 @@
 // added to the outputs once at the end.
 //
 // Every individual reads its first columns on every row, from the L2 as far
-// as it holds them: 0.39 GB at 20,000 x 900 with 800 individuals, about 17
-// TB/s. Bound by instruction issue, per individual and 256 rows 92 vector
-// and 129 scalar ones (115 and 161 with 64-bit addresses and an AND for
-// every compare: 30.3 us an evaluation; 109 and 122 with buffer loads, a
+// as it holds them: 0.36 GB at 20,000 x 900 with 800 individuals, 15 TB/s
+// over the kernel's 24 us. Bound by instruction issue, per individual and 256
+// rows 93 vector and 131 scalar ones (115 and 161 with 64-bit addresses and
+// an AND for every compare: 30.3 us an evaluation; 109 and 122 with buffer loads, a
 // column's address a 32-bit scalar offset: 27.7; 26.3 with the first
 // compares narrowing the execution mask as well). Blocks are placed as
 // those of the pair bitmaps: the blocks of a 256-row chunk run on one XCD
